@@ -203,7 +203,7 @@ def decode_bench(args, wl, shape, model, ids, sched, n_tokens, torch, B) -> int:
             gu_bytes = 2.0 * 2.0 * shape.d_ffn * shape.d_model
             achieved = gu_bytes / (gu_ms / gu_n * 1e-3) / 1e9
             prof = {"ms_by_step": {k: round(v[0], 4) for k, v in sorted(by.items(), key=lambda kv: -kv[1][0])},
-                    "roofline": {"bound": "hbm", "kernel": "gemm_skinny_kernel<EPI_SWIGLU> (gate/up projection, one token row)",
+                    "roofline": {"bound": "hbm", "kernel": "gemm_stream_kernel<EPI_SWIGLU> (gate/up projection, one token row)",
                                  "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                  "frac": round(achieved / PEAK_HBM_GBS, 4), "avg_launch_ms": round(gu_ms / gu_n, 5),
                                  "algorithmic_bytes_per_launch": gu_bytes, "traffic": None}}

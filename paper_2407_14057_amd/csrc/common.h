@@ -159,7 +159,7 @@ struct EpiArgs {
   int sf_blocks_per_seq;             // filled in by the launcher (depends on the workgroup size)
   int stage_out;                     // filled in by the launcher: tile goes out through LDS (see gemm.hip)
   // the caller keeps the ticket counters at the end of the GEMM workspace zeroed
-  // (launch_gemm_counters_clear once before the first use): M <= 32 may take the skinny kernel
+  // (launch_gemm_counters_clear once before the first use): few rows may take the streaming kernel
   int skinny;
   // the caller keeps the flags of the persistent stream-K kernel (also at the end of the GEMM
   // workspace) zeroed likewise: launches whose tile count leaves the last round of the chip partly
@@ -199,6 +199,12 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra,
                           hipStream_t st);
+// The weight-streaming kernel for few rows (gemm_stream.hip).  part: fp32 partial sums of K splits;
+// tickets: zero before the first launch, zero again after each.
+bool gemm_stream_takes(int M, int N, int K);
+hipError_t launch_gemm_stream(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
+                              int lda, int ldw, int ldc, int epi, const EpiArgs& ra, void* part,
+                              size_t part_bytes, unsigned* tickets, size_t ticket_count, hipStream_t st);
 hipError_t launch_gemm_counters_clear(void* sk_ws, hipStream_t st);
 // ORs ST_EXCHANGE into *status if a GEMM since the last clear gave up on an exchange of partial
 // tiles between its workgroups (a flag that never came, or came from another XCD): its output,

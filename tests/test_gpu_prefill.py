@@ -240,6 +240,39 @@ def test_compaction_folded_into_the_next_layer_gives_the_same_bits(tiny_gains, n
     check_against_checker(shape, wb, ids, sched, b, verbose="fused compaction n=%d %s" % (n, sched))
 
 
+@pytest.fixture(scope="module")
+def few_rows_model():
+    """Wide enough that few rows take every tile of the weight-streaming kernel: K long enough to split
+    over workgroups, and QKV / O and down / gate and up on the three sides of its rule on N."""
+    shape = synth.ModelShape(2, 2048, 16, 128, 8320, 512)
+    w = synth.make_weights(shape, 1021, "cpu", gain_jitter=0.3)
+    model = B.Model(shape.as_dict(), _to_dev(w), DEV)
+    yield shape, synth.weights_to_host_bits(w), model
+    model.close()
+
+
+@pytest.mark.parametrize("n", [17, 33, 65, 97, 129, 193, 257, 385, 513])
+def test_few_rows_at_the_edges_of_the_streaming_tiles(few_rows_model, n):
+    """One row past each tile height (a chunk or row block with a single valid row), and the first row
+    count beyond the streaming kernel."""
+    shape, wb, model = few_rows_model
+    ids = synth.make_prompt(n, shape.vocab, 700 + n)
+    outs = [_run(model, ids, []) for _ in range(2)]
+    assert outs[0].status == 0
+    assert torch.equal(outs[0].logits, outs[1].logits)           # every sum in a fixed order
+    check_against_checker(shape, wb, ids, [], outs[0], verbose="few rows n=%d" % n)
+
+
+def test_few_rows_folded_compaction_gives_the_same_bits(few_rows_model):
+    """Row indirection of the A operand and of the residual in the streaming kernel, 300 -> 90 rows."""
+    shape, _, model = few_rows_model
+    ids = synth.make_prompt(300, shape.vocab, 711)
+    a = _snapshot(_run(model, ids, [(1, 300)]), shape.n_layers)
+    b = _snapshot(_run(model, ids, [(1, 300)], flags=B.LAZYLLM_FUSE_COMPACTION), shape.n_layers)
+    for x, y in zip(a, b):
+        assert (x is None and y is None) or torch.equal(x, y)
+
+
 def test_compaction_folded_in_on_a_ragged_batch(tiny_gains):
     shape, wb, model = tiny_gains
     lens = [70, 513, 1, 260]
