@@ -852,20 +852,28 @@ int lazyllm_generation_create(const lazyllm_model* m, const lazyllm_keep* sched,
   auto chk = [&](hipError_t err) { if (err != hipSuccess && rc == LAZYLLM_OK) rc = hip_fail(err); };
   char* S = g->state;
   const int d = c->d_model;
-  // entries never written must still be finite: the attention kernel multiplies the V of
-  // masked keys by probabilities that are exactly 0
-  chk(launch_fill_zero(S, gl.total, st));
+  chk(launch_fill_zero(S, gl.rope, st));           // status and logits
   chk(launch_rope_table((float2*)(S + gl.rope), capacity, c->head_dim, c->rope_theta, st));
-  for (int l = 0; l < c->n_layers && rc == LAZYLLM_OK; ++l) {
+  for (int l = 0; l < c->n_layers && rc == LAZYLLM_OK;) {
+    // the layers of a stage hold the same positions: a launch for up to StateLayers::MAX of them
     const int s = stg.stage_of_layer[l];
-    const int n = prefill->n_tokens[l];
-    chk(launch_scatter_rows(prefill->k[l], prefill->kept_pos[l], n, S + gl.k[l],
-                            stg.first_layer[s] == l ? (uint8_t*)(S + gl.has_kv[s]) : nullptr, kv_dim(c), st));
-    chk(launch_scatter_vt(prefill->v[l], prefill->kept_pos[l], n, kv_dim(c), S + gl.vt[l], gl.vt_ld, st));
-    if (s > 0 && stg.first_layer[s] == l)
-      chk(launch_scatter_rows(prefill->aux_h[l], prefill->aux_pos[l], prefill->n_aux[l],
-                              S + gl.aux_h[s], (uint8_t*)(S + gl.has_aux[s]), d, st));
+    const bool first = stg.first_layer[s] == l;
+    if (first && s > 0)
+      chk(launch_state_rows(prefill->aux_h[l], prefill->aux_pos[l], prefill->n_aux[l], d, capacity, S + gl.aux_h[s],
+                            (uint8_t*)(S + gl.has_aux[s]), st));
+    StateLayers sl{};
+    int m = 0;
+    const int l0 = l;
+    for (; l < c->n_layers && stg.stage_of_layer[l] == s && m < StateLayers::MAX &&
+           prefill->kept_pos[l] == prefill->kept_pos[l0]; ++l, ++m) {
+      sl.k[m] = prefill->k[l]; sl.v[m] = prefill->v[l];
+      sl.k_out[m] = S + gl.k[l]; sl.vt_out[m] = S + gl.vt[l];
+    }
+    chk(launch_state_kv(sl, m, prefill->kept_pos[l0], prefill->n_tokens[l0], kv_dim(c), capacity, gl.vt_ld,
+                        first ? (uint8_t*)(S + gl.has_kv[s]) : nullptr, st));
   }
+  // no Aux Cache belongs to the first stage
+  chk(launch_fill_zero(S + gl.has_aux[0], align_up((size_t)capacity), st));
   if (rc != LAZYLLM_OK) {
     (void)hipHostFree(g->host_counts);
     delete g;

@@ -271,9 +271,18 @@ hipError_t launch_lm_head_fused(const void* h, const int32_t* cu, int n_single, 
 // Bits of the device status word (the public header's LAZYLLM_ST_* values).
 constexpr int ST_BAD_TOKEN = 1, ST_BAD_CU = 2, ST_NO_STATE = 4, ST_EXCHANGE = 8;
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
-hipError_t launch_scatter_rows(const void* src, const int32_t* pos, int n, void* dst, uint8_t* flag,
-                               int d, hipStream_t st);
-hipError_t launch_scatter_vt(const void* v, const int32_t* pos, int n, int d, void* vt, int vt_ld,
+// Generation state from a prefill's packed rows (pos ascending); every entry of the tables is written.
+// flag (may be null for K,V): the stage's presence table.
+struct StateLayers {
+  static constexpr int MAX = 32;
+  const void* k[MAX];
+  const void* v[MAX];
+  void* k_out[MAX];
+  void* vt_out[MAX];
+};
+hipError_t launch_state_kv(const StateLayers& layers, int n_layers, const int32_t* pos, int n, int kvd, int cap,
+                           int vt_ld, uint8_t* flag, hipStream_t st);
+hipError_t launch_state_rows(const void* src, const int32_t* pos, int n, int d, int cap, void* dst, uint8_t* flag,
                              hipStream_t st);
 hipError_t launch_gen_embed(const void* embed, const int32_t* token_id, int vocab, int d, int new_pos,
                             void* h, unsigned long long* ssq, int32_t* run_pos, int32_t* live_row,

@@ -30,62 +30,115 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Packed rows -> position-indexed rows: dst[pos[i]] = src[i], flag[pos[i]] = 1.  One wave per row.
+// The generation state's tables from a prefill's packed results.  Every byte of a table is written
+// exactly once, by the workgroup that owns it: the packed row where a position has one, zeros where
+// not (entries never written must be finite: attention multiplies the V of masked keys by
+// probabilities that are exactly 0).  Bound by HBM: one read of the packed rows, one write of the
+// tables.  Clearing the whole state first and then scattering layer by layer, two launches each,
+// wrote most bytes twice, V^T two bytes at a time: 1.39 ms for 1.8 GB of state (7B shape, 3376
+// positions).
+// Packed rows are in ascending position, so the rows of 64 consecutive positions are consecutive:
+// every wave finds the first by a 64-way search.
 // ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-scatter_rows_kernel(const uint4* __restrict__ src, const int32_t* __restrict__ pos, int n,
-                    uint4* __restrict__ dst, uint8_t* __restrict__ flag, int vpr) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + wave;
-  if (r >= n) return;
-  const int p = pos[r];
-  const uint4* s = src + (size_t)r * vpr;
-  uint4* d = dst + (size_t)p * vpr;
-  for (int v = lane; v < vpr; v += 64) d[v] = s[v];
-  if (lane == 0 && flag != nullptr) flag[p] = 1;
+// First index i in ascending pos[0..n) with pos[i] >= p; called by a whole wave.
+__device__ __forceinline__ int wave_lower_bound(const int32_t* __restrict__ pos, int n, int p, int lane) {
+  int lo = 0, hi = n;                               // the answer is in [lo, hi]
+  while (hi > lo) {
+    const int span = hi - lo, step = (span + 63) / 64;
+    const int i = lo + lane * step;
+    const int below = __popcll(__ballot(i < hi && pos[i < hi ? i : lo] < p));   // lanes 0 .. below-1
+    if (below == 0) return lo;
+    const int last = lo + (below - 1) * step;       // pos[last] < p
+    hi = last + step < hi ? last + step : hi;
+    lo = last + 1;
+  }
+  return lo;
 }
 
-hipError_t launch_scatter_rows(const void* src, const int32_t* pos, int n, void* dst, uint8_t* flag,
-                               int d, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(scatter_rows_kernel, dim3((n + 3) / 4), dim3(256), 0, st, (const uint4*)src, pos,
-                     n, (uint4*)dst, flag, d / 8);
+// row_of[j] = packed row at position p0 + j, or -1.  One wave.
+__device__ __forceinline__ void rows_of_positions(const int32_t* __restrict__ pos, int n, int p0, int lane, int* row_of) {
+  row_of[lane] = -1;
+  const int r = wave_lower_bound(pos, n, p0, lane) + lane;
+  __builtin_amdgcn_wave_barrier();
+  if (r < n && pos[r] - p0 < 64) row_of[pos[r] - p0] = r;
+}
+
+// K and V of the layers of one stage: 64 positions x 64 features of one layer per workgroup.
+__global__ void __launch_bounds__(256)
+state_kv_kernel(StateLayers layers, const int32_t* __restrict__ pos, int n, int kvd, int cap, int vt_ld,
+                uint8_t* __restrict__ flag) {
+  __shared__ int row_of[64];
+  __shared__ uint16_t tile[64][66];
+  const int p0 = blockIdx.x * 64, f0 = blockIdx.y * 64, l = blockIdx.z, t = threadIdx.x;
+  if (t < 64) rows_of_positions(pos, n, p0, t, row_of);
+  __syncthreads();
+  const uint16_t* k = (const uint16_t*)layers.k[l];
+  const uint16_t* v = (const uint16_t*)layers.v[l];
+  uint16_t* ko = (uint16_t*)layers.k_out[l];
+  uint16_t* vo = (uint16_t*)layers.vt_out[l];
+  if (flag != nullptr && f0 == 0 && l == 0 && t < 64 && p0 + t < cap) flag[p0 + t] = row_of[t] >= 0 ? 1 : 0;
+  uint4 kx[2], vx[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int j = u * 32 + (t >> 3), r = row_of[j];
+    kx[u] = vx[u] = make_uint4(0, 0, 0, 0);
+    if (r >= 0) {
+      kx[u] = *(const uint4*)(k + (size_t)r * kvd + f0 + (t & 7) * 8);
+      vx[u] = *(const uint4*)(v + (size_t)r * kvd + f0 + (t & 7) * 8);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int j = u * 32 + (t >> 3);
+    if (p0 + j < cap) *(uint4*)(ko + (size_t)(p0 + j) * kvd + f0 + (t & 7) * 8) = kx[u];
+    uint32_t* w = (uint32_t*)&tile[j][(t & 7) * 8];
+    w[0] = vx[u].x; w[1] = vx[u].y; w[2] = vx[u].z; w[3] = vx[u].w;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {                     // 8 positions of one feature per thread, 128 bytes per feature
+    const int f = u * 32 + (t >> 3), j = (t & 7) * 8;
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = (uint32_t)tile[j + 2 * e][f] | ((uint32_t)tile[j + 2 * e + 1][f] << 16);
+    *(uint4*)(vo + (size_t)(f0 + f) * vt_ld + p0 + j) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+
+hipError_t launch_state_kv(const StateLayers& layers, int n_layers, const int32_t* pos, int n, int kvd, int cap,
+                           int vt_ld, uint8_t* flag, hipStream_t st) {
+  if (n_layers <= 0) return hipSuccess;
+  if (n_layers > StateLayers::MAX || n <= 0 || kvd % 64 != 0 || vt_ld % 64 != 0 || vt_ld < cap) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(state_kv_kernel, dim3(vt_ld / 64, kvd / 64, n_layers), dim3(256), 0, st, layers, pos, n, kvd, cap,
+                     vt_ld, flag);
   return hipGetLastError();
 }
 
-// Packed V rows [n][d] -> transposed, position-indexed vt[f][pos[i]].  A 64-row x 64-feature
-// tile goes through LDS so that the reads are whole rows and each 2-byte store instruction
-// writes one feature of 64 tokens (ascending, mostly adjacent positions).
+// The Aux Cache of one stage: rows of d values at their positions, zeros elsewhere.  One workgroup per
+// 64 positions and 512 features; n may be 0.
 __global__ void __launch_bounds__(256)
-scatter_vt_kernel(const uint16_t* __restrict__ v, const int32_t* __restrict__ pos, int n, int d,
-                  uint16_t* __restrict__ vt, int vt_ld) {
-  __shared__ uint16_t tile[64][66];
-  const int r0 = blockIdx.x * 64, f0 = blockIdx.y * 64;
-  for (int idx = threadIdx.x; idx < 64 * 8; idx += 256) {
-    const int r = idx >> 3, c = idx & 7;
-    uint4 x = make_uint4(0, 0, 0, 0);
-    if (r0 + r < n) x = *(const uint4*)(v + (size_t)(r0 + r) * d + f0 + c * 8);
-    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      tile[r][c * 8 + 2 * e] = (uint16_t)(w[e] & 0xffff);
-      tile[r][c * 8 + 2 * e + 1] = (uint16_t)(w[e] >> 16);
-    }
-  }
+state_rows_kernel(const uint4* __restrict__ src, const int32_t* __restrict__ pos, int n, int vpr, int cap,
+                  uint4* __restrict__ dst, uint8_t* __restrict__ flag) {
+  __shared__ int row_of[64];
+  const int p0 = blockIdx.x * 64, v = blockIdx.y * 64 + (threadIdx.x & 63);
+  if (threadIdx.x < 64) rows_of_positions(pos, n, p0, threadIdx.x, row_of);
   __syncthreads();
-  const int r = threadIdx.x & 63;
-  if (r0 + r < n) {
-    const int p = pos[r0 + r];
-    for (int f = threadIdx.x >> 6; f < 64; f += 4) vt[(size_t)(f0 + f) * vt_ld + p] = tile[r][f];
+  if (blockIdx.y == 0 && threadIdx.x < 64 && p0 + (int)threadIdx.x < cap)
+    flag[p0 + threadIdx.x] = row_of[threadIdx.x] >= 0 ? 1 : 0;
+  if (v >= vpr) return;
+#pragma unroll 4
+  for (int j = threadIdx.x >> 6; j < 64; j += 4) {
+    if (p0 + j >= cap) break;
+    const int r = row_of[j];
+    dst[(size_t)(p0 + j) * vpr + v] = r >= 0 ? src[(size_t)r * vpr + v] : make_uint4(0, 0, 0, 0);
   }
 }
 
-hipError_t launch_scatter_vt(const void* v, const int32_t* pos, int n, int d, void* vt, int vt_ld,
+hipError_t launch_state_rows(const void* src, const int32_t* pos, int n, int d, int cap, void* dst, uint8_t* flag,
                              hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  if (d % 64 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(scatter_vt_kernel, dim3((n + 63) / 64, d / 64), dim3(256), 0, st,
-                     (const uint16_t*)v, pos, n, d, (uint16_t*)vt, vt_ld);
+  if (n < 0 || cap <= 0 || d % 8 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(state_rows_kernel, dim3((cap + 63) / 64, (d / 8 + 63) / 64), dim3(256), 0, st, (const uint4*)src, pos,
+                     n, d / 8, cap, (uint4*)dst, flag);
   return hipGetLastError();
 }
 

@@ -289,3 +289,43 @@ def test_long_sequence_selection_beyond_lds(tiny):
             assert abs(s.sum() - 1.0) < 2e-4
             prev = sel
     gen.close()
+
+
+@pytest.mark.parametrize("n,room,sched", [(1, 1, []), (63, 1, [(1, 500)]), (64, 5, [(2, 990)]), (130, 63, [(1, 30), (3, 500)]),
+                                          (700, 13, [(1, 700), (2, 1000), (3, 5)])])
+def test_generation_state_holds_every_packed_row_and_zeros_elsewhere(n, room, sched):
+    """The state's tables right after its creation, element by element, in a buffer that held other
+    values: K and transposed V at the kept positions, the Aux Cache at the dropped ones, zeros and
+    clear flags everywhere else; position counts around the 64-position tiles."""
+    shape = synth.TINY
+    w = synth.make_weights(shape, 1031, "cpu")
+    model = B.Model(shape.as_dict(), {k: ([x.to(DEV) for x in v] if isinstance(v, list) else v.to(DEV)) for k, v in w.items()}, DEV)
+    ids = torch.from_numpy(synth.make_prompt(n, shape.vocab, 90 + n)).to(DEV)
+    out = model.prefill(ids, sched)
+    cap = n + room
+    dirty = torch.full((B.lazyllm_generation_state_bytes(model.cfg, sched, cap),), 0x5A, dtype=torch.uint8, device=DEV)
+    gen = B.Generation(model, sched, out, cap)
+    B.lazyllm_generation_destroy(gen.handle)
+    gen.state = dirty
+    gen.handle = B.lazyllm_generation_create(model.handle, sched, cap, out.res, dirty, None)
+    torch.cuda.synchronize()
+    view = gen.view()
+    for l in range(shape.n_layers):
+        pos = out.kept_pos(l).long()
+        k = torch.zeros_like(view["k"][l])
+        k[pos] = out.k(l).view(len(pos), -1)
+        assert torch.equal(view["k"][l], k)
+        vt = torch.zeros_like(view["vt"][l])
+        vt[:, pos] = out.v(l).view(len(pos), -1).t()
+        assert torch.equal(view["vt"][l], vt)
+        flags = torch.zeros_like(view["has_kv"][l])
+        flags[pos] = 1
+        assert torch.equal(view["has_kv"][l], flags)
+        if view["aux_h"][l] is not None:
+            aux, has = torch.zeros_like(view["aux_h"][l]), torch.zeros_like(view["has_aux"][l])
+            if out.n_aux[l]:
+                aux[out.aux_pos(l).long()] = out.aux_h(l)
+                has[out.aux_pos(l).long()] = 1
+            assert torch.equal(view["aux_h"][l], aux) and torch.equal(view["has_aux"][l], has)
+    gen.close()
+    model.close()
