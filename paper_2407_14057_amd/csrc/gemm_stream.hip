@@ -23,12 +23,14 @@
 //     the order of every sum is fixed.
 // Measured, cold weights, us at 1 / 16 / 32 / 64 / 96 / 128 rows (before: the kernels this one took
 // over from, a weight-streaming kernel through LDS up to 16 rows, tile kernels beyond):
-//   QKV (100 MB)      26 / 37 / 58 / 59 / 60 / 62  ->  19 / 20 / 21 / 25 / 29 / 32
-//   O (34 MB)         12 / 18 / 25 / 26 / 28 / 29  ->  11 / 11 / 12 / 13 / 14 / 14
-//   gate/up (180 MB)  42 / 53 / 59 / 59 / 59 / 60  ->  30 / 31 / 32 / 36 / 40 / 43
-//   down (90 MB)      24 / 36 / 38 / 39 / 41 / 42  ->  18 / 19 / 19 / 22 / 29 / 32
+//   QKV (100 MB)      26 / 37 / 58 / 59 / 60 / 62  ->  19 / 20 / 21 / 24 / 30 / 31
+//   O (34 MB)         12 / 18 / 25 / 26 / 28 / 29  ->  11 / 11 / 12 / 13 / 16 / 17
+//   gate/up (180 MB)  42 / 53 / 59 / 59 / 59 / 60  ->  30 / 31 / 30 / 34 / 40 / 42
+//   down (90 MB)      24 / 36 / 38 / 39 / 41 / 42  ->  18 / 19 / 19 / 22 / 28 / 30
 // i.e. 6.0 TB/s for gate/up at one row; from 64 rows on the LDS reads of A and the products of a step
-// (about 1100 and 900 cycles at 128 rows) no longer hide under the stream.
+// (about 1100 and 900 cycles at 128 rows and four column waves) no longer hide under the stream.
+//   * One K group alone (KW = 1: six, eight or twelve column waves) has nothing to add up and keeps its
+//     sums in registers to the end, so that LDS holds the two A stages only.
 #include "common.h"
 #include "gemm_shared.h"
 
@@ -139,14 +141,13 @@ __device__ __forceinline__ void stream_block_out(floatx4_t x, floatx4_t y, int r
 template <int EPI, int TM, int CW, int KW, bool NTW>
 __global__ void __launch_bounds__(CW * KW * 64)
 gemm_stream_kernel(const uint16_t* __restrict__ A, const char* __restrict__ W, uint16_t* __restrict__ C,
-                       const uint16_t* __restrict__ R, int M, int units, int lda, int ldc, int col_wgs,
+                       const uint16_t* __restrict__ R, int M, int units, int lda, int ldc, int col_waves, int col_wgs,
                        int chunks, int ks, int grid_main, StreamW sw, float* __restrict__ part,
                        unsigned* __restrict__ tickets, EpiArgs ra) {
   using Cols = StreamCols<EPI>;
   constexpr int NW = CW * KW, NT = NW * 64;
   constexpr int UNIT_BYTES = TM * 16 * 128, STAGE_BYTES = KW * UNIT_BYTES;
-  constexpr int NA = STAGE_BYTES / 16 / NT;         // 16-byte pieces of A per thread and step
-  static_assert(STAGE_BYTES % (16 * NT) == 0, "A stage");
+  constexpr int PIECES = STAGE_BYTES / 16, NA = (PIECES + NT - 1) / NT;   // 16-byte pieces of A per step, per thread
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   if ((int)blockIdx.x >= grid_main) {              // side job (see EpiArgs): Eq. 1 scores
     const int sb = (int)blockIdx.x - grid_main;
@@ -172,9 +173,11 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, const char* __restrict__ W, u
   const int step0 = all_steps * split / ks, n = all_steps * (split + 1) / ks - step0;
 
   // both blocks of a wave lie in one group of 128 features
+  // (a wave past the last column reads nothing: zeros)
+  const bool has_cols = CW % 3 != 0 || wg * CW + cw < col_waves;
   const int g0 = Cols::block(wg * CW + cw, 0), g1 = Cols::block(wg * CW + cw, 1);
   const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(W + (unsigned long long)(g0 >> 3) * sw.group), 0, (int)sw.bytes, 0x00020000);
+      (void*)(W + (has_cols ? (unsigned long long)(g0 >> 3) * sw.group : 0)), 0, has_cols ? (int)sw.bytes : 0, 0x00020000);
   const uint32_t w_lane = (uint32_t)l15 * sw.row + (uint32_t)(sw.swz ? (l4 ^ swz32(l15)) : l4) * 16;
   const uint32_t w_off[2] = {w_lane + (uint32_t)(g0 & 7) * sw.block, w_lane + (uint32_t)(g1 & 7) * sw.block};
   // A: piece j of a step is chunk j % 8 of row (j / 8) % (TM*16) of unit j / (TM*128)
@@ -183,7 +186,8 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, const char* __restrict__ W, u
   int a_unit[NA];
 #pragma unroll
   for (int q = 0; q < NA; ++q) {
-    const int j = q * NT + (int)threadIdx.x, tr = (j >> 3) % (TM * 16), ch = j & 7;
+    const int jq = q * NT + (int)threadIdx.x, j = PIECES % NT == 0 || jq < PIECES ? jq : PIECES - 1;
+    const int tr = (j >> 3) % (TM * 16), ch = j & 7;
     a_unit[q] = j / (TM * 128);
     int r = m0 + (tr < rows ? tr : rows - 1);       // rows past the edge: the last row again
     if (ra.a_rows != nullptr) r = ra.a_rows[r];
@@ -261,13 +265,16 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, const char* __restrict__ W, u
 #undef LZ_STREAM_BARRIER
   __syncthreads();
 
-  // ---- the waves' partial sums, added over the KW groups in order
+  // ---- the waves' partial sums, added over the KW groups in order (one group: they stay in registers)
+  constexpr int RED_BYTES = KW > 1 ? NW * TM * 2048 : 0;
   floatx4_t* red = (floatx4_t*)lds;                 // [wave][row block][block][lane]
-  unsigned long long* row_ssq = (unsigned long long*)(lds + NW * TM * 2048);
+  unsigned long long* row_ssq = (unsigned long long*)(lds + RED_BYTES);
+  if (KW > 1) {
 #pragma unroll
-  for (int t = 0; t < TM; ++t)
+    for (int t = 0; t < TM; ++t)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) red[((wave * TM + t) * 2 + c) * 64 + lane] = acc[t][c];
+      for (int c = 0; c < 2; ++c) red[((wave * TM + t) * 2 + c) * 64 + lane] = acc[t][c];
+  }
   if (EPI == EPI_RESIDUAL && threadIdx.x < TM * 16) row_ssq[threadIdx.x] = 0;
   if (ra.ssq_clear != nullptr && wg == 0 && split == 0 && threadIdx.x < TM * 16 && (int)threadIdx.x < rows)
     ra.ssq_clear[m0 + threadIdx.x] = 0;
@@ -280,18 +287,38 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, const char* __restrict__ W, u
     for (int g = 1; g < KW; ++g) v += red[(((g * CW + w0) * TM + t) * 2 + c) * 64 + lane];
     return v;
   };
+  auto finish = [&](int t, int cg, const floatx4_t (&v)[2]) {
+    const int row = m0 + t * 16 + l15;
+    if (CW % 3 == 0 && cg >= col_waves) return;
+    unsigned long long* rsq = row_ssq + t * 16 + l15;
+    if (Cols::PAIRED) {
+      stream_block_out<EPI, Cols::PD>(v[0], v[1], row, row < M, Cols::block(cg, 0), lane, C, R, ldc, ra, rsq);
+    } else {
+      stream_block_out<EPI, Cols::PD>(v[0], v[0], row, row < M, Cols::block(cg, 0), lane, C, R, ldc, ra, rsq);
+      stream_block_out<EPI, Cols::PD>(v[1], v[1], row, row < M, Cols::block(cg, 1), lane, C, R, ldc, ra, rsq);
+    }
+  };
   const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(part + ((size_t)wg * chunks + chunk) * ks * (TM * CW * 512)), 0, ks * (TM * CW * 2048), 0x00020000);
   constexpr int AGENT = 16;                         // sc1: at the level every XCD sees
   if (ks > 1) {
     __shared__ unsigned last_flag;
-    for (int job = wave; job < jobs; job += NW)
+    auto leave = [&](int job, int c, floatx4_t v) {
+      __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4_t*>(&v), prsrc,
+                                             split * (TM * CW * 2048) + (job * 2 + c) * 1024 + lane * 16, 0, AGENT);
+    };
+    if (KW > 1) {
+      for (int job = wave; job < jobs; job += NW)
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const floatx4_t v = total(job, c);
-        __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4_t*>(&v), prsrc,
-                                               split * (TM * CW * 2048) + (job * 2 + c) * 1024 + lane * 16, 0, AGENT);
-      }
+        for (int c = 0; c < 2; ++c) leave(job, c, total(job, c));
+    } else {
+#pragma unroll
+      for (int t = 0; t < TM; ++t)
+        if (t * 16 < rows) {
+          leave(t * CW + cw, 0, acc[t][0]);
+          leave(t * CW + cw, 1, acc[t][1]);
+        }
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -302,34 +329,33 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, const char* __restrict__ W, u
     __syncthreads();
     if (last_flag == 0) return;
   }
-  for (int job = wave; job < jobs; job += NW) {
-    floatx4_t v[2];
-    if (ks > 1) {
+  if (KW == 1 && ks == 1) {
 #pragma unroll
-      for (int c = 0; c < 2; ++c) v[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-      for (int sp = 0; sp < ks; sp += 4) {
-        u32x4_t p[4][2];                            // (past the last split: out of range, zeros)
+    for (int t = 0; t < TM; ++t)
+      if (t * 16 < rows) finish(t, wg * CW + cw, acc[t]);
+  } else {
+    for (int job = wave; job < jobs; job += NW) {
+      floatx4_t v[2];
+      if (ks > 1) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int c = 0; c < 2; ++c) v[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        for (int sp = 0; sp < ks; sp += 4) {
+          u32x4_t p[4][2];                          // (past the last split: out of range, zeros)
 #pragma unroll
-          for (int c = 0; c < 2; ++c)
-            p[u][c] = __builtin_amdgcn_raw_buffer_load_b128(prsrc, (sp + u) * (TM * CW * 2048) + (job * 2 + c) * 1024 + lane * 16, 0, AGENT);
+          for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+            for (int c = 0; c < 2; ++c)
+              p[u][c] = __builtin_amdgcn_raw_buffer_load_b128(prsrc, (sp + u) * (TM * CW * 2048) + (job * 2 + c) * 1024 + lane * 16, 0, AGENT);
 #pragma unroll
-          for (int c = 0; c < 2; ++c) v[c] += *reinterpret_cast<const floatx4_t*>(&p[u][c]);
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) v[c] += *reinterpret_cast<const floatx4_t*>(&p[u][c]);
+        }
+      } else {
+        v[0] = total(job, 0);
+        v[1] = total(job, 1);
       }
-    } else {
-      v[0] = total(job, 0);
-      v[1] = total(job, 1);
-    }
-    const int t = job / CW, cg = wg * CW + job % CW, row = m0 + t * 16 + l15;
-    unsigned long long* rsq = row_ssq + t * 16 + l15;
-    if (Cols::PAIRED) {
-      stream_block_out<EPI, Cols::PD>(v[0], v[1], row, row < M, Cols::block(cg, 0), lane, C, R, ldc, ra, rsq);
-    } else {
-      stream_block_out<EPI, Cols::PD>(v[0], v[0], row, row < M, Cols::block(cg, 0), lane, C, R, ldc, ra, rsq);
-      stream_block_out<EPI, Cols::PD>(v[1], v[1], row, row < M, Cols::block(cg, 1), lane, C, R, ldc, ra, rsq);
+      finish(job / CW, wg * CW + job % CW, v);
     }
   }
   if (EPI == EPI_RESIDUAL && ra.ssq_out != nullptr) {
@@ -343,11 +369,11 @@ static hipError_t launch_stream_cfg(const void* A, const void* W, void* C, const
                                         int lda, int ldc, int ks, const StreamW& sw, const EpiArgs& ra, float* part,
                                         size_t part_bytes, unsigned* tickets, size_t ticket_count, hipStream_t st) {
   constexpr int NW = CW * KW;
-  constexpr int LDS_STAGES = 2 * KW * TM * 2048, LDS_RED = NW * TM * 2048 + TM * 128;
+  constexpr int LDS_STAGES = 2 * KW * TM * 2048, LDS_RED = (KW > 1 ? NW * TM * 2048 : 0) + TM * 128;
   constexpr int LDS_BYTES = LDS_STAGES > LDS_RED ? LDS_STAGES : LDS_RED;
   static_assert(LDS_BYTES <= 159 * 1024, "LDS of a CU");
-  if (N % (CW * 32) != 0) return hipErrorInvalidValue;
-  const int col_wgs = N / (CW * 32), chunks = (M + TM * 16 - 1) / (TM * 16);
+  if (CW % 3 != 0 && N % (CW * 32) != 0) return hipErrorInvalidValue;
+  const int col_waves = N / 32, col_wgs = (col_waves + CW - 1) / CW, chunks = (M + TM * 16 - 1) / (TM * 16);
   const int steps = (K / BK + KW - 1) / KW;
   if (ks > steps) ks = steps;                       // every split has at least one step
   if (ks < 1) ks = 1;
@@ -365,28 +391,38 @@ static hipError_t launch_stream_cfg(const void* A, const void* W, void* C, const
     attr_set = true;
   }
   hipLaunchKernelGGL(kern, dim3(grid_main + side), dim3(NW * 64), LDS_BYTES, st, (const uint16_t*)A,
-                     (const char*)W, (uint16_t*)C, (const uint16_t*)R, M, K / BK, lda, ldc, col_wgs, chunks, ks,
+                     (const char*)W, (uint16_t*)C, (const uint16_t*)R, M, K / BK, lda, ldc, col_waves, col_wgs, chunks, ks,
                      grid_main, sw, part, tickets, ea);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------
 // Tile by shape: TM row blocks per chunk, CW x KW waves, ks K splits.  false: the tile kernels are
-// the better ones there (or level).  The lines are where the sweeps over the 7B projections cross
-// (cold weights; us this kernel / best tile kernel), n64 = N / 64 column pairs of waves:
-//   up to 32 and 64 rows: TM 2 and 4.  Two column waves x four K groups make N / 64 workgroups; a
-//     wide N (gate/up: 344) is better off with four x two (172 workgroups: 35.5 against 43.5).
-//   65 .. 128 rows: narrow N (O, down) in two chunks of 64 rows (14.4 against 17.8 for one chunk
-//     of 96 or 128), else TM 6 and 8 on four x two waves.
-//   129 .. 256 rows: TM 6 / 8 in two chunks: QKV 38 / 62, 44 / 62; O 19 / 30, 23 / 31; down 34 / 46,
-//     40 / 50.  Gate/up only from 193 rows on, with eight column waves (74 / 85; 160 rows: 72 / 68).
-//   257 .. 512 rows, narrow N only: O 25 / 33 (355 rows), 32 / 38 (512); down 52 / 62, 66 / 72;
-//     640 rows: 49 / 46, not taken.  QKV at 355 rows 71 / 65, gate/up 109 / 91: not taken.
+// the better ones there.
 //   K up to 1024: any number of rows, on two x four waves, in chunks as tall as still make about two
 //     workgroups per CU.  Such a launch is a chain of latencies, not a stream (one to four steps;
 //     512 rows, N = 256, K = 704: 12.3 us on the tile kernels' eleven steps), and the sums come in
 //     the same order whatever the number of rows: a packed batch gives the bits of its prompts.
-// ks: as many splits as make 256 workgroups, each of at least four steps.
+//   Longer K, up to 640 rows: of the tiles below the one whose estimated time is the shortest, among
+//     those that need one workgroup per CU at most.  From 32 rows on a workgroup's own time counts
+//     (its LDS reads and products do not hide under the stream), so what wins is the tile that spreads
+//     the columns over the most of the 256 CUs: 22016 columns make 172 workgroups of four column
+//     waves but 230 of three, 12288 columns in two splits 192 or 256.  In us:
+//       a 64-wide K unit   TM * (0.035 + 0.0104 CW): measured 0.50 for 8 x 3, 0.55 8 x 4, 0.82 8 x 6,
+//                          0.86 8 x 8, 1.25 8 x 12, 0.66 6 x 6, 1.08 6 x 12, 1.48 10 x 12
+//       a launch           8, and for every further row chunk a tenth of the stream of W again
+//       ks > 1             2, and the partial sums out and back at 4 TB/s
+//     Up to 16 rows and for narrow N up to 256 rows the sweeps leave one tile each: two column waves
+//     x four K groups (a wide N: four x two, 35.5 against 43.5 at one row), O in two chunks of 64 rows
+//     (65 .. 128 rows: 16.5 / 17.3 in one of 128), down in one (28 / 30), four x two beyond.
+//     Measured, cold weights, the same kernel with 4 or 8 column waves / best tile kernel -> now:
+//       gate/up  64 rows 37 / 59 -> 34, 97: 43 / 59 -> 40, 176: 72 / 68 -> 52, 256: 67 / 85 -> 59,
+//                355: 113 / 94 -> 79, 512: 123 / 107 -> 92, 613: - / 148 -> 107
+//       QKV      64 rows 26 / 59 -> 24, 128: 35 / 62 -> 31, 192: 41 / 62 -> 37, 256: 47 / 62 -> 42,
+//                355: 72 / 72 -> 52, 512: - / 79 -> 62, 613: - / 91 -> 69
+//       down     97 rows 30 / 41 -> 28, 512: 66 / 72 -> 62, 613: - / 91 -> 74;  O  613: - / 51 -> 40
+//     768 rows and taller chunks (TM 12): the accumulators spill beside twelve waves (328 us).
+// ks: every split has at least four steps.
 // ------------------------------------------------------------------------------------------
 struct StreamPlan {
   int tm, cw, kw, ks;
@@ -401,30 +437,47 @@ static bool stream_plan(int M, int N, int K, StreamPlan* p) {
     p->tm = (long)n64 * ((M + 31) / 32) <= 512 ? 2 : (long)n64 * ((M + 63) / 64) <= 512 ? 4 : 8;
     return true;
   }
+  if (M > 640) return false;
   const bool narrow = n64 <= 64, wide = n64 > 256;
-  p->cw = 4;
-  p->kw = 2;
+  const double stream = 2.0 * N * K / 5.6e6;
+  double best = 0.0;
+  auto consider = [&](int tm, int cw, int kw) {
+    if (cw % 3 != 0 && N % (cw * 32) != 0) return;
+    const int cols = (N / 32 + cw - 1) / cw, chunks = (M + tm * 16 - 1) / (tm * 16);
+    const int per_xcd = (cols + 7) / 8 * chunks;     // (a column group's workgroups share an XCD of 32 CUs)
+    int most = (units + kw - 1) / kw / 4;
+    if (most < 1) most = 1;
+    for (int ks = 1; ks <= most && (ks == 1 || per_xcd * ks <= 32); ++ks) {
+      double us = 8.0 + (double)units / ks * tm * (0.035 + 0.0104 * cw) + 0.1 * stream * (chunks - 1);
+      us *= (per_xcd * ks + 31) / 32;                // (more than one round of the CUs)
+      if (ks > 1) us += 2.0 + 8.0 * M * N * ks / 4e6;
+      if (best == 0.0 || us < 0.98 * best) {
+        best = us;
+        *p = StreamPlan{tm, cw, kw, ks};
+      }
+    }
+  };
   if (M <= 64) {
-    p->tm = M <= 32 ? 2 : 4;
-    if (!wide) { p->cw = 2; p->kw = 4; }
-  } else if (M <= 128 && narrow) {
-    p->tm = 4; p->cw = 2; p->kw = 4;
-  } else if (M <= 128) {
-    p->tm = M <= 96 ? 6 : 8;
-  } else if (M <= 256 && !wide) {
-    p->tm = M <= 192 ? 6 : 8;
-  } else if (M > 192 && M <= 256 && N % 256 == 0) {
-    p->tm = 8; p->cw = 8; p->kw = 1;
-  } else if (M <= 512 && narrow) {
-    p->tm = M <= 384 ? 6 : 8;
+    const int tm = M <= 32 ? 2 : 4;
+    if (!wide) consider(tm, 2, 4);
+    if (!narrow && (M > 16 || wide)) consider(tm, 4, 2);
+    if (!narrow && M > 16) consider(tm, 3, 2);
+  } else if (M <= 256 && narrow) {
+    if (M > 128) consider(M <= 192 ? 6 : 8, 4, 2);
+    else if (K < 8192) consider(4, 2, 4);
+    else consider(8, 2, 4);
   } else {
-    return false;
+    const int tm = M <= 96 || (M > 128 && M <= 192) || (M > 256 && M <= 384) ? 6 : 8;
+    consider(tm, 4, 2);
+    consider(tm, 3, 2);
+    consider(8, 8, 1);
+    consider(tm, 6, 1);
+    consider(tm, 12, 1);
+    if (M > 384) consider(10, 12, 1);
+    // (beyond 128 rows only in one round: the tile kernels are better at several)
+    if (M > 128 && (N / 32 + p->cw * 8 - 1) / (p->cw * 8) * ((M + p->tm * 16 - 1) / (p->tm * 16)) > 32) return false;
   }
-  const int wgs = N / (p->cw * 32) * ((M + p->tm * 16 - 1) / (p->tm * 16));
-  const int most = (units + p->kw - 1) / p->kw / 4;
-  p->ks = 256 / wgs < most ? 256 / wgs : most;
-  if (p->ks < 1) p->ks = 1;
-  return true;
+  return best > 0.0;
 }
 
 bool gemm_stream_takes(int M, int N, int K) {
@@ -462,12 +515,21 @@ hipError_t launch_gemm_stream(const void* A, const void* W, void* C, const void*
   do {                                                                                                     \
     LZ_STREAM_TILE(E, 2, 2, 4)                                                                             \
     LZ_STREAM_TILE(E, 4, 2, 4)                                                                             \
-    if (p.tm == 8 && p.cw == 2) LZ_STREAM(E, 8, 2, 4, false);                                              \
+    LZ_STREAM_TILE(E, 8, 2, 4)                                                                             \
+    if (p.tm == 2 && p.cw == 3) LZ_STREAM(E, 2, 3, 2, true);                                               \
+    if (p.tm == 4 && p.cw == 3) LZ_STREAM(E, 4, 3, 2, true);                                               \
     if (p.tm == 2 && p.cw == 4) LZ_STREAM(E, 2, 4, 2, true);                                               \
     if (p.tm == 4 && p.cw == 4) LZ_STREAM(E, 4, 4, 2, true);                                               \
+    LZ_STREAM_TILE(E, 6, 3, 2)                                                                             \
+    LZ_STREAM_TILE(E, 8, 3, 2)                                                                             \
     LZ_STREAM_TILE(E, 6, 4, 2)                                                                             \
     LZ_STREAM_TILE(E, 8, 4, 2)                                                                             \
+    if (p.tm == 6 && p.cw == 6) LZ_STREAM(E, 6, 6, 1, false);                                              \
+    if (p.tm == 8 && p.cw == 6) LZ_STREAM(E, 8, 6, 1, false);                                              \
     if (p.tm == 8 && p.cw == 8) LZ_STREAM(E, 8, 8, 1, false);                                              \
+    if (p.tm == 6 && p.cw == 12) LZ_STREAM(E, 6, 12, 1, false);                                            \
+    if (p.tm == 8 && p.cw == 12) LZ_STREAM(E, 8, 12, 1, false);                                            \
+    if (p.tm == 10 && p.cw == 12) LZ_STREAM(E, 10, 12, 1, false);                                          \
     return hipErrorInvalidValue;                                                                           \
   } while (0)
   switch (epi) {

@@ -243,7 +243,8 @@ def test_compaction_folded_into_the_next_layer_gives_the_same_bits(tiny_gains, n
 @pytest.fixture(scope="module")
 def few_rows_model():
     """Wide enough that few rows take every tile of the weight-streaming kernel: K long enough to split
-    over workgroups, and QKV / O and down / gate and up on the three sides of its rule on N."""
+    over workgroups, and QKV / O and down / gate and up on the three sides of its rule on N.  520 column
+    waves of gate and up: not a multiple of the three, six or twelve of a workgroup."""
     shape = synth.ModelShape(2, 2048, 16, 128, 8320, 512)
     w = synth.make_weights(shape, 1021, "cpu", gain_jitter=0.3)
     model = B.Model(shape.as_dict(), _to_dev(w), DEV)
@@ -251,7 +252,7 @@ def few_rows_model():
     model.close()
 
 
-@pytest.mark.parametrize("n", [17, 33, 65, 97, 129, 193, 257, 385, 513])
+@pytest.mark.parametrize("n", [17, 33, 65, 97, 129, 193, 257, 385, 481, 513, 641])
 def test_few_rows_at_the_edges_of_the_streaming_tiles(few_rows_model, n):
     """One row past each tile height (a chunk or row block with a single valid row), and the first row
     count beyond the streaming kernel."""
@@ -261,6 +262,20 @@ def test_few_rows_at_the_edges_of_the_streaming_tiles(few_rows_model, n):
     assert outs[0].status == 0
     assert torch.equal(outs[0].logits, outs[1].logits)           # every sum in a fixed order
     check_against_checker(shape, wb, ids, [], outs[0], verbose="few rows n=%d" % n)
+
+
+@pytest.mark.parametrize("n,gate_up", [(300, 8256), (400, 11072), (520, 11072)])
+def test_few_rows_with_twelve_column_waves(n, gate_up):
+    """Tiles of six, eight and ten row blocks on twelve column waves: gate and up of 516 and 692 column waves
+    (43 workgroups exactly; the last one two thirds full)."""
+    shape = synth.ModelShape(2, 2048, 16, 128, gate_up, 512)
+    w = synth.make_weights(shape, 1031, "cpu", gain_jitter=0.3)
+    model = B.Model(shape.as_dict(), _to_dev(w), DEV)
+    ids = synth.make_prompt(n, shape.vocab, 720 + n)
+    out = _run(model, ids, [])
+    assert out.status == 0
+    check_against_checker(shape, synth.weights_to_host_bits(w), ids, [], out, verbose="twelve column waves n=%d" % n)
+    model.close()
 
 
 def test_few_rows_folded_compaction_gives_the_same_bits(few_rows_model):
