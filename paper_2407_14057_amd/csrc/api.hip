@@ -739,7 +739,7 @@ void layout_generation(const lazyllm_config* c, const Stages* st, int cap, GenLa
 // Scratch of one step; rows are bounded by the capacity (every token could be revived at once).
 struct GenWorkspace {
   size_t h0, h1, ssq0, ssq1, q, o, act, score, scores, member, bits, run_pos, live_row, src_row,
-      park_src, park_pos, counts, xf, att_ws, gemm_ws, total;
+      park_src, park_pos, xf, att_ws, gemm_ws, total;
 };
 
 void layout_gen_workspace(const lazyllm_config* c, int n_stages, int cap, GenWorkspace* w) {
@@ -762,7 +762,6 @@ void layout_gen_workspace(const lazyllm_config* c, int n_stages, int cap, GenWor
   w->src_row = take(T * 4);
   w->park_src = take(T * 4);
   w->park_pos = take(T * 4);
-  w->counts = take((size_t)n_stages * 16);
   w->xf = take(d * 4);
   w->att_ws = take(decode_attention_workspace_bytes(c->d_model, c->n_heads));
   w->gemm_ws = take(gemm_workspace_bytes());
@@ -778,6 +777,7 @@ struct lazyllm_generation {
   char* state;
   int capacity, n_prompt, n_tokens;
   int32_t* host_counts;     // pinned host memory, [n_stages][4]
+  int32_t* host_counts_dev; // the same memory as the GPU sees it
   // set while a step is being enqueued and cleared when it has been enqueued completely: a step
   // that returns an error after its first launch has already changed has_kv / has_aux / live_row
   // without advancing n_tokens, so every later step is refused
@@ -842,7 +842,9 @@ int lazyllm_generation_create(const lazyllm_model* m, const lazyllm_keep* sched,
   g->capacity = capacity; g->n_prompt = n_prompt; g->n_tokens = n_prompt; g->failed = false;
   g->host_counts = nullptr;
   hipError_t e = hipHostMalloc((void**)&g->host_counts, (size_t)stg.n_stages * 16, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&g->host_counts_dev, g->host_counts, 0);
   if (e != hipSuccess) {
+    if (g->host_counts != nullptr) (void)hipHostFree(g->host_counts);
     delete g;
     g_last_hip_error = (int)e;
     return LAZYLLM_ENOMEM;
@@ -958,26 +960,24 @@ int lazyllm_decode_step(lazyllm_generation* g, const int32_t* token_id, void* wo
   int cur = 0, M = 1;
 
   g->failed = true;                  // until the whole step is enqueued (cleared at the end)
-  LZ_HIP(launch_gemm_counters_clear(W + ws.gemm_ws, st));
-  LZ_HIP(launch_decode_attention_counters_clear(W + ws.att_ws, decode_attention_workspace_bytes(d, H), st));
   LZ_RUN(LAZYLLM_STEP_EMBED, -1, 1, 2.0 * rowb,
          launch_gen_embed(m->embed, token_id, c->vocab, d, new_pos, hbuf[0], ssq_attn, run_pos_of(0),
-                          live_row, (uint8_t*)(S + gl.has_kv[0]), res->status, st));
+                          live_row, (uint8_t*)(S + gl.has_kv[0]), res->status, W + ws.gemm_ws, W + ws.att_ws,
+                          decode_attention_workspace_bytes(d, H), st));
   for (int l = 0; l < L; ++l) {
     const int s = stg.stage_of_layer[l];
     if (s > 0 && stg.first_layer[s] == l) {
       // Sec. 3.2: this step's scores of layer l-1 pick the tokens of layer l; selected tokens
       // without K,V here run the layer (from the state they carry, or revived from this layer's
       // Aux Cache), unselected tokens that carry a state leave it in the Aux Cache.
-      int32_t* counts_dev = (int32_t*)(W + ws.counts) + 4 * s;
+      // (counts straight into the generation's pinned host memory: no copy behind the kernel)
       LZ_RUN(LAZYLLM_STEP_SELECT, l, n_tot, 8.0 * n_tot,
              launch_gen_stage(scores_of(l - 1), s > 1 ? member_of(s - 1) : nullptr, n_tot, sel_count[s],
                               member_of(s), bits_of(s), (uint8_t*)(S + gl.has_kv[s]),
                               (uint8_t*)(S + gl.has_aux[s]), live_row, run_pos_of(s), src_row,
-                              park_src, park_pos, counts_dev, res->status, st));
+                              park_src, park_pos, g->host_counts_dev + 4 * s, res->status, st));
       // how many rows run this stage decides every launch shape below: the one place a step
       // waits for the GPU
-      LZ_HIP(hipMemcpyAsync(g->host_counts + 4 * s, counts_dev, 16, hipMemcpyDeviceToHost, st));
       LZ_HIP(hipStreamSynchronize(st));
       const int rows = g->host_counts[4 * s], parked = g->host_counts[4 * s + 1];
       if (rows < 1 || rows > sel_count[s] || parked < 0 || parked > M ||
@@ -1036,7 +1036,7 @@ int lazyllm_decode_step(lazyllm_generation* g, const int32_t* token_id, void* wo
            launch_gemm(W + ws.act, m->wdown[l], h, h, M, d, fp, fp, fp, d, EPI_RESIDUAL, st, &ed,
                        W + ws.gemm_ws, gemm_workspace_bytes()));
   }
-  LZ_HIP(launch_gemm_exchange_check(W + ws.gemm_ws, res->status, st));
+  // (no projection of a step takes a form that waits for another workgroup: nothing to check, unlike a prefill)
   if (lm_head_fused_fits(1, d)) {
     LZ_RUN(LAZYLLM_STEP_LM_HEAD, -1, 1, (double)c->vocab * rowb,
            launch_lm_head_fused(hbuf[cur], nullptr, M, 1, m->final_norm, m->lm_head, res->logits, d, c->vocab,

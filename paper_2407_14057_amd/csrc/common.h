@@ -26,6 +26,13 @@ __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u 
 __device__ __forceinline__ float bf16_to_float(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
 
 // 8 bf16 (one 16-byte vector) <-> 8 floats
+// 16 bytes that nobody reads again before the caches have turned over (streams of weights and of K, V)
+__device__ __forceinline__ uint4 load_once(const uint4* p) {
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  const u4 v = __builtin_nontemporal_load((const u4*)p);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ __forceinline__ void unpack8(const uint4& v, float* f) {
   f[0] = bf16_lo(v.x); f[1] = bf16_hi(v.x); f[2] = bf16_lo(v.y); f[3] = bf16_hi(v.y);
   f[4] = bf16_lo(v.z); f[5] = bf16_hi(v.z); f[6] = bf16_lo(v.w); f[7] = bf16_hi(v.w);
@@ -206,6 +213,7 @@ hipError_t launch_gemm_stream(const void* A, const void* W, void* C, const void*
                               int lda, int ldw, int ldc, int epi, const EpiArgs& ra, void* part,
                               size_t part_bytes, unsigned* tickets, size_t ticket_count, hipStream_t st);
 hipError_t launch_gemm_counters_clear(void* sk_ws, hipStream_t st);
+void* gemm_counter_region(void* sk_ws, size_t* bytes);            // what that call clears
 // ORs ST_EXCHANGE into *status if a GEMM since the last clear gave up on an exchange of partial
 // tiles between its workgroups (a flag that never came, or came from another XCD): its output,
 // and everything computed from it, is then not to be used.
@@ -286,7 +294,8 @@ hipError_t launch_state_rows(const void* src, const int32_t* pos, int n, int d, 
                              hipStream_t st);
 hipError_t launch_gen_embed(const void* embed, const int32_t* token_id, int vocab, int d, int new_pos,
                             void* h, unsigned long long* ssq, int32_t* run_pos, int32_t* live_row,
-                            uint8_t* has_kv0, int32_t* status, hipStream_t st);
+                            uint8_t* has_kv0, int32_t* status, void* gemm_ws, void* att_ws,
+                            size_t att_ws_bytes, hipStream_t st);
 hipError_t launch_gen_stage(const float* s, const uint8_t* member_prev, int n_tot, int k,
                             uint8_t* member, unsigned long long* member_bits, uint8_t* has_kv,
                             uint8_t* has_aux, int32_t* live_row, int32_t* run_pos,
@@ -303,8 +312,7 @@ hipError_t launch_decode_attention(const void* q, const int32_t* qpos, int M, co
                                    void* split_ws = nullptr, size_t split_ws_bytes = 0,
                                    int kv_group = 1);
 size_t decode_attention_workspace_bytes(int d_model, int n_heads);
-// the ticket counters at the end of that workspace must be zero before the first attention launch
-hipError_t launch_decode_attention_counters_clear(void* split_ws, size_t split_ws_bytes, hipStream_t st);
+// (the ticket counters at its end must be zero before the first attention launch: launch_gen_embed)
 
 struct PlanArgs {
   int32_t n_stages;                     // pruning stages after stage 0

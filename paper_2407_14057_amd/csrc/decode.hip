@@ -144,15 +144,21 @@ hipError_t launch_state_rows(const void* src, const int32_t* pos, int n, int d, 
 
 // ------------------------------------------------------------------------------------------
 // Start of a step: the new token's embedding row (with its sum of squares for the folded
-// RMSNorm), its position, and the tables that say "only the new token carries a state".
-// One workgroup.
+// RMSNorm), its position, the tables that say "only the new token carries a state", and the
+// zeroed ticket counters of the step's GEMMs and attention (two launches of their own before:
+// 4 us of 210 per step of the small model, 9 of 3400 of the 7B).  One workgroup.
 // ------------------------------------------------------------------------------------------
+constexpr size_t DATT_COUNTER_BYTES = 4096;       // one ticket counter per K,V head
+
 __global__ void __launch_bounds__(256)
 gen_embed_kernel(const uint4* __restrict__ embed, const int32_t* __restrict__ token_id, int vocab,
                  int vpr, int new_pos, uint4* __restrict__ h, unsigned long long* __restrict__ ssq,
                  int32_t* __restrict__ run_pos, int32_t* __restrict__ live_row,
-                 uint8_t* __restrict__ has_kv0, int32_t* __restrict__ status) {
+                 uint8_t* __restrict__ has_kv0, int32_t* __restrict__ status, uint4* __restrict__ clear0,
+                 int n0, uint4* __restrict__ clear1, int n1) {
   __shared__ float red[4];
+  for (int i = threadIdx.x; i < n0; i += 256) clear0[i] = make_uint4(0, 0, 0, 0);
+  for (int i = threadIdx.x; i < n1; i += 256) clear1[i] = make_uint4(0, 0, 0, 0);
   int id = token_id[0];
   if (id < 0 || id >= vocab) {
     if (threadIdx.x == 0) atomicOr(status, ST_BAD_TOKEN);
@@ -181,9 +187,16 @@ gen_embed_kernel(const uint4* __restrict__ embed, const int32_t* __restrict__ to
 
 hipError_t launch_gen_embed(const void* embed, const int32_t* token_id, int vocab, int d, int new_pos,
                             void* h, unsigned long long* ssq, int32_t* run_pos, int32_t* live_row,
-                            uint8_t* has_kv0, int32_t* status, hipStream_t st) {
+                            uint8_t* has_kv0, int32_t* status, void* gemm_ws, void* att_ws,
+                            size_t att_ws_bytes, hipStream_t st) {
+  size_t gemm_bytes = 0;
+  void* gemm_counters = gemm_counter_region(gemm_ws, &gemm_bytes);
+  if (att_ws_bytes < DATT_COUNTER_BYTES || ((uintptr_t)gemm_counters & 15) != 0 || (((uintptr_t)att_ws + att_ws_bytes) & 15) != 0)
+    return hipErrorInvalidValue;
   hipLaunchKernelGGL(gen_embed_kernel, dim3(1), dim3(256), 0, st, (const uint4*)embed, token_id, vocab,
-                     d / 8, new_pos, (uint4*)h, ssq, run_pos, live_row, has_kv0, status);
+                     d / 8, new_pos, (uint4*)h, ssq, run_pos, live_row, has_kv0, status, (uint4*)gemm_counters,
+                     (int)(gemm_bytes / 16), (uint4*)((char*)att_ws + att_ws_bytes - DATT_COUNTER_BYTES),
+                     (int)(DATT_COUNTER_BYTES / 16));
   return hipGetLastError();
 }
 
@@ -468,7 +481,8 @@ decode_attn_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict__ q
 // per dimension row of V^T, all of a chunk's loads in flight before the first use; rows of K
 // whose key takes no part are not read.  The G query heads that share a K,V head are served by
 // the same loads.  Scores move from "lanes of a key" to "lane = key" through a wave-private LDS
-// row, the probabilities move back the same way.  The 4 waves of a workgroup interleave the
+// row, the probabilities move back the same way.  K, V are read once: non-temporal loads, 18.3 us
+// against 19.0 for 3376 keys of 32 heads (55 MB).  The 4 waves of a workgroup interleave the
 // chunks of the workgroup's key range and are merged through LDS; key ranges (blockIdx.y, at
 // most 16) are merged by the workgroup that finishes last.  `counters` (one per K,V head) must
 // be zero on entry and are zero again on exit.
@@ -523,10 +537,10 @@ decode_attn1_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict__ 
     for (int i = 0; i < NKI; ++i) {
       const int j = i * KPI + kg;
       kr[i] = make_uint4(0u, 0u, 0u, 0u);
-      if ((word >> j) & 1ull) kr[i] = *(const uint4*)(kbase + (size_t)(k0 + j) * kvd);
+      if ((word >> j) & 1ull) kr[i] = load_once((const uint4*)(kbase + (size_t)(k0 + j) * kvd));
     }
 #pragma unroll
-    for (int i = 0; i < NVI; ++i) vr[i] = *(const uint4*)(vbase + (size_t)i * 8 * vt_ld + k0);
+    for (int i = 0; i < NVI; ++i) vr[i] = load_once((const uint4*)(vbase + (size_t)i * 8 * vt_ld + k0));
     // scores: each lane's 8 dimensions, then a sum over the CHK lanes of a key
 #pragma unroll
     for (int i = 0; i < NKI; ++i) {
@@ -711,17 +725,10 @@ decode_attn_merge_kernel(const float* __restrict__ po, const float2* __restrict_
   if (zstat != nullptr && row == M - 1 && dim == 0) zstat[head] = make_float2(m, inv);
 }
 
-constexpr size_t DATT_COUNTER_BYTES = 4096;       // one ticket counter per K,V head
-
 size_t decode_attention_workspace_bytes(int d_model, int n_heads) {
   // 16 splits of up to 128 queries: fp32 outputs and (max, sum) pairs; then the one-query
   // kernel's ticket counters
   return (size_t)16 * 128 * ((size_t)d_model * 4 + (size_t)n_heads * 8) + DATT_COUNTER_BYTES;
-}
-
-hipError_t launch_decode_attention_counters_clear(void* split_ws, size_t split_ws_bytes, hipStream_t st) {
-  if (split_ws == nullptr || split_ws_bytes < DATT_COUNTER_BYTES) return hipErrorInvalidValue;
-  return launch_fill_zero((char*)split_ws + split_ws_bytes - DATT_COUNTER_BYTES, DATT_COUNTER_BYTES, st);
 }
 
 hipError_t launch_decode_attention(const void* q, const int32_t* qpos, int M, const void* k,
@@ -743,13 +750,15 @@ hipError_t launch_decode_attention(const void* q, const int32_t* qpos, int M, co
     counters = (unsigned*)((char*)split_ws + split_ws_bytes);
   }
   // A step's queries (the new token and the revived ones) make few workgroups: split the keys so
-  // that about 512 are in flight, each with at least two key tiles, as far as the workspace for
-  // the splits' partial results reaches.
+  // that about 256 are in flight, each with at least two key tiles, as far as the workspace for
+  // the splits' partial results reaches.  (512 wait less for their keys but leave and merge twice the
+  // partial results, 2 KB per query, head and split: 129 .. 256 queries of 32 heads, 2048 keys,
+  // 30.5 us against 27.7 and the merge besides; four steps after a pruned prefill 0.8 ms of 24.)
   const int qblocks = (M + 127) / 128, d_model = n_heads * head_dim;
   int n_splits = 1;
   if (split_ws != nullptr) {
     const int tiles = (n_keys + 63) / 64;
-    n_splits = 512 / (n_heads * qblocks);
+    n_splits = 256 / (n_heads * qblocks);
     if (n_splits > tiles / 2) n_splits = tiles / 2;
     if (n_splits > 16) n_splits = 16;
     const size_t per_split = (size_t)M * ((size_t)d_model * 4 + (size_t)n_heads * 8);

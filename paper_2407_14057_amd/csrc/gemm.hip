@@ -1344,8 +1344,15 @@ hipError_t launch_pack_kblock(const void* W, int N, int K, int ldw, void* Wb, hi
   return hipGetLastError();
 }
 
+void* gemm_counter_region(void* sk_ws, size_t* bytes) {
+  *bytes = SK_TICKET_BYTES + PSK_FLAG_BYTES;
+  return (char*)sk_ws + SK_PART_BYTES;
+}
+
 hipError_t launch_gemm_counters_clear(void* sk_ws, hipStream_t st) {
-  return launch_fill_zero((char*)sk_ws + SK_PART_BYTES, SK_TICKET_BYTES + PSK_FLAG_BYTES, st);
+  size_t bytes = 0;
+  void* counters = gemm_counter_region(sk_ws, &bytes);
+  return launch_fill_zero(counters, bytes, st);
 }
 
 __global__ void exchange_check_kernel(const unsigned* __restrict__ give_ups, int32_t* __restrict__ status) {

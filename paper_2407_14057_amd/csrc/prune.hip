@@ -489,9 +489,10 @@ gen_stage_kernel(const float* __restrict__ s, const uint8_t* __restrict__ member
   if (threadIdx.x == 0) {
     int tot = 0;
     for (int w = 0; w < SEL_WAVES; ++w) tot += wsum[w];
-    counts[0] = run_rows;
-    counts[1] = run_park;
-    counts[2] = tot;
+    // (host memory: the step waits for them)
+    __hip_atomic_store(counts + 0, run_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(counts + 1, run_park, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(counts + 2, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
