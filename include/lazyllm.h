@@ -346,7 +346,8 @@ int lazyllm_profile_end(lazyllm_profile_record* out, int32_t capacity, int32_t* 
  * Bits 8..15 of `epilogue` force a tile configuration (measurement hook; 0 = the
  * library chooses): 2 = 128x128, 3 = 128x128 in waves of 32x128, 4 = 128x256, 5 = 256x256 ping-pong, 7 = 192x256
  * ping-pong, 6 = 128x128 stream-K (needs the workspace), 8 = the weight-streaming
- * kernel of the decoding steps (M <= 32, needs the workspace), 9 / 10 = the 256x256 / 192x256
+ * kernel of few token rows (shapes that lazyllm_op_gemm_stream_plan accepts, needs the workspace),
+ * 9 / 10 = the 256x256 / 192x256
  * ping-pong tiles under the persistent stream-K schedule (need the workspace), 13 = 128x256 on
  * 8 waves of 32x128 with three stages, 14 = 256x256 on four waves of 128x128 (one per SIMD).  EINVAL where a
  * configuration does not fit the shape. */
@@ -354,6 +355,11 @@ size_t lazyllm_op_gemm_workspace_bytes(void);
 int lazyllm_op_gemm(const void* A, const void* W, void* C, const void* R, int32_t M, int32_t N,
                     int32_t K, int32_t lda, int32_t ldw, int32_t ldc, int32_t epilogue,
                     void* workspace, size_t ws_bytes, void* hip_stream);
+
+/* The tile on which the weight-streaming kernel runs a shape (host only, nothing is enqueued):
+ * plan = {row blocks of 16, column waves of 32 features, K groups of a workgroup, K splits over
+ * workgroups}.  EINVAL where the library leaves the shape to the tile kernels. */
+int lazyllm_op_gemm_stream_plan(int32_t M, int32_t N, int32_t K, int32_t plan[4]);
 
 /* lazyllm_op_gemm with RMSNorm (the pre-norm of Sec. 3.1's Llama blocks) folded in, the form
  * the prefill runs.  ssq: uint64 [M], a row's sum of squares in 2^-32 fixed point.
@@ -386,8 +392,9 @@ int lazyllm_op_pack_weight_ksteps(const void* W, int32_t N, int32_t K, int32_t l
  * the model: measurement and tests).  W [N, K] bf16 (device, row stride ldw elements) is rewritten
  * into `packed` (N * K * 2 bytes, device, 16-byte aligned): for every group of 128 output
  * features and every 32-element K step the 8 KB of its eight operand blocks, stored
- * contiguously, steps of a group one after the other: a block of 16 features is 1 KB in one piece.  N % 128 == 0, K % 64 == 0.  lazyllm_op_gemm reads such a weight when bit 30 of
- * `epilogue` is set together with the forced configuration 8 (ldw is then ignored). */
+ * contiguously, steps of a group one after the other: a block of 16 features is 1 KB in one piece.
+ * N % 128 == 0, K % 64 == 0.  lazyllm_op_gemm reads such a weight when bit 30 of `epilogue` is set
+ * together with the forced configuration 8 (ldw is then ignored). */
 int lazyllm_op_pack_weight_stream(const void* W, int32_t N, int32_t K, int32_t ldw, void* packed,
                                   void* hip_stream);
 

@@ -123,6 +123,7 @@ _SIGNATURES = {
     "lazyllm_op_gemm": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32,
                                   C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                   C.c_void_p, C.c_size_t, C.c_void_p]),
+    "lazyllm_op_gemm_stream_plan": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]),
     "lazyllm_op_gemm_rmsnorm": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32,
                                           C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                           C.c_int32, C.c_void_p, C.c_float, C.c_void_p, C.c_void_p,
@@ -321,6 +322,12 @@ def lazyllm_op_gemm(A, W, Cout, R, M, N, K, lda, ldw, ldc, epilogue, stream=None
     wsb = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().lazyllm_op_gemm(_ptr(A), _ptr(W), _ptr(Cout), _ptr(R), M, N, K, lda, ldw, ldc,
                                  epilogue, _ptr(workspace), wsb, _stream_ptr(stream)))
+
+
+def lazyllm_op_gemm_stream_plan(M, N, K):
+    """(row blocks, column waves, K groups, K splits) of the weight-streaming kernel, or None where the tile kernels serve the shape."""
+    plan = (C.c_int32 * 4)()
+    return tuple(plan) if lib().lazyllm_op_gemm_stream_plan(M, N, K, plan) == LAZYLLM_OK else None
 
 
 def lazyllm_op_gemm_rmsnorm(A, W, Cout, R, M, N, K, lda, ldw, ldc, epilogue, ssq_in=None, eps=1e-5,

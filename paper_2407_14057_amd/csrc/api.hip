@@ -1099,7 +1099,7 @@ int lazyllm_op_gemm(const void* A, const void* W, void* C, const void* R, int32_
   if (M == 0) return LAZYLLM_OK;
   if (workspace != nullptr && ((uintptr_t)workspace & 255) != 0) return LAZYLLM_EINVAL;
   const int forced = (epilogue >> 8) & 0xff;
-  if (forced == 8 && M > 32) return LAZYLLM_EINVAL;
+  if (forced == 8 && !gemm_stream_takes(M, N, K)) return LAZYLLM_EINVAL;
   if ((forced == 8 || forced == 9 || forced == 10) && (workspace == nullptr || ws_bytes < gemm_workspace_bytes()))
     return LAZYLLM_EINVAL;
   EpiArgs ea{};
@@ -1112,6 +1112,11 @@ int lazyllm_op_gemm(const void* A, const void* W, void* C, const void* R, int32_
   LZ_HIP(launch_gemm(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, (hipStream_t)hip_stream, &ea,
                      workspace, ws_bytes));
   return LAZYLLM_OK;
+}
+
+int lazyllm_op_gemm_stream_plan(int32_t M, int32_t N, int32_t K, int32_t plan[4]) {
+  if (plan == nullptr) return LAZYLLM_EINVAL;
+  return gemm_stream_takes(M, N, K, plan) ? LAZYLLM_OK : LAZYLLM_EINVAL;
 }
 
 int lazyllm_op_gemm_rmsnorm(const void* A, const void* W, void* C, const void* R, int32_t M,

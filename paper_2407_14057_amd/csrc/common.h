@@ -207,8 +207,9 @@ hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, 
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra,
                           hipStream_t st);
 // The weight-streaming kernel for few rows (gemm_stream.hip).  part: fp32 partial sums of K splits;
-// tickets: zero before the first launch, zero again after each.
-bool gemm_stream_takes(int M, int N, int K);
+// tickets: zero before the first launch, zero again after each.  takes(): whether its rule takes the
+// shape, and on which tile (row blocks, column waves, K groups, K splits).
+bool gemm_stream_takes(int M, int N, int K, int* tile = nullptr);
 hipError_t launch_gemm_stream(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                               int lda, int ldw, int ldc, int epi, const EpiArgs& ra, void* part,
                               size_t part_bytes, unsigned* tickets, size_t ticket_count, hipStream_t st);

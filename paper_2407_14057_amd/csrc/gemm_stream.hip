@@ -480,9 +480,13 @@ static bool stream_plan(int M, int N, int K, StreamPlan* p) {
   return best > 0.0;
 }
 
-bool gemm_stream_takes(int M, int N, int K) {
+bool gemm_stream_takes(int M, int N, int K, int* tile) {
   StreamPlan p;
-  return M > 0 && N % 128 == 0 && K % BK == 0 && stream_plan(M, N, K, &p);
+  if (M <= 0 || N <= 0 || K <= 0 || N % 128 != 0 || K % BK != 0 || !stream_plan(M, N, K, &p)) return false;
+  if (tile != nullptr) {
+    tile[0] = p.tm; tile[1] = p.cw; tile[2] = p.kw; tile[3] = p.ks;
+  }
+  return true;
 }
 
 hipError_t launch_gemm_stream(const void* A, const void* W, void* C, const void* R, int M, int N, int K, int lda,

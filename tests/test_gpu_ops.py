@@ -173,7 +173,7 @@ def test_gemm_tile_of_32_row_waves(M, N, K, epi):
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 def test_gemm_skinny_streamed_weight_layout(M, N, K, epi):
     """The weight rewritten as sequential streams (lazyllm_op_pack_weight_stream) must give the
-    bits of the row-major weight: the kernel sees the same LDS slots either way."""
+    bits of the row-major weight: the same operands reach the products in the same order either way."""
     rng = np.random.default_rng(M * 13 + N + K + epi)
     A = _rand_bf16(rng, (M, K))
     Wbig = _rand_bf16(rng, (N, K + 8), 1.0 / math.sqrt(K))      # a row stride above K
@@ -238,13 +238,70 @@ def test_gemm_k_step_major_weight_layout(cfg, M, N, K, epi):
     assert torch.equal(outs[0], outs[1])
 
 
-def test_gemm_skinny_refuses_more_than_32_rows():
-    A = torch.zeros(33, 64, dtype=torch.bfloat16, device=DEV)
-    W = torch.zeros(128, 64, dtype=torch.bfloat16, device=DEV)
-    Cout = torch.zeros(33, 128, dtype=torch.bfloat16, device=DEV)
+def test_gemm_streaming_refuses_rows_beyond_its_rule():
+    M, N, K = 641, 128, 1088
+    assert B.lazyllm_op_gemm_stream_plan(M, N, K) is None and B.lazyllm_op_gemm_stream_plan(M - 1, N, K) is not None
+    A = torch.zeros(M, K, dtype=torch.bfloat16, device=DEV)
+    W = torch.zeros(N, K, dtype=torch.bfloat16, device=DEV)
+    Cout = torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
     ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
     with pytest.raises(B.LazyLLMError):
-        B.lazyllm_op_gemm(A, W, Cout, None, 33, 128, 64, 64, 64, 128, B.EPI_STORE | (8 << 8), workspace=ws)
+        B.lazyllm_op_gemm(A, W, Cout, None, M, N, K, K, K, N, B.EPI_STORE | (8 << 8), workspace=ws)
+
+
+# (row blocks, column waves, K groups, K splits) and a shape that takes them: every tile that is built,
+# one row chunk or several, with and without a K split; rows one past a block or a chunk; column waves
+# that are not a multiple of the three, six or twelve of a workgroup; odd numbers of K units
+STREAM_TILES = [
+    ((2, 2, 4, 1), 1, 128, 64), ((2, 2, 4, 1), 1000, 256, 704), ((2, 2, 4, 5), 7, 2048, 5504), ((2, 3, 2, 1), 17, 16512, 1088),
+    ((2, 3, 2, 4), 24, 6144, 4096), ((2, 4, 2, 1), 1, 16512, 1088), ((2, 4, 2, 5), 18, 6144, 4096), ((4, 2, 4, 1), 65, 128, 1088),
+    ((4, 2, 4, 2), 65, 128, 2112), ((4, 2, 4, 1), 33, 128, 1088), ((4, 2, 4, 2), 33, 128, 2112), ((4, 3, 2, 1), 33, 16512, 1088),
+    ((4, 3, 2, 4), 33, 4224, 2112), ((4, 4, 2, 1), 33, 24832, 1088), ((4, 4, 2, 1), 33, 28672, 4096), ((4, 4, 2, 5), 40, 6144, 4096),
+    ((6, 3, 2, 1), 65, 4480, 1088), ((6, 3, 2, 2), 65, 4224, 1088), ((6, 3, 2, 1), 257, 1280, 1088), ((6, 3, 2, 4), 289, 256, 2112),
+    ((6, 4, 2, 1), 65, 28672, 4096), ((6, 4, 2, 5), 70, 6144, 4096), ((6, 4, 2, 1), 129, 4096, 1088), ((6, 4, 2, 2), 129, 128, 1088),
+    ((6, 6, 1, 1), 129, 16512, 1088), ((6, 6, 1, 4), 257, 128, 1088), ((6, 12, 1, 1), 257, 16512, 1088), ((6, 12, 1, 5), 257, 6144, 8192),
+    ((8, 2, 4, 4), 65, 4096, 8192), ((8, 2, 4, 4), 128, 4096, 11008), ((8, 3, 2, 1), 97, 6144, 1088), ((8, 3, 2, 2), 97, 4224, 1088),
+    ((8, 3, 2, 1), 385, 1408, 1088), ((8, 3, 2, 4), 513, 128, 2112), ((8, 4, 2, 1), 97, 28672, 4096), ((8, 4, 2, 4), 97, 6272, 2240),
+    ((8, 4, 2, 1), 193, 4096, 1088), ((8, 4, 2, 2), 193, 128, 1088), ((8, 6, 1, 1), 193, 16512, 1088), ((8, 6, 1, 4), 385, 128, 1088),
+    ((8, 8, 1, 1), 129, 24832, 1088), ((8, 8, 1, 8), 97, 8192, 16384), ((8, 12, 1, 1), 513, 9600, 1088), ((8, 12, 1, 4), 400, 5120, 13824),
+    ((10, 12, 1, 1), 513, 20608, 1088), ((10, 12, 1, 4), 513, 5120, 13824),
+]
+
+
+@pytest.mark.parametrize("tile,M,N,K", STREAM_TILES)
+def test_gemm_streaming_tiles(tile, M, N, K):
+    """Every tile of the weight-streaming kernel, all three epilogues: each element against float64, and the
+    same bits from the row-major weight, from its streaming layout and from a second run (sums in a fixed
+    order, tickets back at zero)."""
+    assert B.lazyllm_op_gemm_stream_plan(M, N, K) == tile
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M * 17 + N + K)
+    A = torch.randn(M, K, generator=g, device=DEV).to(torch.bfloat16)
+    W = (torch.randn(N, K, generator=g, device=DEV) / math.sqrt(K)).to(torch.bfloat16)
+    R = torch.randn(M, N, generator=g, device=DEV).to(torch.bfloat16)
+    Wp = torch.empty_like(W)
+    B.lazyllm_op_pack_weight_stream(W, N, K, K, Wp)
+    ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
+    acc = A.double() @ W.double().t()
+    for epi in (B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU):
+        ref, ld = acc, N
+        if epi == B.EPI_RESIDUAL:
+            ref = R.double() + acc
+        elif epi == B.EPI_SWIGLU:
+            blocks = acc.view(M, N // 64, 2, 32)
+            ref, ld = (torch.nn.functional.silu(blocks[:, :, 0]) * blocks[:, :, 1]).reshape(M, N // 2), N // 2
+        outs = []
+        for w, flag in ((W, 0), (Wp, 1 << 30), (Wp, 1 << 30)):
+            Cout = R.clone() if epi == B.EPI_RESIDUAL else torch.full((M, ld), 7.0, dtype=torch.bfloat16, device=DEV)
+            B.lazyllm_op_gemm(A, w, Cout, Cout if epi == B.EPI_RESIDUAL else None, M, N, K, K, K, ld, epi | (8 << 8) | flag,
+                              workspace=ws)
+            torch.cuda.synchronize()
+            assert int(ws[-8192:].view(torch.int32).abs().sum()) == 0
+            outs.append(Cout)
+        # half an ulp of the bf16 result and the fp32 sums, as for the other kernels above
+        bad = (outs[0].double() - ref).abs() > 2.0 ** -8 * ref.abs() + 2e-3
+        assert not bool(bad.any()), (epi, int(bad.sum()))
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[1], outs[2]), epi
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (355, 4096, 4096), (1182, 4096, 1408), (130, 256, 11008),

@@ -176,3 +176,35 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+# the tiles gemm_stream.hip builds; three- and four-wave tiles of two or four row blocks: one row chunk only
+_BUILT = {(2, 2, 4), (4, 2, 4), (8, 2, 4), (2, 3, 2), (4, 3, 2), (2, 4, 2), (4, 4, 2), (6, 3, 2), (8, 3, 2), (6, 4, 2), (8, 4, 2),
+          (6, 6, 1), (8, 6, 1), (8, 8, 1), (6, 12, 1), (8, 12, 1), (10, 12, 1)}
+_MODELS = {"7b": (4096, 4096, 11008), "grouped query 8b": (4096, 1024, 14336), "narrow": (1280, 1280, 3456), "2048": (2048, 512, 8192),
+           "3072": (3072, 1024, 8192), "5120": (5120, 5120, 13824), "8192": (8192, 1024, 28672), "tiny": (256, 256, 704), "1024": (1024, 1024, 2816)}
+
+
+def _projections(d, kv, ffn):
+    return [(d + 2 * kv, d), (d, d), (2 * ffn, d), (d, ffn)]
+
+
+def test_streaming_plan_returns_tiles_that_are_built():
+    for d, kv, ffn in _MODELS.values():
+        for N, K in _projections(d, kv, ffn):
+            for M in range(1, 700):
+                p = B.lazyllm_op_gemm_stream_plan(M, N, K)
+                if p is None:
+                    assert M > 32, (M, N, K)                 # few rows always stream
+                    continue
+                tm, cw, kw, ks = p
+                assert (tm, cw, kw) in _BUILT, (M, N, K, p)
+                assert ks >= 1 and ks * kw <= max(K // 64, kw), (M, N, K, p)
+                assert cw % 3 == 0 or N % (cw * 32) == 0, (M, N, K, p)
+                if cw in (3, 4) and tm in (2, 4):
+                    assert M <= tm * 16, (M, N, K, p)
+    assert B.lazyllm_op_gemm_stream_plan(0, 4096, 4096) is None
+    assert B.lazyllm_op_gemm_stream_plan(1, 4000, 4096) is None and B.lazyllm_op_gemm_stream_plan(1, 4096, 100) is None
+    assert B.lib().lazyllm_op_gemm_stream_plan(1, 128, 64, None) == B.LAZYLLM_EINVAL
+    # a forced streaming launch beyond the rule is refused before the device is touched
+    assert B.lib().lazyllm_op_gemm(16, 16, 16, None, 641, 128, 1088, 1088, 1088, 128, 8 << 8, 256, 1 << 30, None) == B.LAZYLLM_EINVAL
