@@ -1425,7 +1425,9 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
     // the 192-row tile is taken when its count aligns too and it pads fewer rows (O projection at
     // 600 / 768 / 861 / 1000 rows: 49 -> 46, 56 -> 49, 57 -> 50, 59 -> 57 us; down projection at
     // 861 / 1000 rows, 64 tiles of 256 rows in four pieces each: 111 -> 95, 122 -> 106).
-    if ((epilogue == EPI_STORE || epilogue == EPI_RESIDUAL) && ra.psk_ready && sk_ws != nullptr &&
+    // Not with a K of at most 1024: sixteen steps are shorter than the exchange (8192 rows, N = 512,
+    // K = 512: 36 us against 13 on 128x128 tiles; 4096 rows, N = K = 1024: 40 against 19).
+    if (K > 1024 && (epilogue == EPI_STORE || epilogue == EPI_RESIDUAL) && ra.psk_ready && sk_ws != nullptr &&
         sk_ws_bytes >= gemm_workspace_bytes() && N % 256 == 0 && fits32) {
       const long t192 = (long)((M + 191) / 192) * (N / 256);
       const long least = K >= 8192 ? 48 : 64;

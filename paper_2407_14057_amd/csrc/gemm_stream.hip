@@ -399,10 +399,20 @@ static hipError_t launch_stream_cfg(const void* A, const void* W, void* C, const
 // ------------------------------------------------------------------------------------------
 // Tile by shape: TM row blocks per chunk, CW x KW waves, ks K splits.  false: the tile kernels are
 // the better ones there.
-//   K up to 1024: any number of rows, on two x four waves, in chunks as tall as still make about two
-//     workgroups per CU.  Such a launch is a chain of latencies, not a stream (one to four steps;
-//     512 rows, N = 256, K = 704: 12.3 us on the tile kernels' eleven steps), and the sums come in
-//     the same order whatever the number of rows: a packed batch gives the bits of its prompts.
+//   K up to 1024: two x four waves, in the shortest chunks whose workgroups go through the 32 CUs of
+//     an XCD at once (those of a column group share an XCD), and up to 32 rows in any case.  Such a
+//     launch is a chain of latencies, not a stream: one to four steps where the tile kernels make up
+//     to sixteen.  In one round it is the faster one, in more the tile kernels are, whose tiles reread
+//     A less and overlap one tile's stores with the next one's loads.  Measured, streaming / tile, us:
+//       N 1536 K 512   640 rows, 30 workgroups per XCD  7.0 / 11.9;  1536 rows, 36  18.6 / 12.4
+//       N 1024 K 1024  2048 rows, 32  14.6 / 16.6;  2560 rows, 40  24.5 / 17.3;  8192 rows  63 / 40
+//       N 8192 K 1024 (gate/up)  256 rows, 32  12.9 / 18.2;  384 rows, 48  23.6 / 19.1;  2048 rows  95 / 37
+//     3584 rows end it for narrow N too: N 512 K 960 15.9 / 15.9 at 3072 rows, 17.6 / 16.1 at 4096.
+//     A K of one step (up to 256) goes on to two and a half rounds of the tallest chunks, so that a
+//     packed batch of up to 3584 rows of such a model has the bits of its prompts run alone (the sums
+//     come in the same order whatever the rows).  There QKV, O, gate/up and down (N 768, 256, 1408,
+//     256) take 8.9 + 5.4 + 11.2 + 7.2 / 9.8 + 9.3 + 7.5 + 13.1 at 2048 rows and, the price of it,
+//     12.6 + 8.1 + 14.8 + 13.0 / 10.1 + 9.5 + 9.1 + 13.4 at 3072.
 //   Longer K, up to 640 rows: of the tiles below the one whose estimated time is the shortest, among
 //     those that need one workgroup per CU at most.  From 32 rows on a workgroup's own time counts
 //     (its LDS reads and products do not hide under the stream), so what wins is the tile that spreads
@@ -431,10 +441,13 @@ struct StreamPlan {
 static bool stream_plan(int M, int N, int K, StreamPlan* p) {
   const int n64 = N / 64, units = K / BK;
   if (units <= 16) {
-    p->cw = 2;
-    p->kw = 4;
-    p->ks = 1;
-    p->tm = (long)n64 * ((M + 31) / 32) <= 512 ? 2 : (long)n64 * ((M + 63) / 64) <= 512 ? 4 : 8;
+    auto per_xcd = [&](int tm) { return (long)((n64 + 7) / 8) * ((M + tm * 16 - 1) / (tm * 16)); };
+    *p = StreamPlan{2, 2, 4, 1};
+    if (M <= 32 || per_xcd(2) <= 32) return true;
+    if (M > 3584) return false;
+    if (per_xcd(4) <= 32) p->tm = 4;
+    else if (per_xcd(8) <= 32) p->tm = 8;
+    else return units <= 4 && per_xcd(8) <= 80;
     return true;
   }
   if (M > 640) return false;

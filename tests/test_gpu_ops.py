@@ -253,7 +253,8 @@ def test_gemm_streaming_refuses_rows_beyond_its_rule():
 # one row chunk or several, with and without a K split; rows one past a block or a chunk; column waves
 # that are not a multiple of the three, six or twelve of a workgroup; odd numbers of K units
 STREAM_TILES = [
-    ((2, 2, 4, 1), 1, 128, 64), ((2, 2, 4, 1), 1000, 256, 704), ((2, 2, 4, 5), 7, 2048, 5504), ((2, 3, 2, 1), 17, 16512, 1088),
+    ((2, 2, 4, 1), 1, 128, 64), ((2, 2, 4, 1), 1000, 256, 704), ((4, 2, 4, 1), 512, 2048, 1024), ((8, 2, 4, 1), 1000, 2048, 1024),
+    ((8, 2, 4, 1), 700, 1408, 256), ((2, 2, 4, 1), 1500, 1408, 256), ((2, 2, 4, 5), 7, 2048, 5504), ((2, 3, 2, 1), 17, 16512, 1088),
     ((2, 3, 2, 4), 24, 6144, 4096), ((2, 4, 2, 1), 1, 16512, 1088), ((2, 4, 2, 5), 18, 6144, 4096), ((4, 2, 4, 1), 65, 128, 1088),
     ((4, 2, 4, 2), 65, 128, 2112), ((4, 2, 4, 1), 33, 128, 1088), ((4, 2, 4, 2), 33, 128, 2112), ((4, 3, 2, 1), 33, 16512, 1088),
     ((4, 3, 2, 4), 33, 4224, 2112), ((4, 4, 2, 1), 33, 24832, 1088), ((4, 4, 2, 1), 33, 28672, 4096), ((4, 4, 2, 5), 40, 6144, 4096),
@@ -329,11 +330,12 @@ def test_gemm_stream_k(M, N, K, epi):
 @pytest.mark.parametrize("epi,M,N,K", [(B.EPI_SWIGLU, 355, 22016, 256), (B.EPI_SWIGLU, 450, 22016, 128),
                                        (B.EPI_SWIGLU, 600, 22016, 192), (B.EPI_SWIGLU, 1000, 22016, 128),
                                        (B.EPI_RESIDUAL, 600, 4096, 512), (B.EPI_RESIDUAL, 861, 4096, 512),
-                                       (B.EPI_RESIDUAL, 861, 4096, 8192), (B.EPI_STORE, 700, 12288, 256)])
+                                       (B.EPI_RESIDUAL, 861, 4096, 8192), (B.EPI_STORE, 700, 12288, 256),
+                                       (B.EPI_RESIDUAL, 600, 4096, 1088), (B.EPI_RESIDUAL, 861, 4096, 1088)])
 def test_gemm_library_choice_with_a_workspace(epi, M, N, K):
     """With a workspace the library may choose the persistent stream-K schedule on its own: gate/up
     with a last round two thirds empty (172 or 344 tiles of either height), the O and down
-    projections at 64 - 127 aligned tiles, a last round 0.4 or more empty.  Every element against the
+    projections at 64 - 127 aligned tiles (K above 1024), a last round 0.4 or more empty.  Every element against the
     definition, the same bits twice, flags back at zero."""
     rng = np.random.default_rng(epi * 977 + M + N + K)
     A = _rand_bf16(rng, (M, K))

@@ -208,3 +208,27 @@ def test_streaming_plan_returns_tiles_that_are_built():
     assert B.lib().lazyllm_op_gemm_stream_plan(1, 128, 64, None) == B.LAZYLLM_EINVAL
     # a forced streaming launch beyond the rule is refused before the device is touched
     assert B.lib().lazyllm_op_gemm(16, 16, 16, None, 641, 128, 1088, 1088, 1088, 128, 8 << 8, 256, 1 << 30, None) == B.LAZYLLM_EINVAL
+
+
+def test_streaming_plan_of_a_short_k_ends_after_one_round_of_the_compute_units():
+    """K up to 1024: whatever the widths, no more workgroups than the 32 compute units of an XCD hold at
+    once, beyond that the tile kernels (twice to three times as fast from a few rounds on).  The one
+    exception is a K of one step, up to the row count for which packed prompts keep their own bits."""
+    for d, kv, ffn in [(256, 256, 704), (512, 512, 960), (768, 768, 1024), (1024, 1024, 1024), (1024, 256, 4096)]:
+        for N, K in _projections(d, kv, ffn):
+            if K > 1024:
+                continue
+            taken = 0
+            for M in list(range(1, 600)) + list(range(600, 17000, 37)):
+                p = B.lazyllm_op_gemm_stream_plan(M, N, K)
+                if p is None:
+                    continue
+                taken = M
+                per_xcd = -(-(N // 64) // 8) * -(-M // (p[0] * 16))
+                assert M <= 32 or per_xcd <= 32 or (K <= 256 and M <= 3584), (M, N, K, p, per_xcd)
+            assert 128 <= taken <= 3584, (N, K, taken)
+    for M, N, K in [(2048, 8192, 1024), (8192, 1024, 1024), (1536, 1536, 512), (4096, 256, 256), (16384, 256, 704)]:
+        assert B.lazyllm_op_gemm_stream_plan(M, N, K) is None, (M, N, K)
+    # the packed batch of a thousand short prompts and each of its prompts: the same kernel, the same order of sums
+    for N, K in _projections(256, 256, 704):
+        assert B.lazyllm_op_gemm_stream_plan(3094, N, K)[1:] == B.lazyllm_op_gemm_stream_plan(5, N, K)[1:]
