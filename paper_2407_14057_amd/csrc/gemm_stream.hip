@@ -428,6 +428,8 @@ static hipError_t launch_stream_cfg(const void* A, const void* W, void* C, const
 //     Measured, cold weights, the same kernel with 4 or 8 column waves / best tile kernel -> now:
 //       gate/up  64 rows 37 / 59 -> 34, 97: 43 / 59 -> 40, 176: 72 / 68 -> 52, 256: 67 / 85 -> 59,
 //                355: 113 / 94 -> 79, 512: 123 / 107 -> 92, 613: - / 148 -> 107
+//       gate/up  N 28672, eight row blocks on twelve waves from 289 rows (six make a fourth chunk, 300
+//                workgroups): 289 rows - / 107 -> 92, 384: - / 110 -> 98
 //       QKV      64 rows 26 / 59 -> 24, 128: 35 / 62 -> 31, 192: 41 / 62 -> 37, 256: 47 / 62 -> 42,
 //                355: 72 / 72 -> 52, 512: - / 79 -> 62, 613: - / 91 -> 69
 //       down     97 rows 30 / 41 -> 28, 512: 66 / 72 -> 62, 613: - / 91 -> 74;  O  613: - / 51 -> 40
@@ -487,6 +489,7 @@ static bool stream_plan(int M, int N, int K, StreamPlan* p) {
     consider(tm, 6, 1);
     consider(tm, 12, 1);
     if (M > 384) consider(10, 12, 1);
+    else if (M > 256 && n64 > 384) consider(8, 12, 1);   // (six blocks: four chunks, two rounds)
     // (beyond 128 rows only in one round: the tile kernels are better at several)
     if (M > 128 && (N / 32 + p->cw * 8 - 1) / (p->cw * 8) * ((M + p->tm * 16 - 1) / (p->tm * 16)) > 32) return false;
   }

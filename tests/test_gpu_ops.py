@@ -264,7 +264,7 @@ STREAM_TILES = [
     ((8, 2, 4, 4), 65, 4096, 8192), ((8, 2, 4, 4), 128, 4096, 11008), ((8, 3, 2, 1), 97, 6144, 1088), ((8, 3, 2, 2), 97, 4224, 1088),
     ((8, 3, 2, 1), 385, 1408, 1088), ((8, 3, 2, 4), 513, 128, 2112), ((8, 4, 2, 1), 97, 28672, 4096), ((8, 4, 2, 4), 97, 6272, 2240),
     ((8, 4, 2, 1), 193, 4096, 1088), ((8, 4, 2, 2), 193, 128, 1088), ((8, 6, 1, 1), 193, 16512, 1088), ((8, 6, 1, 4), 385, 128, 1088),
-    ((8, 8, 1, 1), 129, 24832, 1088), ((8, 8, 1, 8), 97, 8192, 16384), ((8, 12, 1, 1), 513, 9600, 1088), ((8, 12, 1, 4), 400, 5120, 13824),
+    ((8, 8, 1, 1), 129, 24832, 1088), ((8, 8, 1, 8), 97, 8192, 16384), ((8, 12, 1, 1), 289, 28672, 1088), ((8, 12, 1, 1), 513, 9600, 1088), ((8, 12, 1, 4), 400, 5120, 13824),
     ((10, 12, 1, 1), 513, 20608, 1088), ((10, 12, 1, 4), 513, 5120, 13824),
 ]
 

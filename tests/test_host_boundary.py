@@ -232,3 +232,14 @@ def test_streaming_plan_of_a_short_k_ends_after_one_round_of_the_compute_units()
     # the packed batch of a thousand short prompts and each of its prompts: the same kernel, the same order of sums
     for N, K in _projections(256, 256, 704):
         assert B.lazyllm_op_gemm_stream_plan(3094, N, K)[1:] == B.lazyllm_op_gemm_stream_plan(5, N, K)[1:]
+
+
+def test_streaming_plan_has_no_holes_in_the_rows_of_the_shipped_models():
+    """Once the tile kernels take a projection of the 4096-wide models, they take it at every larger row count."""
+    for d, kv, ffn in (_MODELS["7b"], _MODELS["grouped query 8b"]):
+        for N, K in _projections(d, kv, ffn):
+            taken = [M for M in range(1, 900) if B.lazyllm_op_gemm_stream_plan(M, N, K) is not None]
+            assert taken == list(range(1, len(taken) + 1)), (N, K, [a for a, b in zip(taken, taken[1:]) if b != a + 1])
+            assert len(taken) == (480 if N == 28672 else 640)
+    for M in (289, 355, 384):
+        assert B.lazyllm_op_gemm_stream_plan(M, 28672, 4096) == (8, 12, 1, 1)
