@@ -433,6 +433,15 @@ static hipError_t launch_stream_cfg(const void* A, const void* W, void* C, const
 //       QKV      64 rows 26 / 59 -> 24, 128: 35 / 62 -> 31, 192: 41 / 62 -> 37, 256: 47 / 62 -> 42,
 //                355: 72 / 72 -> 52, 512: - / 79 -> 62, 613: - / 91 -> 69
 //       down     97 rows 30 / 41 -> 28, 512: 66 / 72 -> 62, 613: - / 91 -> 74;  O  613: - / 51 -> 40
+//     The estimate is fitted to 4096-wide models.  Over 450 random shapes (K 1088 .. 29000, 17 .. 640
+//     rows) its tile is ahead of the tile kernels or within 4 % (461 rows, N 2176, K 8064: 4 .. 8 % behind),
+//     but for these, left out:
+//       twelve waves unsplit on fewer than 168 CUs (N not a multiple of 256, where eight waves do not
+//       fit): N 24704, 160 / 200 rows 78 / 87 against 69 / 72; N 15488, 257 rows 41 against 36
+//       N 4352 .. 5120, K from 8192, 289 .. 384 rows: 57 .. 86 against 55 .. 80
+//     and for these, on the next best tile instead:
+//       one K group, N below 1024, K below 2048, 385 rows and more: 19 .. 26 against 17 .. 19, now 16 .. 18
+//       twelve waves, K from 16384, up to 128 rows: N 8192 K 28672, 65 rows 111 against 103, now 82
 //     768 rows and taller chunks (TM 12): the accumulators spill beside twelve waves (328 us).
 // ks: every split has at least four steps.
 // ------------------------------------------------------------------------------------------
@@ -485,13 +494,18 @@ static bool stream_plan(int M, int N, int K, StreamPlan* p) {
     const int tm = M <= 96 || (M > 128 && M <= 192) || (M > 256 && M <= 384) ? 6 : 8;
     consider(tm, 4, 2);
     consider(tm, 3, 2);
-    consider(8, 8, 1);
-    consider(tm, 6, 1);
-    consider(tm, 12, 1);
-    if (M > 384) consider(10, 12, 1);
-    else if (M > 256 && n64 > 384) consider(8, 12, 1);   // (six blocks: four chunks, two rounds)
+    if (n64 >= 16 || units >= 32 || M <= 384) {
+      consider(8, 8, 1);
+      consider(tm, 6, 1);
+      if (M > 128 || units < 256) consider(tm, 12, 1);
+      if (M > 384) consider(10, 12, 1);
+    }
+    if (M > 256 && M <= 384 && n64 > 384) consider(8, 12, 1);   // (six blocks: four chunks, two rounds)
     // (beyond 128 rows only in one round: the tile kernels are better at several)
-    if (M > 128 && (N / 32 + p->cw * 8 - 1) / (p->cw * 8) * ((M + p->tm * 16 - 1) / (p->tm * 16)) > 32) return false;
+    const int cols = (N / 32 + p->cw - 1) / p->cw, chunks = (M + p->tm * 16 - 1) / (p->tm * 16);
+    if (M > 128 && (cols + 7) / 8 * chunks > 32) return false;
+    if (p->cw == 12 && p->ks == 1 && M <= 288 && cols * chunks < 168) return false;
+    if (!narrow && n64 <= 80 && units >= 128 && M > 288 && M <= 384) return false;
   }
   return best > 0.0;
 }

@@ -260,10 +260,10 @@ STREAM_TILES = [
     ((4, 3, 2, 4), 33, 4224, 2112), ((4, 4, 2, 1), 33, 24832, 1088), ((4, 4, 2, 1), 33, 28672, 4096), ((4, 4, 2, 5), 40, 6144, 4096),
     ((6, 3, 2, 1), 65, 4480, 1088), ((6, 3, 2, 2), 65, 4224, 1088), ((6, 3, 2, 1), 257, 1280, 1088), ((6, 3, 2, 4), 289, 256, 2112),
     ((6, 4, 2, 1), 65, 28672, 4096), ((6, 4, 2, 5), 70, 6144, 4096), ((6, 4, 2, 1), 129, 4096, 1088), ((6, 4, 2, 2), 129, 128, 1088),
-    ((6, 6, 1, 1), 129, 16512, 1088), ((6, 6, 1, 4), 257, 128, 1088), ((6, 12, 1, 1), 257, 16512, 1088), ((6, 12, 1, 5), 257, 6144, 8192),
+    ((6, 6, 1, 1), 129, 16512, 1088), ((6, 6, 1, 4), 257, 128, 1088), ((6, 12, 1, 1), 257, 24704, 1088), ((6, 12, 1, 5), 257, 6144, 8192),
     ((8, 2, 4, 4), 65, 4096, 8192), ((8, 2, 4, 4), 128, 4096, 11008), ((8, 3, 2, 1), 97, 6144, 1088), ((8, 3, 2, 2), 97, 4224, 1088),
     ((8, 3, 2, 1), 385, 1408, 1088), ((8, 3, 2, 4), 513, 128, 2112), ((8, 4, 2, 1), 97, 28672, 4096), ((8, 4, 2, 4), 97, 6272, 2240),
-    ((8, 4, 2, 1), 193, 4096, 1088), ((8, 4, 2, 2), 193, 128, 1088), ((8, 6, 1, 1), 193, 16512, 1088), ((8, 6, 1, 4), 385, 128, 1088),
+    ((8, 4, 2, 1), 193, 4096, 1088), ((8, 4, 2, 2), 193, 128, 1088), ((8, 6, 1, 1), 193, 16512, 1088), ((8, 6, 1, 8), 385, 128, 2112),
     ((8, 8, 1, 1), 129, 24832, 1088), ((8, 8, 1, 8), 97, 8192, 16384), ((8, 12, 1, 1), 289, 28672, 1088), ((8, 12, 1, 1), 513, 9600, 1088), ((8, 12, 1, 4), 400, 5120, 13824),
     ((10, 12, 1, 1), 513, 20608, 1088), ((10, 12, 1, 4), 513, 5120, 13824),
 ]

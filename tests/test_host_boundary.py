@@ -243,3 +243,17 @@ def test_streaming_plan_has_no_holes_in_the_rows_of_the_shipped_models():
             assert len(taken) == (480 if N == 28672 else 640)
     for M in (289, 355, 384):
         assert B.lazyllm_op_gemm_stream_plan(M, 28672, 4096) == (8, 12, 1, 1)
+
+
+def test_streaming_plan_leaves_out_the_tiles_that_lose_to_the_tile_kernels():
+    plan = B.lazyllm_op_gemm_stream_plan
+    for N in (24704, 26752, 30848):                          # half the chip idle on twelve waves
+        for M in (129, 160, 200, 256):
+            assert plan(M, N, 4096) is None, (M, N)
+    assert plan(257, 15488, 2048) is None and plan(257, 24704, 4096) == (6, 12, 1, 1) and plan(257, 22016, 4096) == (6, 12, 1, 1)
+    for N, K in ((4352, 11008), (5120, 8192), (5120, 13824)):
+        assert all(plan(M, N, K) is None for M in range(289, 385)) and plan(288, N, K) is not None and plan(385, N, K) is not None
+    for N in (256, 512, 768):
+        for K in (1088, 1408):
+            assert all(plan(M, N, K)[2] > 1 for M in range(385, 641))
+    assert plan(65, 8192, 28672) == (6, 4, 2, 4)
