@@ -439,6 +439,10 @@ int lazyllm_op_qkv_rope(const void* x, const void* wqkv, const int32_t* pos, int
                         void* rope_table, void* q, void* k, void* v, int32_t rows, int32_t n_heads,
                         int32_t head_dim, float theta, void* hip_stream);
 
+/* Into how many key ranges a decoding step splits the attention of `rows` >= 2 token rows that run a
+ * layer (host only, nothing is enqueued).  At least 1; EINVAL for arguments no step has. */
+int lazyllm_op_decode_key_splits(int32_t rows, int32_t n_keys, int32_t n_heads, int32_t head_dim);
+
 /* Transposed copy vt[H, hd, vt_ld] of v[rows, H, hd] that the attention kernel
  * reads (columns rows..roundup(rows,64)-1 are zeroed; vt_ld % 64 == 0). */
 int lazyllm_op_v_transpose(const void* v, void* vt, int32_t vt_ld, int32_t rows, int32_t n_heads,

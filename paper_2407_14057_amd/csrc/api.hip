@@ -1231,6 +1231,11 @@ int lazyllm_op_qkv_rope(const void* x, const void* wqkv, const int32_t* pos, int
   return LAZYLLM_OK;
 }
 
+int lazyllm_op_decode_key_splits(int32_t rows, int32_t n_keys, int32_t n_heads, int32_t head_dim) {
+  if (rows < 2 || n_keys <= 0 || n_heads <= 0 || (head_dim != 64 && head_dim != 128)) return LAZYLLM_EINVAL;
+  return decode_key_splits(rows, n_keys, n_heads, head_dim, decode_attention_workspace_bytes(n_heads * head_dim, n_heads));
+}
+
 int lazyllm_op_v_transpose(const void* v, void* vt, int32_t vt_ld, int32_t rows, int32_t n_heads,
                            int32_t head_dim, void* hip_stream) {
   if (!v || !vt || rows <= 0 || n_heads <= 0 || (head_dim != 64 && head_dim != 128) ||

@@ -313,6 +313,8 @@ hipError_t launch_decode_attention(const void* q, const int32_t* qpos, int M, co
                                    void* split_ws = nullptr, size_t split_ws_bytes = 0,
                                    int kv_group = 1);
 size_t decode_attention_workspace_bytes(int d_model, int n_heads);
+// key ranges over which M >= 2 queries are split
+int decode_key_splits(int M, int n_keys, int n_heads, int head_dim, size_t split_ws_bytes);
 // (the ticket counters at its end must be zero before the first attention launch: launch_gen_embed)
 
 struct PlanArgs {

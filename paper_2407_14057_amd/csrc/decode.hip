@@ -731,6 +731,30 @@ size_t decode_attention_workspace_bytes(int d_model, int n_heads) {
   return (size_t)16 * 128 * ((size_t)d_model * 4 + (size_t)n_heads * 8) + DATT_COUNTER_BYTES;
 }
 
+// A step's queries (the new token and the revived ones) make few workgroups: the keys are split, each
+// split with at least two key tiles, as far as the workspace for the splits' partial results reaches
+// (2 KB per query, head and split, left and merged again: what a split costs).  As many splits as make
+// one round of the 256 CUs, where those fill seven eighths of it: more of them wait less for their keys
+// but merge more.  Where one round leaves more idle (three, five or more blocks of 128 queries of 32
+// heads), or gives each workgroup all of more than 2048 keys, about two workgroups per CU; up to 1024
+// keys the one round always.  Measured with the merge, us, one round / about 512 workgroups:
+//   32 heads, 4096 keys: 128 queries 35 / 44, 256: 54 / 62, 384: 90 / 75, 512: 92 / 92, 640: 159 / 101,
+//                        768: 159 / 122, 1024: 159 / 151
+//             2048 keys: 128: 25 / 37, 256: 34 / 44, 384: 53 / 50, 512: 54 / 59, 640: 82 / 63, 1024: 83 / 90
+//             1024 keys: 128: 23 / 23, 256: 27 / 34, 384: 34 / 38, 512: 36 / 42
+//   40 heads, 4096 keys: 128: 43 / 56, 256: 68 / 77, 384: 92 / 98, 512: 159 / 109, 640: 160 / 143
+//   64 heads, 4096 keys: 128: 55 / 65, 256: 93 / 100, 384: 158 / 123, 512: 160 / 156; 2048 keys, 512: 83 / 90
+int decode_key_splits(int M, int n_keys, int n_heads, int head_dim, size_t split_ws_bytes) {
+  const int base = n_heads * ((M + 127) / 128), tiles = (n_keys + 63) / 64, one = 256 / base;
+  const bool fills = one * base >= 224;
+  int n_splits = tiles <= 16 || (fills && (one > 1 || tiles <= 32)) ? one : 512 / base;
+  if (n_splits > tiles / 2) n_splits = tiles / 2;
+  if (n_splits > 16) n_splits = 16;
+  const size_t per_split = (size_t)M * ((size_t)n_heads * head_dim * 4 + (size_t)n_heads * 8);
+  while (n_splits > 1 && (size_t)n_splits * per_split + DATT_COUNTER_BYTES > split_ws_bytes) --n_splits;
+  return n_splits < 1 ? 1 : n_splits;
+}
+
 hipError_t launch_decode_attention(const void* q, const int32_t* qpos, int M, const void* k,
                                    const void* vt, int vt_ld, const unsigned long long* sel_bits,
                                    int n_keys, void* o, int n_heads, int head_dim, hipStream_t st,
@@ -749,22 +773,8 @@ hipError_t launch_decode_attention(const void* q, const int32_t* qpos, int M, co
     split_ws_bytes -= DATT_COUNTER_BYTES;
     counters = (unsigned*)((char*)split_ws + split_ws_bytes);
   }
-  // A step's queries (the new token and the revived ones) make few workgroups: split the keys so
-  // that about 256 are in flight, each with at least two key tiles, as far as the workspace for
-  // the splits' partial results reaches.  (512 wait less for their keys but leave and merge twice the
-  // partial results, 2 KB per query, head and split: 129 .. 256 queries of 32 heads, 2048 keys,
-  // 30.5 us against 27.7 and the merge besides; four steps after a pruned prefill 0.8 ms of 24.)
-  const int qblocks = (M + 127) / 128, d_model = n_heads * head_dim;
-  int n_splits = 1;
-  if (split_ws != nullptr) {
-    const int tiles = (n_keys + 63) / 64;
-    n_splits = 256 / (n_heads * qblocks);
-    if (n_splits > tiles / 2) n_splits = tiles / 2;
-    if (n_splits > 16) n_splits = 16;
-    const size_t per_split = (size_t)M * ((size_t)d_model * 4 + (size_t)n_heads * 8);
-    while (n_splits > 1 && (size_t)n_splits * per_split > split_ws_bytes) --n_splits;
-    if (n_splits < 1) n_splits = 1;
-  }
+  const int d_model = n_heads * head_dim, qblocks = (M + 127) / 128;
+  int n_splits = split_ws != nullptr ? decode_key_splits(M, n_keys, n_heads, head_dim, split_ws_bytes + DATT_COUNTER_BYTES) : 1;
   // only the new token runs the layer: the streaming kernel, about four 64-key chunks per workgroup
   const bool one_query = M == 1 && split_ws != nullptr && (kv_group == 1 || kv_group == 2 || kv_group == 4);
   if (one_query) {

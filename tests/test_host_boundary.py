@@ -257,3 +257,23 @@ def test_streaming_plan_leaves_out_the_tiles_that_lose_to_the_tile_kernels():
         for K in (1088, 1408):
             assert all(plan(M, N, K)[2] > 1 for M in range(385, 641))
     assert plan(65, 8192, 28672) == (6, 4, 2, 4)
+
+
+def test_decode_key_splits_leave_no_wide_step_on_one_range():
+    """Workgroups of a step's attention (heads x blocks of 128 rows x key ranges): one full round of the 256
+    compute units, else about two per unit; never a single range of a long sequence while the workspace
+    holds another, which took 1.3 to 1.7 times as long."""
+    splits = B.lib().lazyllm_op_decode_key_splits
+    assert [splits(m, 4096, 32, 128) for m in (2, 128, 129, 256, 384, 512, 640, 768, 1024, 1025)] == [8, 8, 4, 4, 5, 2, 3, 2, 2, 1]
+    assert [splits(m, 2048, 32, 128) for m in (128, 256, 384, 512, 640, 768, 1024)] == [8, 4, 5, 2, 3, 2, 1]
+    assert [splits(m, 1024, 32, 128) for m in (128, 256, 384, 512)] == [8, 4, 2, 2]
+    assert [splits(m, 4096, 40, 128) for m in (128, 256, 384, 512, 640)] == [6, 3, 2, 3, 2]
+    for heads, hd in ((4, 64), (8, 64), (32, 128), (40, 128), (64, 128)):
+        for keys in (64, 700, 1500, 2500, 4096, 8192):
+            for m in range(2, 2049, 7):
+                n, base, tiles = splits(m, keys, heads, hd), heads * -(-m // 128), (keys + 63) // 64
+                assert 1 <= n <= 16 and (n == 1 or n <= tiles // 2), (heads, keys, m, n)
+                assert n == 1 or n * m <= 16 * 128, (heads, keys, m, n)          # what the workspace holds
+                if keys > 2048 and base <= 256 and 2 * m <= 16 * 128:
+                    assert n > 1, (heads, keys, m)
+    assert splits(1, 64, 4, 64) == B.LAZYLLM_EINVAL and splits(2, 0, 4, 64) == B.LAZYLLM_EINVAL and splits(2, 64, 4, 96) == B.LAZYLLM_EINVAL
