@@ -34,7 +34,7 @@ def gate_up_traffic_bytes():
 
 
 STEP_KERNEL = {"gemm_gate_up": "gemm_pp_kernel<4,2,2,4,EPI_SWIGLU> (RMSNorm scale + gate/up projection + SiLU*mul; at 355 rows "
-                               "the same epilogue under gemm_psk_kernel<2,4,3,2,EPI_SWIGLU>)",
+                               "the same epilogue under gemm_stream_kernel<EPI_SWIGLU>)",
                "gemm_qkv": "gemm_pp_kernel<4,2,2,4,EPI_QKV_ROPE128> (RMSNorm scale + QKV projection + RoPE + V^T)",
                "gemm_down": "gemm_pp_kernel<4,2,2,4,EPI_RESIDUAL> (down projection + residual + row sums of squares)",
                "gemm_o": "gemm_pp_kernel<4,2,2,4,EPI_RESIDUAL> (O projection + residual + row sums of squares)"}

@@ -25,7 +25,6 @@ __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u 
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 __device__ __forceinline__ float bf16_to_float(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
 
-// 8 bf16 (one 16-byte vector) <-> 8 floats
 // 16 bytes that nobody reads again before the caches have turned over (streams of weights and of K, V)
 __device__ __forceinline__ uint4 load_once(const uint4* p) {
   typedef unsigned int u4 __attribute__((ext_vector_type(4)));
@@ -33,6 +32,7 @@ __device__ __forceinline__ uint4 load_once(const uint4* p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// 8 bf16 (one 16-byte vector) <-> 8 floats
 __device__ __forceinline__ void unpack8(const uint4& v, float* f) {
   f[0] = bf16_lo(v.x); f[1] = bf16_hi(v.x); f[2] = bf16_lo(v.y); f[3] = bf16_hi(v.y);
   f[4] = bf16_lo(v.z); f[5] = bf16_hi(v.z); f[6] = bf16_lo(v.w); f[7] = bf16_hi(v.w);

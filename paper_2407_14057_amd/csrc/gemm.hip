@@ -1412,6 +1412,9 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
     // (operands of 4 GB and more: only the 4-wave kernels, which address with 64-bit offsets)
     const bool fits32 = pp_operands_fit_32bit(M, N, K, lda, ldw, ra.w_blocked != 0);
     const long big_tiles = fits32 ? (long)((M + 255) / 256) * (N / 256) : 0;
+    // (Figures at up to 640 rows, here and below, are those of launches without the weight's streaming
+    // layout, i.e. of the single-step entry points: the model's projections of so few rows go to the
+    // streaming kernel, see the rule further down.)
     // Stream-K pays when the data-parallel grid would leave most CUs idle through a long K
     // loop (measured at M = 355: O projection 46 -> 40 us, down projection 114 -> 70 us); with
     // more tiles the 128x128 partial-sum traffic eats the gain (M = 1182: +-5 %).
