@@ -408,11 +408,12 @@ static hipError_t launch_stream_cfg(const void* A, const void* W, void* C, const
 //       N 1024 K 1024  2048 rows, 32  14.6 / 16.6;  2560 rows, 40  24.5 / 17.3;  8192 rows  63 / 40
 //       N 8192 K 1024 (gate/up)  256 rows, 32  12.9 / 18.2;  384 rows, 48  23.6 / 19.1;  2048 rows  95 / 37
 //     3584 rows end it for narrow N too: N 512 K 960 15.9 / 15.9 at 3072 rows, 17.6 / 16.1 at 4096.
-//     A K of one step (up to 256) goes on to two and a half rounds of the tallest chunks, so that a
-//     packed batch of up to 3584 rows of such a model has the bits of its prompts run alone (the sums
-//     come in the same order whatever the rows).  There QKV, O, gate/up and down (N 768, 256, 1408,
-//     256) take 8.9 + 5.4 + 11.2 + 7.2 / 9.8 + 9.3 + 7.5 + 13.1 at 2048 rows and, the price of it,
-//     12.6 + 8.1 + 14.8 + 13.0 / 10.1 + 9.5 + 9.1 + 13.4 at 3072.
+//     A K of one step (up to 256) goes on to two and a half rounds of the tallest chunks and 3200 rows,
+//     so that a packed batch of so many rows has the bits of its prompts run alone (the sums come in
+//     the same order whatever the rows).  There QKV, O, gate/up and down (N 768, 256, 1536, 256; K 256
+//     and 768) take 8.8 + 5.4 + 11.0 + 7.3 / 9.8 + 9.3 + 7.6 + 13.6 at 2048 rows and, the price of it,
+//     10.5 + 8.0 + 13.0 + 11.4 / 9.9 + 9.5 + 7.9 + 13.9 at 2560, 12.5 + 8.1 + 14.9 + 13.6 / 10.1 + 9.5
+//     + 9.3 + 14.0 at 3072.
 //   Longer K, up to 640 rows: of the tiles below the one whose estimated time is the shortest, among
 //     those that need one workgroup per CU at most.  From 32 rows on a workgroup's own time counts
 //     (its LDS reads and products do not hide under the stream), so what wins is the tile that spreads
@@ -458,7 +459,7 @@ static bool stream_plan(int M, int N, int K, StreamPlan* p) {
     if (M > 3584) return false;
     if (per_xcd(4) <= 32) p->tm = 4;
     else if (per_xcd(8) <= 32) p->tm = 8;
-    else return units <= 4 && per_xcd(8) <= 80;
+    else return units <= 4 && M <= 3200 && per_xcd(8) <= 80;
     return true;
   }
   if (M > 640) return false;

@@ -267,8 +267,9 @@ def test_few_rows_at_the_edges_of_the_streaming_tiles(few_rows_model, n):
 
 @pytest.mark.parametrize("n,gate_up", [(300, 8256), (400, 11072), (520, 11072)])
 def test_few_rows_with_twelve_column_waves(n, gate_up):
-    """Tiles of six, eight and ten row blocks on twelve column waves: gate and up of 516 and 692 column waves
-    (43 workgroups exactly; the last one two thirds full)."""
+    """Tiles of six, eight and ten row blocks on twelve column waves: gate and up of 520 and 696 column waves,
+    padded to whole 128s (the last of 44 workgroups a third full; 58 workgroups exactly)."""
+    assert B.lazyllm_op_gemm_stream_plan(n, (2 * gate_up + 255) // 256 * 256, 2048) == ({300: 6, 400: 8, 520: 10}[n], 12, 1, 1)
     shape = synth.ModelShape(2, 2048, 16, 128, gate_up, 512)
     w = synth.make_weights(shape, 1031, "cpu", gain_jitter=0.3)
     model = B.Model(shape.as_dict(), _to_dev(w), DEV)
