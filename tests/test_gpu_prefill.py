@@ -265,11 +265,11 @@ def test_few_rows_at_the_edges_of_the_streaming_tiles(few_rows_model, n):
     check_against_checker(shape, wb, ids, [], outs[0], verbose="few rows n=%d" % n)
 
 
-@pytest.mark.parametrize("n,gate_up", [(300, 8256), (400, 11072), (520, 11072)])
-def test_few_rows_with_twelve_column_waves(n, gate_up):
-    """Tiles of six, eight and ten row blocks on twelve column waves: gate and up of 520 and 696 column waves,
-    padded to whole 128s (the last of 44 workgroups a third full; 58 workgroups exactly)."""
-    assert B.lazyllm_op_gemm_stream_plan(n, (2 * gate_up + 255) // 256 * 256, 2048) == ({300: 6, 400: 8, 520: 10}[n], 12, 1, 1)
+@pytest.mark.parametrize("n,gate_up,tile", [(300, 8256, (8, 8, 1)), (300, 11072, (6, 12, 1)), (400, 11072, (8, 12, 1)), (520, 11072, (10, 12, 1))])
+def test_few_rows_with_eight_and_twelve_column_waves(n, gate_up, tile):
+    """Tiles of eight column waves and of six, eight and ten row blocks on twelve: gate and up of 520 and 696
+    column waves (each of the two padded to whole 128s), 65 workgroups of eight and 58 of twelve."""
+    assert B.lazyllm_op_gemm_stream_plan(n, (2 * gate_up + 255) // 256 * 256, 2048) == tile + (1,)
     shape = synth.ModelShape(2, 2048, 16, 128, gate_up, 512)
     w = synth.make_weights(shape, 1031, "cpu", gain_jitter=0.3)
     model = B.Model(shape.as_dict(), _to_dev(w), DEV)
