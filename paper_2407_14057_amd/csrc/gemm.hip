@@ -1,8 +1,9 @@
 // bf16 GEMM on the gfx950 matrix cores: C[M,N] = A[M,K] W[N,K]^T, fp32 accumulation.
-// Both operands are K-contiguous, which is the layout v_mfma_f32_32x32x16_bf16 wants:
-// lane l supplies row (l & 31), k elements 8*(l >> 5) .. +8 of a 32x16 operand block.
+// Both operands are K-contiguous, which is the layout the MFMA instructions want: lane l of
+// v_mfma_f32_32x32x16_bf16 supplies row (l & 31), k elements 8*(l >> 5) .. +8 of a 32x16 operand
+// block, of v_mfma_f32_16x16x32_bf16 row (l & 15), k elements 8*(l >> 4) .. +8 of a 16x32 block.
 //
-// Workgroup = WM x WN waves, each wave owns TM x TN blocks of 32x32 (fp32 accumulators stay
+// Workgroup = WM x WN waves, each wave owns TM x TN blocks of 32x32 or 16x16 (fp32 accumulators stay
 // in registers for the whole K loop).  K advances 64 elements per step; the A and W slabs of
 // a step are copied global -> LDS by global_load_lds (no register staging) into one of two
 // LDS stages while the other stage feeds the MFMAs.
@@ -154,7 +155,7 @@ gemm_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   for (int t = 0; t < NS; ++t)
     if (t < KT) issue(t, t * BK);
   float rs[TM];
-  load_row_scales<TM>(rs, ra, M, m0, wm, lane);
+  load_row_scales<32, TM>(rs, ra, M, m0, wm, lane);
   // (three steps in flight: only the first has to be there; the row scales fetched last are needed in the epilogue)
   if (NS == 3 && KT >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * (A_INSTR + W_INSTR)) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -189,7 +190,7 @@ gemm_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #undef LZ_MFMAS
 #undef LZ_SCHED
 
-  gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
+  gemm_epilogue<32, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
 }
 
 template <int WM, int WN, int TM, int TN, int NS = 2>
@@ -240,21 +241,29 @@ static hipError_t launch_cfg(const void* A, const void* W, void* C, const void* 
 // Ping-pong kernel on 8 waves: the 256x256x64 tile as 4 x 2 waves of 64 x 128, or the 192x256x64
 // tile as 2 x 4 waves of 96 x 64 (the figures below are for the first).  The two
 // waves that share a SIMD (wave w and w + 4) run the same loop half a step apart: while one
-// is in a COMPUTE phase (16 back-to-back MFMAs, nothing else), the other is in a MEMORY phase
+// is in a COMPUTE phase (32 back-to-back MFMAs, nothing else), the other is in a MEMORY phase
 // (the 12 LDS reads of its next half step, its global -> LDS copies, the waits).  A workgroup
 // barrier closes every phase, so the matrix pipe of each SIMD always has exactly one wave
 // feeding it and that wave's instruction stream is pure MFMA.
 //   phase p:      0      1      2      3      4    ...
 //   waves 0-3:   M(0a)  C(0a)  M(0b)  C(0b)  M(1a) ...       a, b = first / second half of a
 //   waves 4-7:    -     M(0a)  C(0a)  M(0b)  C(0b) ...              64-wide K step
-// The global -> LDS copies are issued from COMPUTE phases, one after each of the first eight
-// MFMAs: the matrix pipe accepts a new MFMA only every 32 cycles, so the copies ride in issue
+// The global -> LDS copies are issued from COMPUTE phases, one after every second of the first
+// sixteen MFMAs: the matrix pipe accepts a new MFMA only every 16 cycles, so the copies ride in issue
 // slots that are idle anyway, whereas in front of the LDS reads of a memory phase they delay
 // those reads and make the memory phase the longer one (measured: 1.69 vs 1.30 PFLOP/s in a
 // loop of this shape).  The stage of K step t is last read in phase 4t+3 and step t+1 is first
 // read in phase 4t+4, so every wave copies its share of step t+1 during C(t a) (phases 4t+1 and
 // 4t+2) and waits for it before the barrier that ends phase 4t+3.
+// The products are made by v_mfma_f32_16x16x32, not 32x32x16, although both take the pipe the same
+// time per FLOP: under this part's power limit the clock is what counts, and the smaller shape moves
+// half the accumulator registers per FLOP.  Register-only loops with gaussian operands hold 1.99
+// against 1.74 PFLOP/s, with the wave tile's fragments re-read from LDS 1.55-1.61 against 1.49; here,
+// 3376 rows of the 4096 / 11008-wide layer: QKV 318 -> 304 us, O 106 -> 101, gate/up 518 -> 497, down
+// 262 -> 247; 8192 rows 685 -> 663, 242 -> 233, 1197 -> 1154, 627 -> 605.  Same sums in the same order.
 // ------------------------------------------------------------------------------------------
+constexpr int COPY_EVERY = 2;                     // MFMAs per copy in a compute phase that carries copies
+
 template <int WM, int WN, int TM, int TN, int EPI>
 __global__ void __launch_bounds__(512)
 gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
@@ -262,10 +271,10 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                int lda, int ldw, int ldc, int tiles_m, int tiles_n, int group_m, EpiArgs ra) {
   constexpr int NWAVES = 8;
   static_assert(WM * WN == NWAVES, "eight waves: two per SIMD");
-  constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16;
   constexpr int A_INSTR = BM / 8 / NWAVES, W_INSTR = BN / 8 / NWAVES;    // copies per wave and K step
   constexpr int NCOPY = A_INSTR + W_INSTR;
-  static_assert(BM % 64 == 0 && BN % 64 == 0 && NCOPY <= 2 * TM * TN, "tile/wave mismatch");
+  static_assert(BM % 64 == 0 && BN % 64 == 0 && NCOPY * COPY_EVERY <= TM * TN, "tile/wave mismatch");
   constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   // The SiLU*mul form walks its tiles when there are more tiles than compute units: `ra.pp_walkers`
@@ -348,52 +357,49 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
             lds + stage * STAGE_BYTES + BM * ROW_BYTES + (wave * W_INSTR + q - A_INSTR) * 1024);
   };
 
-  uint32_t koff[4];
+  // MFMA operand addresses: row (l & 15) of a 16-row block, chunk 4 * half step + (l >> 4)
+  uint32_t koff[2];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-    koff[ks] = (uint32_t)(((ks * 2 + (lane >> 5)) ^ swz64(lane & 31)) * 16);
-  const uint32_t a_row = (uint32_t)((wm * TM * 32 + (lane & 31)) * ROW_BYTES);
-  const uint32_t w_row = (uint32_t)(BM * ROW_BYTES + (wn * TN * 32 + (lane & 31)) * ROW_BYTES);
+  for (int h = 0; h < 2; ++h)
+    koff[h] = (uint32_t)(((h * 4 + (lane >> 4)) ^ swz64(lane & 15)) * 16);
+  const uint32_t a_row = (uint32_t)((wm * TM * 16 + (lane & 15)) * ROW_BYTES);
+  const uint32_t w_row = (uint32_t)(BM * ROW_BYTES + (wn * TN * 16 + (lane & 15)) * ROW_BYTES);
 
-  floatx16_t acc[TM][TN];
-  bf16x8_t af[2][TM], wf[2][TN];
+  floatx4_t acc[TM][TN];
+  bf16x8_t af[TM], wf[TN];
 
-  // 2*TM*TN MFMAs with one copy behind each of the first NCOPY
+  // TM*TN MFMAs with a copy behind every COPY_EVERY-th of the first NCOPY * COPY_EVERY
 #define LZ_COMPUTE_COPY_PHASE(stage, k0)                                                       \
   do {                                                                                         \
     __builtin_amdgcn_s_setprio(1);                                                             \
-    _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2)                                           \
-      _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j) {                                       \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[k2][j], af[k2][i], acc[i][j], \
-                                                              0, 0, 0);                        \
-          if ((k2 * TM + i) * TN + j < NCOPY) issue_one((stage), (k0), (k2 * TM + i) * TN + j); \
-        }                                                                                      \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                             \
+      _Pragma("unroll") for (int i = 0; i < TM; ++i) {                                         \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], af[i], acc[i][j], 0, 0, 0); \
+        const int n = j * TM + i;                                                              \
+        if ((n + 1) % COPY_EVERY == 0 && n / COPY_EVERY < NCOPY)                               \
+          issue_one((stage), (k0), n / COPY_EVERY);                                            \
+      }                                                                                        \
     _Pragma("unroll") for (int n = 0; n < NCOPY; ++n) {                                        \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
+      __builtin_amdgcn_sched_group_barrier(0x008, COPY_EVERY, 0);                              \
       __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);                                       \
     }                                                                                          \
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * TM * TN - NCOPY, 0);                       \
+    __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - NCOPY * COPY_EVERY, 0);              \
     __builtin_amdgcn_s_setprio(0);                                                             \
   } while (0)
 
 #define LZ_MEM_PHASE(st, h)                                                                    \
   do {                                                                                         \
-    _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2) {                                         \
-      _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-        af[k2][i] = *(const bf16x8_t*)((st) + a_row + i * 32 * ROW_BYTES + koff[2 * (h) + k2]); \
-      _Pragma("unroll") for (int j = 0; j < TN; ++j)                                           \
-        wf[k2][j] = *(const bf16x8_t*)((st) + w_row + j * 32 * ROW_BYTES + koff[2 * (h) + k2]); \
-    }                                                                                          \
+    _Pragma("unroll") for (int i = 0; i < TM; ++i)                                             \
+      af[i] = *(const bf16x8_t*)((st) + a_row + i * 16 * ROW_BYTES + koff[h]);                 \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                             \
+      wf[j] = *(const bf16x8_t*)((st) + w_row + j * 16 * ROW_BYTES + koff[h]);                 \
   } while (0)
 #define LZ_COMPUTE_PHASE()                                                                     \
   do {                                                                                         \
     __builtin_amdgcn_s_setprio(1);                                                             \
-    _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2)                                           \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                             \
       _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j)                                         \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[k2][j], af[k2][i], acc[i][j], \
-                                                              0, 0, 0);                        \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], af[i], acc[i][j], 0, 0, 0); \
     __builtin_amdgcn_s_setprio(0);                                                             \
   } while (0)
   // End of a phase: nothing may be scheduled across it.  The barrier is the bare instruction:
@@ -421,7 +427,7 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   const int KT = K / BK;
   issue(0, 0);
   float rs[TM];
-  load_row_scales<TM>(rs, ra, M, m0, wm, lane);
+  load_row_scales<16, TM>(rs, ra, M, m0, wm, lane);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   int par = 0;                                    // stage that holds step 0 of the current tile
@@ -431,7 +437,7 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
     unsigned ticket = 0;
     if (PERSIST && tk != nullptr && threadIdx.x == 0)
       asm volatile("global_atomic_add %0, %1, %2, off sc0"
@@ -442,7 +448,7 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #pragma unroll
     for (int i = 0; i < TM; ++i) ssq_next[i] = 0;
     if (group == 1) LZ_PHASE_END();               // the second group starts one phase later
-    const bool idle_wave = m0 + wm * TM * 32 >= M;
+    const bool idle_wave = m0 + wm * TM * 16 >= M;
     for (int kt = 0; kt < KT; ++kt) {
       const char* cur = lds + ((kt + par) & 1) * STAGE_BYTES;
       const int st_next = (kt + 1 + par) & 1;
@@ -465,7 +471,7 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
           if (ra.ssq_in != nullptr) {             // (used after the loop: nobody waits for it here)
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-              const int row = m0_next + (wm * TM + i) * 32 + (lane & 31);
+              const int row = m0_next + (wm * TM + i) * 16 + (lane & 15);
               const int rc = row < M ? row : M - 1;
               ssq_next[i] = ra.ssq_in[ra.a_rows != nullptr ? ra.a_rows[rc] : rc];
             }
@@ -509,10 +515,10 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     // so the tile still goes out through LDS in whole rows.
     if (ra.stage_out) {
       static_assert(BM * (BN / 2) * 2 <= STAGE_BYTES, "the SiLU*mul tile must fit one stage");
-      staged_tile_out<TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs,
+      staged_tile_out<16, TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs,
                                                    lds + ((KT - 1 + par) & 1) * STAGE_BYTES);
     } else {
-      gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
+      gemm_epilogue<16, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
     }
     if (!has_next) {
       if (tk != nullptr && threadIdx.x == 0) {
@@ -527,7 +533,7 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     par = (par + KT) & 1;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
-      rs[i] = (ra.ssq_in != nullptr && m0 + (wm * TM + i) * 32 + (lane & 31) < M)
+      rs[i] = (ra.ssq_in != nullptr && m0 + (wm * TM + i) * 16 + (lane & 15) < M)
                   ? rsqrtf((float)ssq_next[i] * ra.ssq_mul + ra.eps) : 0.f;
   }
 #undef LZ_MEM_PHASE
@@ -536,11 +542,11 @@ gemm_pp_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #undef LZ_PHASE_END
 #undef LZ_HAND_TICKET
   if (!ra.stage_out) {
-    gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
+    gemm_epilogue<16, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
     return;
   }
   static_assert(BM * BN * 2 <= 2 * STAGE_BYTES, "staged tile must fit the stages");
-  staged_tile_out<TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs, lds);
+  staged_tile_out<16, TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs, lds);
 }
 
 // Workgroups of a persistent kernel that are resident at once (one per CU when the device is
@@ -565,7 +571,7 @@ template <int WM, int WN, int TM, int TN>
 static hipError_t launch_pp(const void* A, const void* W, void* C, const void* R, int M, int N,
                             int K, int lda, int ldw, int ldc, int epi, int group_m,
                             const EpiArgs& ra, hipStream_t st) {
-  constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16;
   constexpr int LDS_BYTES = 2 * (BM + BN) * ROW_BYTES + 16;      // two stages and the ticket slot
   if (N % BN != 0) return hipErrorInvalidValue;
   if (!pp_operands_fit_32bit(M, N, K, lda, ldw, ra.w_blocked != 0)) return hipErrorInvalidValue;
@@ -608,7 +614,7 @@ static hipError_t launch_pp(const void* A, const void* W, void* C, const void* R
   else if (epi == EPI_SWIGLU) LZ_GEMM(EPI_SWIGLU);
   else if (epi == EPI_QKV_ROPE) {
     if (ra.head_dim == 64) LZ_GEMM(EPI_QKV_ROPE64);
-    else if constexpr (TN >= 4) LZ_GEMM(EPI_QKV_ROPE128);
+    else if constexpr (TN >= 8) LZ_GEMM(EPI_QKV_ROPE128);
     else return hipErrorInvalidValue;
   }
   else return hipErrorInvalidValue;
@@ -654,10 +660,10 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                 float* __restrict__ part, unsigned* __restrict__ flags, EpiArgs ra) {
   constexpr int NWAVES = 8;
   static_assert(WM * WN == NWAVES, "eight waves: two per SIMD");
-  constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16;
   constexpr int A_INSTR = BM / 8 / NWAVES, W_INSTR = BN / 8 / NWAVES;
   constexpr int NCOPY = A_INSTR + W_INSTR;
-  static_assert(BM % 64 == 0 && BN % 64 == 0 && NCOPY <= 2 * TM * TN, "tile/wave mismatch");
+  static_assert(BM % 64 == 0 && BN % 64 == 0 && NCOPY * COPY_EVERY <= TM * TN, "tile/wave mismatch");
   constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
   constexpr int TILE_FLOATS = BM * BN;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -711,19 +717,19 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   // ---- K steps ka .. kb-1 of tile `pid` into acc (the ping-pong schedule of gemm_pp_kernel, stage
   // (kt - ka) & 1; every wave passes the same number of barriers).  On return every wave has read
   // its last fragments; the caller must pass a workgroup barrier before LDS is written again.
-  auto run_range = [&](int pid, int ka, int kb, floatx16_t (&acc)[TM][TN], float (&rs)[TM], int& m0,
+  auto run_range = [&](int pid, int ka, int kb, floatx4_t (&acc)[TM][TN], float (&rs)[TM], int& m0,
                        int& n0) {
     LZ_FRESH_LANE();
     int tile_m, tile_n;
     workgroup_tile(pid, tiles_m, tiles_n, group_m, tile_m, tile_n);
     m0 = tile_m * BM; n0 = tile_n * BN;
     const int crow = lane >> 3;
-    uint32_t koff[4];
+    uint32_t koff[2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      koff[ks] = (uint32_t)(((ks * 2 + (lane >> 5)) ^ swz64(lane & 31)) * 16);
-    const uint32_t a_row = (uint32_t)((wm * TM * 32 + (lane & 31)) * ROW_BYTES);
-    const uint32_t w_row = (uint32_t)(BM * ROW_BYTES + (wn * TN * 32 + (lane & 31)) * ROW_BYTES);
+    for (int h = 0; h < 2; ++h)
+      koff[h] = (uint32_t)(((h * 4 + (lane >> 4)) ^ swz64(lane & 15)) * 16);
+    const uint32_t a_row = (uint32_t)((wm * TM * 16 + (lane & 15)) * ROW_BYTES);
+    const uint32_t w_row = (uint32_t)(BM * ROW_BYTES + (wn * TN * 16 + (lane & 15)) * ROW_BYTES);
     uint32_t a_off[A_INSTR], w_off[W_INSTR];
 #pragma unroll
     for (int q = 0; q < A_INSTR; ++q) {
@@ -757,43 +763,40 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    bf16x8_t af[2][TM], wf[2][TN];
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+    bf16x8_t af[TM], wf[TN];
 
-#define LZ_COMPUTE_COPY_PHASE(stage, ktn)                                                      \
+#define LZ_COMPUTE_COPY_PHASE(stage, ktn)                                                       \
   do {                                                                                         \
     __builtin_amdgcn_s_setprio(1);                                                             \
-    _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2)                                           \
-      _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j) {                                       \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[k2][j], af[k2][i], acc[i][j], \
-                                                              0, 0, 0);                        \
-          if ((k2 * TM + i) * TN + j < NCOPY) issue_one((stage), (ktn), (k2 * TM + i) * TN + j); \
-        }                                                                                      \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                             \
+      _Pragma("unroll") for (int i = 0; i < TM; ++i) {                                         \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], af[i], acc[i][j], 0, 0, 0); \
+        const int n = j * TM + i;                                                              \
+        if ((n + 1) % COPY_EVERY == 0 && n / COPY_EVERY < NCOPY)                               \
+          issue_one((stage), (ktn), n / COPY_EVERY);                                            \
+      }                                                                                        \
     _Pragma("unroll") for (int n = 0; n < NCOPY; ++n) {                                        \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
+      __builtin_amdgcn_sched_group_barrier(0x008, COPY_EVERY, 0);                              \
       __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);                                       \
     }                                                                                          \
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * TM * TN - NCOPY, 0);                       \
+    __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - NCOPY * COPY_EVERY, 0);              \
     __builtin_amdgcn_s_setprio(0);                                                             \
   } while (0)
+
 #define LZ_MEM_PHASE(st, h)                                                                    \
   do {                                                                                         \
-    _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2) {                                         \
-      _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-        af[k2][i] = *(const bf16x8_t*)((st) + a_row + i * 32 * ROW_BYTES + koff[2 * (h) + k2]); \
-      _Pragma("unroll") for (int j = 0; j < TN; ++j)                                           \
-        wf[k2][j] = *(const bf16x8_t*)((st) + w_row + j * 32 * ROW_BYTES + koff[2 * (h) + k2]); \
-    }                                                                                          \
+    _Pragma("unroll") for (int i = 0; i < TM; ++i)                                             \
+      af[i] = *(const bf16x8_t*)((st) + a_row + i * 16 * ROW_BYTES + koff[h]);                 \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                             \
+      wf[j] = *(const bf16x8_t*)((st) + w_row + j * 16 * ROW_BYTES + koff[h]);                 \
   } while (0)
 #define LZ_COMPUTE_PHASE()                                                                     \
   do {                                                                                         \
     __builtin_amdgcn_s_setprio(1);                                                             \
-    _Pragma("unroll") for (int k2 = 0; k2 < 2; ++k2)                                           \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                             \
       _Pragma("unroll") for (int i = 0; i < TM; ++i)                                           \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j)                                         \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[k2][j], af[k2][i], acc[i][j], \
-                                                              0, 0, 0);                        \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], af[i], acc[i][j], 0, 0, 0); \
     __builtin_amdgcn_s_setprio(0);                                                             \
   } while (0)
 #define LZ_PHASE_END()                                                                         \
@@ -805,11 +808,11 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 
 #pragma unroll
     for (int q = 0; q < NCOPY; ++q) issue_one(0, ka, q);
-    load_row_scales<TM>(rs, ra, M, m0, wm, lane);
+    load_row_scales<16, TM>(rs, ra, M, m0, wm, lane);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (group == 1) LZ_PHASE_END();
-    const bool idle_wave = m0 + wm * TM * 32 >= M;
+    const bool idle_wave = m0 + wm * TM * 16 >= M;
     if (idle_wave) {
       // all of this wave's rows are past M (last tile row): it copies its share of the stages and
       // keeps the barriers, but runs no MFMA (a loop of its own, so that the accumulators of the
@@ -851,20 +854,20 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #undef LZ_PHASE_END
   };
 
-  auto finish_tile = [&](floatx16_t (&acc)[TM][TN], const float (&rs)[TM], int m0, int n0) {
+  auto finish_tile = [&](floatx4_t (&acc)[TM][TN], const float (&rs)[TM], int m0, int n0) {
     LZ_FRESH_LANE();
     if (EPI == EPI_SWIGLU || !ra.stage_out) {
-      gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
+      gemm_epilogue<16, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
     } else {
       static_assert(BM * ((EPI == EPI_SWIGLU) ? BN / 2 : BN) * 2 <= 2 * STAGE_BYTES, "staged tile must fit the stages");
-      staged_tile_out<TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs, lds);
+      staged_tile_out<16, TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs, lds);
     }
     __syncthreads();                                // the next item refills stage 0
   };
 
   // ---- 1. whole tiles
   for (int r = 0; r < full; ++r) {
-    floatx16_t acc[TM][TN];
+    floatx4_t acc[TM][TN];
     float rs[TM];
     int m0, n0;
     run_range(r * G + g, 0, KT, acc, rs, m0, n0);
@@ -873,7 +876,7 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 
   // ---- 2. the piece of somebody else's tile: partial sums to slot g, then the flag
   if (oth_tile >= 0) {
-    floatx16_t acc[TM][TN];
+    floatx4_t acc[TM][TN];
     float rs[TM];
     int m0, n0;
     run_range(sk_pid(oth_tile), oth_ka, oth_kb, acc, rs, m0, n0);
@@ -883,13 +886,9 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4)
-            dst[((wave * (TM * TN) + i * TN + j) * 4 + q4) * 64 + lane] =
-                make_float4(acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2],
-                            acc[i][j][4 * q4 + 3]);
-        }
+        for (int j = 0; j < TN; ++j)
+          dst[(wave * (TM * TN) + i * TN + j) * 64 + lane] =
+              make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
       // Every wave's stores have reached the L2 (vmcnt), then the flag goes up.  The reader sits
       // on the same XCD, behind the same L2, so there is nothing to write back or to invalidate
       // (a release fence writes the whole L2 back and an acquire fence empties it for everybody
@@ -904,7 +903,7 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 
   // ---- 3. the end of the tile this workgroup owns, plus the pieces the others left
   if (own_tile >= 0) {
-    floatx16_t acc[TM][TN];
+    floatx4_t acc[TM][TN];
     float rs[TM];
     int m0, n0;
     run_range(sk_pid(own_tile), own_ka, KT, acc, rs, m0, n0);
@@ -933,33 +932,19 @@ gemm_psk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
         for (int ip = i_first; ip < gi; ++ip) {               // ascending K order
           if (ubegin(ip + 1) <= ubegin(ip)) continue;
           const float4* src = (const float4*)(part + (size_t)(xcd + 8 * ip) * TILE_FLOATS);
-          // four blocks (64 registers, free now that the operand fragments are dead) per round trip
-          constexpr int NB = TM * TN, BATCH = 4;
-          static_assert(NB % 2 == 0, "blocks are fetched in batches");
+          // sixteen blocks (64 registers, free now that the operand fragments are dead) per round trip
+          constexpr int NB = TM * TN, BATCH = NB % 16 == 0 ? 16 : 12;
+          static_assert(NB % BATCH == 0, "blocks are fetched in batches");
 #pragma unroll
           for (int b0 = 0; b0 < NB; b0 += BATCH) {
-            floatx4_t v[BATCH][4];
-            {
+            floatx4_t v[BATCH];
 #pragma unroll
-              for (int u = 0; u < BATCH; ++u)
-                if (b0 + u < NB) {
-#pragma unroll
-                  for (int q4 = 0; q4 < 4; ++q4) {
-                    const float4 t = src[((wave * NB + b0 + u) * 4 + q4) * 64 + lane];
-                    v[u][q4] = floatx4_t{t.x, t.y, t.z, t.w};
-                  }
-                }
+            for (int u = 0; u < BATCH; ++u) {
+              const float4 t = src[(wave * NB + b0 + u) * 64 + lane];
+              v[u] = floatx4_t{t.x, t.y, t.z, t.w};
             }
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u)
-              if (b0 + u < NB) {
-                const int i = (b0 + u) / TN, j = (b0 + u) % TN;
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                  acc[i][j][4 * q4] += v[u][q4][0]; acc[i][j][4 * q4 + 1] += v[u][q4][1];
-                  acc[i][j][4 * q4 + 2] += v[u][q4][2]; acc[i][j][4 * q4 + 3] += v[u][q4][3];
-                }
-              }
+            for (int u = 0; u < BATCH; ++u) acc[(b0 + u) / TN][(b0 + u) % TN] += v[u];
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -991,7 +976,7 @@ template <int WM, int WN, int TM, int TN>
 static hipError_t launch_psk(const void* A, const void* W, void* C, const void* R, int M, int N,
                              int K, int lda, int ldw, int ldc, int epi, int group_m,
                              const EpiArgs& ra, void* ws, hipStream_t st) {
-  constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16;
   constexpr int LDS_BYTES = 2 * (BM + BN) * ROW_BYTES;
   if (N % BN != 0 || ws == nullptr) return hipErrorInvalidValue;
   // the kernel addresses both operands with 32-bit byte offsets
@@ -1032,7 +1017,7 @@ static hipError_t launch_psk(const void* A, const void* W, void* C, const void* 
   else if (epi == EPI_SWIGLU) LZ_GEMM(EPI_SWIGLU);
   else if (epi == EPI_QKV_ROPE) {
     if (ra.head_dim == 64) LZ_GEMM(EPI_QKV_ROPE64);
-    else if constexpr (TN >= 4) LZ_GEMM(EPI_QKV_ROPE128);
+    else if constexpr (TN >= 8) LZ_GEMM(EPI_QKV_ROPE128);
     else return hipErrorInvalidValue;
   }
   else return hipErrorInvalidValue;
@@ -1170,7 +1155,7 @@ gemm_sk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #undef LZ_LOAD_FRAGS
 #undef LZ_MFMAS
     if (ka == 0 && kb == KT) {
-      gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
+      gemm_epilogue<32, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
     } else {
       // fp32 partial sums of this piece, tile-local row-major [128][128]
       float* dst = partial + ((size_t)g * 2 + (tile == first_tile ? 0 : 1)) * SK_TILE_ELEMS;
@@ -1530,15 +1515,15 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
             rw.walk_tickets = (sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes() && ra.psk_ready)
                                   ? (unsigned*)((char*)sk_ws + SK_PART_BYTES + SK_TICKET_BYTES) + WALK_TICKET_WORD
                                   : nullptr;
-            return cfg == 5 ? launch_pp<4, 2, 2, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, rw, st)
-                            : launch_pp<2, 4, 3, 2>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, rw, st);
+            return cfg == 5 ? launch_pp<4, 2, 4, 8>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, rw, st)
+                            : launch_pp<2, 4, 6, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, rw, st);
     }
     case 9:                                             // 256x256 ping-pong, persistent stream-K
             if (sk_ws == nullptr || sk_ws_bytes < gemm_workspace_bytes() || !ra.psk_ready) return hipErrorInvalidValue;
-            return launch_psk<4, 2, 2, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, sk_ws, st);
+            return launch_psk<4, 2, 4, 8>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, sk_ws, st);
     case 10:                                            // 192x256 ping-pong, persistent stream-K
             if (sk_ws == nullptr || sk_ws_bytes < gemm_workspace_bytes() || !ra.psk_ready) return hipErrorInvalidValue;
-            return launch_psk<2, 4, 3, 2>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, sk_ws, st);
+            return launch_psk<2, 4, 6, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, sk_ws, st);
     case 6:                                             // 128x128 stream-K + fix-up
             if (sk_ws == nullptr || sk_ws_bytes < gemm_workspace_bytes()) return hipErrorInvalidValue;
             if (ra.a_rows != nullptr) return hipErrorInvalidValue;   // (no row indirection on its A operand)

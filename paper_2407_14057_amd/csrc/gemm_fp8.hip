@@ -295,10 +295,10 @@ gemm_f8_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ W,
   }
 
   if (EPI == EPI_SWIGLU || !ra.stage_out) {
-    gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
+    gemm_epilogue<32, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
     return;
   }
-  staged_tile_out<TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, nullptr, lds);
+  staged_tile_out<32, TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, nullptr, lds);
 }
 
 hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const float* sw, void* C,

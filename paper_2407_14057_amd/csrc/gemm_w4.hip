@@ -118,7 +118,7 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     for (int q = 0; q < NCOPY; ++q) issue_one(1, 1, q);
   }
   float rs[TM];
-  load_row_scales<TM>(rs, ra, M, m0, wm, lane);
+  load_row_scales<32, TM>(rs, ra, M, m0, wm, lane);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   LZ_LOAD_FRAGS(0, lds, 0);
@@ -168,10 +168,10 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   // staged output below reuses the stages, so they are drained first)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (EPI == EPI_SWIGLU || !ra.stage_out) {
-    gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
+    gemm_epilogue<32, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
     return;
   }
-  staged_tile_out<TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs, lds);
+  staged_tile_out<32, TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, rs, lds);
 }
 
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
