@@ -202,10 +202,12 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
                        int lda, int ldw, int ldc, int epilogue, hipStream_t st,
                        const EpiArgs* rope = nullptr, void* sk_ws = nullptr, size_t sk_ws_bytes = 0);
 
-// The 256x256 tile on four waves of 128x128, one per SIMD (gemm_w4.hip); N % 256 == 0.
+// The 256x256 tile on four waves of 128x128, one per SIMD (gemm_w4.hip); N % 256 == 0.  stream_k: with
+// the K steps of the last round's tiles shared out (part, flags: see there).
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra,
-                          hipStream_t st);
+                          int stream_k, float* part, unsigned* flags, hipStream_t st);
+int gemm_aligned_grid(int G, int tiles);
 // The weight-streaming kernel for few rows (gemm_stream.hip).  part: fp32 partial sums of K splits;
 // tickets: zero before the first launch, zero again after each.  takes(): whether its rule takes the
 // shape, and on which tile (row blocks, column waves, K groups, K splits).

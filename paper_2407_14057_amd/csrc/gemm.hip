@@ -968,7 +968,7 @@ static bool psk_pieces_align(int G, int tiles) {
   const int per_xcd = tiles / 8, S = (G / 8) / per_xcd;
   return S >= 2 && S * per_xcd * 4 >= (G / 8) * 3;
 }
-static int psk_aligned_grid(int G, int tiles) {
+int gemm_aligned_grid(int G, int tiles) {
   return psk_pieces_align(G, tiles) ? 8 * ((G / 8) / (tiles / 8)) * (tiles / 8) : G;
 }
 
@@ -1005,7 +1005,7 @@ static hipError_t launch_psk(const void* A, const void* W, void* C, const void* 
     }                                                                                            \
     int G = resident < 256 ? resident : 256;                                                     \
     G &= ~7;                                         /* whole rounds over the 8 XCDs */          \
-    G = psk_aligned_grid(G, tiles_m * tiles_n);                                                  \
+    G = gemm_aligned_grid(G, tiles_m * tiles_n);                                                  \
     if (G < 8 || (size_t)G * BM * BN * sizeof(float) > SK_PART_BYTES || G > PSK_FLAG_WORDS_MAX)  \
       return hipErrorInvalidConfiguration;                                                       \
     hipLaunchKernelGGL(kern, dim3(G + side), dim3(512), LDS_BYTES, st, (const uint16_t*)A,       \
@@ -1391,7 +1391,7 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
               : epilogue == EPI_SWIGLU ? (tm256 < 8 ? 1 : tm256 > 40 ? 2 : tall) : 4;
   }
   if (cfg == 0) {
-    // 256x256 tiles on 8 waves in ping-pong phases have the best reuse and keep the matrix pipe
+    // 256x256 tiles on four waves (gemm_w4.hip) have the best reuse and keep the matrix pipe
     // fed; when they would leave much of the 256 CUs idle, smaller tiles on 4 waves win.  The
     // rotary epilogue needs a wave to span a whole head (128 columns for head_dim 128).
     // (operands of 4 GB and more: only the 4-wave kernels, which address with 64-bit offsets)
@@ -1405,7 +1405,7 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
     // more tiles the 128x128 partial-sum traffic eats the gain (M = 1182: +-5 %).
     // Fewer 256x256 tiles than CUs, but a whole number (>= 2) of workgroups per tile on every XCD:
     // the persistent stream-K schedule then gives each workgroup one piece of one tile (see
-    // psk_aligned_grid).  Measured, cold weights, against the best other form: down projection at
+    // gemm_aligned_grid).  Measured, cold weights, against the best other form: down projection at
     // 600 / 844 / 1182 / 1400 rows 106 -> 87, 107 -> 100, 153 -> 124, 166 -> 138 us; O projection at
     // 1182 / 1400 rows 68.5 -> 63, 68.7 -> 66.6 (but 50 -> 56 at 600 rows, and at 355 rows the 128x128
     // stream-K form below stays ahead: 62 against 79 us).
@@ -1498,6 +1498,10 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
   }
   if (ra.w_packed && cfg != 8) return hipErrorInvalidValue;
   if (ra.w_blocked && cfg == 8 && ra.w_stream == nullptr) return hipErrorInvalidValue;
+  // (the 256x256 tile stores 16 bytes at a time: other outputs go to the 128x128 tile)
+  if ((cfg == 5 || cfg == 9 || cfg == 14) && epilogue != EPI_QKV_ROPE && N % 256 == 0 &&
+      (ldc % 8 != 0 || ((uintptr_t)C & 15) != 0 || ((uintptr_t)R & 15) != 0))
+    cfg = 2;
   switch (cfg) {
     case 2:                                             // 128x128, 4 waves of 64x64
             return launch_cfg<2, 2, 2, 2>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, st);
@@ -1505,22 +1509,22 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
             return launch_cfg<4, 1, 1, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, st);
     case 13: if (N % 256) return hipErrorInvalidValue;  // 128x256, 8 waves of 32x128 (whole heads), three stages
             return launch_cfg<4, 2, 1, 4, 3>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, st);
-    case 14: if (N % 256) return hipErrorInvalidValue;  // 256x256, 4 waves of 128x128 (one per SIMD)
-            return launch_gemm_w4(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, st);
     case 4: if (N % 256) return hipErrorInvalidValue;   // 128x256, 4 waves of 64x128
             return launch_cfg<2, 2, 2, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, st);
-    case 5:                                             // 256x256, 8 waves of 64x128, ping-pong
+    case 5:                                             // 256x256, 4 waves of 128x128
+    case 14:
+            return launch_gemm_w4(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, 0, nullptr, nullptr, st);
     case 7: {                                           // 192x256, 8 waves of 96x64, ping-pong
             EpiArgs rw = ra;                            // (the tile walk's counters live among the flags)
             rw.walk_tickets = (sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes() && ra.psk_ready)
                                   ? (unsigned*)((char*)sk_ws + SK_PART_BYTES + SK_TICKET_BYTES) + WALK_TICKET_WORD
                                   : nullptr;
-            return cfg == 5 ? launch_pp<4, 2, 4, 8>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, rw, st)
-                            : launch_pp<2, 4, 6, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, rw, st);
+            return launch_pp<2, 4, 6, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, rw, st);
     }
-    case 9:                                             // 256x256 ping-pong, persistent stream-K
+    case 9:                                             // 256x256, 4 waves of 128x128, stream-K
             if (sk_ws == nullptr || sk_ws_bytes < gemm_workspace_bytes() || !ra.psk_ready) return hipErrorInvalidValue;
-            return launch_psk<4, 2, 4, 8>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, sk_ws, st);
+            return launch_gemm_w4(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, 1, (float*)sk_ws,
+                                  (unsigned*)((char*)sk_ws + SK_PART_BYTES + SK_TICKET_BYTES), st);
     case 10:                                            // 192x256 ping-pong, persistent stream-K
             if (sk_ws == nullptr || sk_ws_bytes < gemm_workspace_bytes() || !ra.psk_ready) return hipErrorInvalidValue;
             return launch_psk<2, 4, 6, 4>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, sk_ws, st);

@@ -140,6 +140,45 @@ def test_gemm_swiglu_walks_several_tiles_per_workgroup(cfg, M, N, K):
     assert int(ws[-4096:].view(torch.int32).abs().sum()) == 0
 
 
+@pytest.mark.parametrize("M,N,K", [(2111, 7680, 64), (2111, 7680, 192), (2200, 7680, 128), (300, 256, 320), (48, 768, 704)])
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
+def test_gemm_four_wave_tile_runs_through_its_pieces(M, N, K, epi):
+    """The 256x256 tile on four waves of 128x128 (forced): up to 270 tiles on 256 persistent workgroups,
+    whose copies of the next tile's first steps ride in the last steps of this one; K of one, two, three
+    and more steps (the ring of five slots wraps inside a tile and across tiles); last tile rows with
+    idle waves and with ragged blocks.  Data-parallel: the bits of the 128x128 tile, whose sums run in
+    the same order.  Under the stream-K schedule the pieces of a cut tile are added: every element
+    against the definition, the same bits twice, the flags back at zero."""
+    rng = np.random.default_rng(M + 3 * N + K + epi)
+    A = _rand_bf16(rng, (M, K)); W = _rand_bf16(rng, (N, K), 1.0 / math.sqrt(K)); R = _rand_bf16(rng, (M, N))
+    ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
+    ncols = N // 2 if epi == B.EPI_SWIGLU else N
+
+    def run(cfg):
+        guard = torch.full((M + 1, ncols), 7.0, dtype=torch.bfloat16, device=DEV)
+        Cout = guard[:M]
+        if epi == B.EPI_RESIDUAL:
+            Cout.copy_(R)
+        B.lazyllm_op_gemm(A, W, Cout, Cout if epi == B.EPI_RESIDUAL else None, M, N, K, K, K, ncols,
+                          epi | (cfg << 8), workspace=ws)
+        torch.cuda.synchronize()
+        assert int(ws[-4096:].view(torch.int32).abs().sum()) == 0
+        assert bool((guard[M:] == 7.0).all())               # nothing past the last row
+        return Cout
+
+    small, whole, cut, again = run(2), run(5), run(9), run(9)
+    assert torch.equal(small, whole)
+    assert torch.equal(cut, again)
+    acc = _f64(A) @ _f64(W).T
+    if epi == B.EPI_SWIGLU:
+        blocks = acc.reshape(M, N // 64, 2, 32)
+        ref = (O.silu(blocks[:, :, 0, :]) * blocks[:, :, 1, :]).reshape(M, N // 2)
+    else:
+        ref = acc + (_f64(R) if epi == B.EPI_RESIDUAL else 0.0)
+    _assert_bf16_close(_f64(whole), ref, 1.0, "four-wave tile")
+    _assert_bf16_close(_f64(cut), ref, 1.0, "four-wave tile, stream-K")
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 256, 64), (229, 768, 256), (700, 1536, 704), (355, 512, 128), (130, 256, 1408)])
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 def test_gemm_tile_of_32_row_waves(M, N, K, epi):
