@@ -172,10 +172,6 @@ struct EpiArgs {
   // workspace) zeroed likewise: launches whose tile count leaves the last round of the chip partly
   // idle may take that kernel
   int psk_ready;
-  // filled in by the launcher: workgroups that walk the tiles of the ping-pong kernel's SiLU*mul
-  // form, and their ticket counters (inside the flag area above; null: one workgroup per tile)
-  int pp_walkers;
-  unsigned* walk_tickets;
   // the W argument is in the weight-streaming kernel's own layout (launch_pack_stream); only that
   // kernel can read it, so the launch fails where another kernel would be chosen
   int w_packed;
@@ -206,7 +202,7 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
 // the K steps of the last round's tiles shared out (part, flags: see there).
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra,
-                          int stream_k, float* part, unsigned* flags, hipStream_t st);
+                          int stream_k, float* part, unsigned* flags, int rows, hipStream_t st);
 int gemm_aligned_grid(int G, int tiles);
 // The weight-streaming kernel for few rows (gemm_stream.hip).  part: fp32 partial sums of K splits;
 // tickets: zero before the first launch, zero again after each.  takes(): whether its rule takes the

@@ -119,7 +119,9 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   constexpr int NCA = BM / 32, NCW = BN / 32;      // copies per wave of an A / W slab
   constexpr int SLOT = W4_SLOT;
   constexpr int TILE_FLOATS = BM * BN;
+  constexpr int RE = TM == 4 ? 2 : 3;              // MFMAs per fragment read
   static_assert(BM <= 256 && BN == 256, "a slab must fit a slot");
+  static_assert((TM + TN) * RE <= TM * TN + RE - 1 && NCA * 1024 >= 16 * TN * 16 * 2, "reads fit a half step, 16 rows a wave's part of a slab");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   if ((int)blockIdx.x >= G) {                      // side job (see EpiArgs): Eq. 1 scores
     const int sb = (int)blockIdx.x - G;
@@ -219,14 +221,14 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     else if ((n) <= TM) af[buf][(n)-1] = *(const bf16x8_t*)(lds + (sa) + aoff[h] + ((n)-1) * 16 * ROW_BYTES); \
     else wf[buf][(n)-TM] = *(const bf16x8_t*)(lds + (sw) + woff[h] + ((n)-TM) * 16 * ROW_BYTES); \
   } while (0)
-  // TM * TN MFMAs on fragments `buf` (ZERO: from a zero accumulator); behind every third a fragment read
-  // of the next half step (buffer `nb`) until they are through, and the nc copies evenly.  The order is
+  // TM * TN MFMAs on fragments `buf` (ZERO: from a zero accumulator); behind every RE-th a fragment
+  // read of the next half step (buffer `nb`) until they are through, and the nc copies evenly.  The order is
   // the program's: nothing is scheduled across a slot.  RUN = false: reads and copies only.
 #define LZ_HALF(ZERO, RUN, buf, nb, sa, sw, h, copy, nc, slot)                                 \
   unrolled<TM * TN>([&](auto nn) {                                                             \
     constexpr int n = decltype(nn)::value, j = n / TM, i = (j & 1) ? TM - 1 - n % TM : n % TM; \
     if constexpr (RUN) acc_mfma<4 * (i * TN + j), ZERO>(wf[buf][j], af[buf][i]);               \
-    if constexpr (n % 3 == 0 && n / 3 < TM + TN) LZ_READ(nb, sa, sw, h, n / 3);                \
+    if constexpr (n % RE == 0 && n / RE < TM + TN) LZ_READ(nb, sa, sw, h, n / RE);             \
     constexpr int CE = TM * TN / (nc);                                                         \
     if constexpr (n % CE == CE / 2 && n / CE < (nc)) copy(slot, n / CE);                       \
     __builtin_amdgcn_sched_barrier(0);                                                         \
@@ -654,8 +656,11 @@ static hipError_t launch_w4(const void* A, const void* W, void* C, const void* R
 
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra, int stream_k,
-                          float* part, unsigned* flags, hipStream_t st) {
-  return launch_w4<8>(A, W, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st);
+                          float* part, unsigned* flags, int rows, hipStream_t st) {
+  if (rows == 256) return launch_w4<8>(A, W, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st);
+  if (rows == 192) return launch_w4<6>(A, W, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st);
+  if (rows == 128) return launch_w4<4>(A, W, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace lz
