@@ -589,8 +589,9 @@ int lazyllm_prefill_varlen(const lazyllm_model* m, const int32_t* token_ids,
       if (qe != hipSuccess) return qe;
       EpiArgs e8 = *ea;
       e8.w_blocked = 1;                              // the model's codes are K-step-major too
+      e8.psk_ready = 1;
       return launch_gemm_f8(W + ws.a8, (const float*)(W + ws.sa8), w8, sw8, Cout, R, n, N, K, K, K, ldc,
-                            epi, st, &e8);
+                            epi, st, &e8, W + ws.gemm_ws, gemm_workspace_bytes());
     };
     const bool f8 = c->gemm_dtype == 1;
     if (flags & LAZYLLM_KEEP_HIDDEN) {

@@ -194,6 +194,7 @@ void set_last_hip_error(int e);
 
 // sk_ws: optional scratch of gemm_workspace_bytes() for the stream-K variant (fp32 partial tiles).
 size_t gemm_workspace_bytes();
+unsigned* gemm_exchange_flags(void* sk_ws);          // flags of the stream-K schedule of gemm_w4.hip
 hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                        int lda, int ldw, int ldc, int epilogue, hipStream_t st,
                        const EpiArgs* rope = nullptr, void* sk_ws = nullptr, size_t sk_ws_bytes = 0);
@@ -203,7 +204,16 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra,
                           int stream_k, float* part, unsigned* flags, int rows, hipStream_t st);
+hipError_t launch_gemm_w4_f8(const void* A, const float* sa, const void* W, const float* sw, void* C, const void* R,
+                             int M, int N, int K, int lda, int ldw, int ldc, int epi, int group_m,
+                             const EpiArgs& ra, int stream_k, float* part, unsigned* flags, int rows, hipStream_t st);
 int gemm_aligned_grid(int G, int tiles);
+// What a form of that kernel costs, in microseconds: a launch, a K step of a full / part-full round of tiles, the
+// end of a tile (residual or none, rotary, SiLU * mul), and under the stream-K schedule the exchange, every
+// piece that is added, and pieces that do not align with tiles.  See choose_tile in gemm.hip.
+struct TileCost { double launch, step_full, step_low, end[3], exchange, per_piece, ragged; };
+double gemm_w4_cost(const TileCost& c, int rows, bool stream_k, int M, int N, int KT, int epi);
+int gemm_band_height(int M, int epilogue);           // tile rows that share a run of W column blocks
 // The weight-streaming kernel for few rows (gemm_stream.hip).  part: fp32 partial sums of K splits;
 // tickets: zero before the first launch, zero again after each.  takes(): whether its rule takes the
 // shape, and on which tile (row blocks, column waves, K groups, K splits).
@@ -225,7 +235,7 @@ hipError_t launch_quantize_rows_f8(const void* x, int rows, int K, int ldx, void
                                    float* scale, hipStream_t st);
 hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const float* sw, void* C,
                           const void* R, int M, int N, int K, int lda, int ldw, int ldc, int epilogue,
-                          hipStream_t st, const EpiArgs* ea = nullptr);
+                          hipStream_t st, const EpiArgs* ea = nullptr, void* sk_ws = nullptr, size_t sk_ws_bytes = 0);
 
 hipError_t launch_rope_table(float2* table, int n_pos, int head_dim, float theta, hipStream_t st);
 

@@ -558,6 +558,8 @@ hipError_t launch_pack_kblock(const void* W, int N, int K, int ldw, void* Wb, hi
   return hipGetLastError();
 }
 
+unsigned* gemm_exchange_flags(void* sk_ws) { return (unsigned*)((char*)sk_ws + SK_PART_BYTES + SK_TICKET_BYTES); }
+
 void* gemm_counter_region(void* sk_ws, size_t* bytes) {
   *bytes = SK_TICKET_BYTES + PSK_FLAG_BYTES;
   return (char*)sk_ws + SK_PART_BYTES;
@@ -579,6 +581,22 @@ hipError_t launch_gemm_exchange_check(const void* sk_ws, int32_t* status, hipStr
   return hipGetLastError();
 }
 
+int gemm_band_height(int M, int epilogue) {
+  // Band height of the tile walk (tile rows that share a run of W column blocks in an XCD's L2).
+  // Measured with cold K-step-major weights, 256x256 tiles of the four-wave kernel, us by band height:
+  //   gate/up (86 column blocks)  1182 rows: 1: 194, 2: 190, 5: 184;  2364 rows: 1: 371, 5: 349, 10: 355
+  //                               3376 rows: 2: 486, 4..6: 479, 7: 472, 14: 482
+  //                               4916 rows: 2: 671, 4: 653, 5: 654, 16: 669;  8192 rows: 2: 1076, 3: 1068,
+  //                               4: 1049, 5: 1055, 8: 1048, 32: 1114
+  //   QKV (48 column blocks)      1182 rows: 1: 116, 5: 107;  3376 rows: 1: 301, 3..6: 289-292, 14: 301
+  //                               4916 rows: 3: 401, 5: 402, 16: 420;  8192 rows: 2: 652, 4: 630, 5: 636, 32: 715
+  //   O and down projections: within 1 % from 3 to 8 (4 kept).
+  // So: column by column below 8 tile rows, about half the tile rows up to 16 of them, 4 beyond.
+  const int tm256 = (M + 255) / 256;
+  const int tall = tm256 <= 11 ? 5 : tm256 <= 16 ? 7 : 4;
+  return epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU ? (tm256 < 8 ? tm256 : tall) : 4;
+}
+
 // ---- which tile.  Every form's time is estimated, in microseconds, from what its tiles cost (measured at
 // 640 - 8192 rows of eleven projections with K of 768 to 14336 and N of 768 to 28672, cold weights) and
 // the smallest estimate is taken.  Against the best form of each of those 380 cases the choice costs
@@ -590,15 +608,12 @@ hipError_t launch_gemm_exchange_check(const void* sk_ws, int32_t* status, hipStr
 //   * stream-K: the whole rounds, then the remaining tiles' steps shared out evenly; the exchange costs a
 //     fixed part, a part for every piece the owner of a tile adds, and more when the pieces do not
 //     align with tiles (a workgroup then has two pieces), the fewer tiles the more.
-struct TileCost { double launch, step_full, step_low, end[3], exchange, per_piece, ragged; };
 static const TileCost W4_COST[3] = {                // 256, 192, 128 rows; end: residual or none, rotary, SiLU * mul
     {5.75, 1.37, 1.02, {13.1, 19.4, 4.8}, 10.9, 2.6, 15.9},
     {4.5, 1.11, 0.94, {5.9, 14.8, 6.1}, 12.4, 2.0, 24.2},
     {7.2, 0.94, 0.91, {1.5, 5.0, 9.2}, 9.7, 1.5, 7.4}};
 
-static double w4_cost(int form, bool stream_k, int M, int N, int K, int epi) {
-  const TileCost& c = W4_COST[form];
-  const int rows = 256 - 64 * form, KT = K / BK;
+double gemm_w4_cost(const TileCost& c, int rows, bool stream_k, int M, int N, int KT, int epi) {
   const long T = (long)((M + rows - 1) / rows) * (N / 256);
   const double end = c.end[epi == EPI_QKV_ROPE ? 1 : epi == EPI_SWIGLU ? 2 : 0];
   if (!stream_k) {
@@ -639,9 +654,9 @@ static int choose_tile(int M, int N, int K, int epi, int head_dim, bool w4_ok, b
     consider(6, 21.0 + 1.41 * (double)t128 * KT / 512.0);
   if (w4_ok) {
     static const int whole[3] = {5, 7, 15}, cut[3] = {9, 10, 16};
-    for (int f = 0; f < 3; ++f) consider(whole[f], w4_cost(f, false, M, N, K, epi));
+    for (int f = 0; f < 3; ++f) consider(whole[f], gemm_w4_cost(W4_COST[f], 256 - 64 * f, false, M, N, KT, epi));
     if (stream_k_ok)
-      for (int f = 0; f < 3; ++f) consider(cut[f], w4_cost(f, true, M, N, K, epi));
+      for (int f = 0; f < 3; ++f) consider(cut[f], gemm_w4_cost(W4_COST[f], 256 - 64 * f, true, M, N, KT, epi));
   }
   return cfg;
 }
@@ -666,22 +681,7 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
         N != rope->d_model + 2 * kvd || rope->d_model % 128 != 0 || kvd % 128 != 0)
       return hipErrorInvalidValue;
   }
-  if (group_m == 0) {
-    // Band height of the tile walk (tile rows that share a run of W column blocks in an XCD's L2).
-    // Measured with cold K-step-major weights, 256x256 tiles of the four-wave kernel, us by band height:
-    //   gate/up (86 column blocks)  1182 rows: 1: 194, 2: 190, 5: 184;  2364 rows: 1: 371, 5: 349, 10: 355
-    //                               3376 rows: 2: 486, 4..6: 479, 7: 472, 14: 482
-    //                               4916 rows: 2: 671, 4: 653, 5: 654, 16: 669;  8192 rows: 2: 1076, 3: 1068,
-    //                               4: 1049, 5: 1055, 8: 1048, 32: 1114
-    //   QKV (48 column blocks)      1182 rows: 1: 116, 5: 107;  3376 rows: 1: 301, 3..6: 289-292, 14: 301
-    //                               4916 rows: 3: 401, 5: 402, 16: 420;  8192 rows: 2: 652, 4: 630, 5: 636, 32: 715
-    //   O and down projections: within 1 % from 3 to 8 (4 kept).
-    // So: column by column below 8 tile rows, about half the tile rows up to 16 of them, 4 beyond.
-    const int tm256 = (M + 255) / 256;
-    const int tall = tm256 <= 11 ? 5 : tm256 <= 16 ? 7 : 4;
-    group_m = epilogue == EPI_QKV_ROPE ? (tm256 < 8 ? tm256 : tall)
-              : epilogue == EPI_SWIGLU ? (tm256 < 8 ? tm256 : tall) : 4;
-  }
+  if (group_m == 0) group_m = gemm_band_height(M, epilogue);
   const bool ws_ok = sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes();
   // (the four-wave kernel: operands below 4 GB, outputs that 16-byte stores can address)
   const bool w4_ok = N % 256 == 0 && operands_fit_32bit(M, N, K, lda, ldw, ra.w_blocked != 0) &&
@@ -727,8 +727,7 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
     case 9: case 10: case 16:                           // the same three, stream-K
             if (sk_ws == nullptr || sk_ws_bytes < gemm_workspace_bytes() || !ra.psk_ready) return hipErrorInvalidValue;
             return launch_gemm_w4(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, 1, (float*)sk_ws,
-                                  (unsigned*)((char*)sk_ws + SK_PART_BYTES + SK_TICKET_BYTES),
-                                  cfg == 10 ? 192 : cfg == 16 ? 128 : 256, st);
+                                  gemm_exchange_flags(sk_ws), cfg == 10 ? 192 : cfg == 16 ? 128 : 256, st);
     case 6:                                             // 128x128 stream-K + fix-up
             if (sk_ws == nullptr || sk_ws_bytes < gemm_workspace_bytes()) return hipErrorInvalidValue;
             if (ra.a_rows != nullptr) return hipErrorInvalidValue;   // (no row indirection on its A operand)

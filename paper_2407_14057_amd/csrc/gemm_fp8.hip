@@ -75,30 +75,29 @@ hipError_t launch_quantize_rows_f8(const void* x, int rows, int K, int ldx, void
 }
 
 // ------------------------------------------------------------------------------------------
-// Tile kernel: 256 x 256 tile on 8 waves (4 x 2 waves of 64 x 128; TM = 1: 128 x 256 tile, waves
-// of 32 x 128, for launches that would not fill the chip otherwise), 128 K elements (= 128 bytes
-// per operand row, the same LDS geometry as the 16-bit kernels) per step, two LDS stages filled
-// by global -> LDS copies.  Same ping-pong schedule as the 16-bit kernel: the two waves of a SIMD
-// run half a step apart, one in a phase of 8 back-to-back MFMAs (64 cycles each) with the copies
-// of the next step riding behind them, the other reading its next fragments from LDS; a bare
+// Tile kernel for launches of few tiles (larger ones take the four-wave kernel of gemm_w4.hip): 128 x
+// 256 tile on 8 waves of 32 x 128, 128 K elements (= 128 bytes per operand row, the same LDS geometry as
+// the 16-bit kernels) per step, three LDS stages filled by global -> LDS copies.  The two waves of a
+// SIMD run half a step apart, one in a phase of 4 back-to-back MFMAs (64 cycles each) with the copies
+// of a later step riding behind them, the other reading its next fragments from LDS; a bare
 // barrier ends every phase.  A lane's fragment of one MFMA is 32 consecutive bytes of its row
 // (two 16-byte LDS reads); both operands use the same lane -> k assignment, which is all the
 // contraction needs.
 // ------------------------------------------------------------------------------------------
 constexpr int F8_BK = 128;                          // K elements (bytes) per step
 
-template <int EPI, int TM>
+template <int EPI>
 __global__ void __launch_bounds__(512)
 gemm_f8_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ W,
                const float* __restrict__ sa, const float* __restrict__ sw,
                uint16_t* __restrict__ C, const uint16_t* __restrict__ R, int M, int N, int K,
                int lda, int ldw, int ldc, int tiles_m, int tiles_n, int group_m, EpiArgs ra) {
-  constexpr int NWAVES = 8, WM = 4, WN = 2, TN = 4;
+  constexpr int NWAVES = 8, WM = 4, WN = 2, TM = 1, TN = 4;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
   constexpr int A_INSTR = BM / 8 / NWAVES, W_INSTR = BN / 8 / NWAVES;    // copies per wave and K step
   constexpr int NCOPY = A_INSTR + W_INSTR;
   constexpr int CPM = (NCOPY + TM * TN - 1) / (TM * TN);                 // copies behind one MFMA
-  static_assert((TM == 1 || TM == 2) && NCOPY % CPM == 0 && NCOPY / CPM <= TM * TN, "128- or 256-row tiles");
+  static_assert(NCOPY % CPM == 0 && NCOPY / CPM <= TM * TN, "copies ride behind the MFMAs of a phase");
   constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   if ((int)blockIdx.x >= tiles_m * tiles_n) {     // side job (see EpiArgs): Eq. 1 scores
@@ -218,11 +217,10 @@ gemm_f8_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ W,
   } while (0)
 
   // NSTAGE LDS stages: the copies of K step t + NSTAGE - 1 are issued while step t computes, so
-  // NSTAGE - 1 steps are in flight.  The 128-row tile has room for three stages (48 KB each); it
-  // is chosen for launches of few workgroups, where one step in flight per CU (a round trip to
-  // HBM per 48 KB) would be the bound.  Waiting for "all but the newest PEND copies" is enough
+  // NSTAGE - 1 steps are in flight: three stages of 48 KB, because with few workgroups one step in
+  // flight per CU (a round trip to HBM per 48 KB) would be the bound.  Waiting for "all but the newest PEND copies" is enough
   // to know that the next step has landed: the counter retires copies in issue order.
-  constexpr int NSTAGE = TM == 1 ? 3 : 2;
+  constexpr int NSTAGE = 3;
   constexpr int PEND = (NSTAGE - 2) * NCOPY;
   const int KT = K / F8_BK;
 #pragma unroll
@@ -301,10 +299,17 @@ gemm_f8_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ W,
   staged_tile_out<32, TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, nullptr, lds);
 }
 
+// Costs of the four-wave kernel's forms on 8-bit operands (see TileCost; a K step is 128 elements), fitted to
+// the four projections of the 4096 / 11008-wide layer at 97 - 8192 rows; end: residual or none, rotary, SiLU * mul.
+static const TileCost F8_COST[3] = {
+    {6.4, 1.26, 0.96, {14.9, 17.0, 7.5}, 9.0, 2.5, 2.5},
+    {8.3, 1.02, 0.90, {7.8, 11.3, 4.4}, 8.1, 2.3, 5.0},
+    {9.8, 0.91, 0.87, {1.7, 5.2, 1.6}, 7.5, 1.7, 3.1}};
+
 hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const float* sw, void* C,
                           const void* R, int M, int N, int K, int lda, int ldw, int ldc, int epilogue,
-                          hipStream_t st, const EpiArgs* ea_in) {
-  constexpr int BN = 256;
+                          hipStream_t st, const EpiArgs* ea_in, void* sk_ws, size_t sk_ws_bytes) {
+  constexpr int BM = 128, BN = 256, LDS_BYTES = 3 * (BM + BN) * ROW_BYTES;
   if (M <= 0) return hipSuccess;
   if (N % BN != 0 || K % F8_BK != 0 || lda % 16 != 0 || ldw % 16 != 0 || lda < K || ldw < K ||
       ((uintptr_t)A & 15) != 0 || ((uintptr_t)W & 15) != 0 || ((uintptr_t)sw & 15) != 0)
@@ -317,17 +322,28 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
     if (ea_in == nullptr || (ea.head_dim != 64 && ea.head_dim != 128) || N != ea.d_model + 2 * kvd)
       return hipErrorInvalidValue;
   }
-  // One workgroup per CU is resident.  A launch whose 128-row tiles still fit one round of the
-  // 256 CUs takes those (half the K-loop work per workgroup, twice the workgroups); anything
-  // larger takes 256-row tiles, which reuse each W slab for twice the rows (measured: gate/up at
-  // 2364 rows 214 us against 262 us with 128-row tiles, although the latter need fewer
-  // half-rounds).  Every output element sees the same sequence of additions either way.
-  const int tiles_n = N / BN;
-  const long t128 = (long)((M + 127) / 128) * tiles_n;
-  const bool tall = t128 > 256;
-  const int BM = tall ? 256 : 128;
-  const int LDS_BYTES = (tall ? 2 : 3) * (BM + BN) * ROW_BYTES;
-  const int tiles_m = (M + BM - 1) / BM;
+  const int tiles_n = N / BN, tiles_m = (M + BM - 1) / BM, KT = K / F8_BK;
+  // Which kernel: by estimated time, as in the 16-bit GEMM.  The 128-row tile of this file, one workgroup
+  // per CU, is ahead while it fits one round and the K loop is short (K 4096, 12288 features: 34 / 37 us at
+  // 97 / 512 rows against 35 / 44; K 11008: 75 / 76 against 52 / 45 for stream-K on 128-row four-wave
+  // tiles); larger launches take the four-wave kernel (us, 8192 rows, before / now: QKV 422 / 345, O 136 / 121,
+  // gate/up 683 / 536, down 316 / 267; 3376 rows 182 / 169, 59 / 58, 282 / 240, 132 / 120).
+  // Outputs that its 16-byte stores cannot address stay here.
+  int rows = 0, stream_k = 0;                        // 0: this file's kernel
+  if (epilogue == EPI_QKV_ROPE || (ldc % 8 == 0 && ((uintptr_t)C & 15) == 0 && ((uintptr_t)R & 15) == 0)) {
+    const bool sk_ok = ea.psk_ready && sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes();
+    double best = (long)tiles_m * tiles_n <= 256 ? 6.0 + 0.8 * KT + (epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU ? 4.5 : 0.0) : 1e30;
+    for (int f = 0; f < 3; ++f)
+      for (int sk = 0; sk <= (sk_ok ? 1 : 0); ++sk) {
+        const double t = gemm_w4_cost(F8_COST[f], 256 - 64 * f, sk != 0, M, N, KT, epilogue);
+        if (t < best) { best = t; rows = 256 - 64 * f; stream_k = sk; }
+      }
+  }
+  if (rows != 0) {
+    return launch_gemm_w4_f8(A, sa, W, sw, C, R, M, N, K, lda, ldw, ldc, epilogue, gemm_band_height(M, epilogue), ea,
+                             stream_k, stream_k ? (float*)sk_ws : nullptr,
+                             stream_k ? gemm_exchange_flags(sk_ws) : nullptr, rows, st);
+  }
   // K-step-major codes ([K / 128][N][128], see launch_pack_kblock): rows of a step 128 bytes apart
   ea.w_step_bytes = ea.w_blocked ? (unsigned long long)N * ROW_BYTES : (unsigned long long)ROW_BYTES;
   if (ea.w_blocked) ldw = F8_BK;
@@ -336,28 +352,21 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
                      ? (ea.d_model % BN == 0 && (ea.kv_dim > 0 ? ea.kv_dim : ea.d_model) % BN == 0)
                      : (epilogue != EPI_SWIGLU && ldc % 8 == 0 && ((uintptr_t)C & 15) == 0);
   const int side = ea.sf_z != nullptr ? ea.sf_blocks_per_seq * ea.sf_batch : 0;
-  const int band = tall ? 8 : 16;
-  const int group_m = tiles_m < band ? tiles_m : band;
+  const int group_m = tiles_m < 16 ? tiles_m : 16;
   dim3 grid(tiles_m * tiles_n + side), block(512);
-#define LZ_GEMM2(E, TMV)                                                                         \
+#define LZ_GEMM(E)                                                                               \
   do {                                                                                           \
-    auto kern = gemm_f8_kernel<E, TMV>;                                                          \
+    auto kern = gemm_f8_kernel<E>;                                                               \
     static bool attr_set = false;                                                                \
     if (!attr_set) {                                                                             \
       hipError_t e = hipFuncSetAttribute((const void*)kern,                                      \
-                                         hipFuncAttributeMaxDynamicSharedMemorySize,             \
-                                         (TMV == 1 ? 3 : 2) * (128 * TMV + BN) * ROW_BYTES);                      \
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES); \
       if (e != hipSuccess) return e;                                                             \
       attr_set = true;                                                                           \
     }                                                                                            \
     hipLaunchKernelGGL(kern, grid, block, LDS_BYTES, st, (const uint8_t*)A, (const uint8_t*)W,   \
                        sa, sw, (uint16_t*)C, (const uint16_t*)R, M, N, K, lda, ldw, ldc,         \
                        tiles_m, tiles_n, group_m, ea);                                           \
-  } while (0)
-#define LZ_GEMM(E)                                                                               \
-  do {                                                                                           \
-    if (tall) LZ_GEMM2(E, 2);                                                                    \
-    else LZ_GEMM2(E, 1);                                                                         \
   } while (0)
   if (epilogue == EPI_STORE) LZ_GEMM(EPI_STORE);
   else if (epilogue == EPI_RESIDUAL) LZ_GEMM(EPI_RESIDUAL);
@@ -368,7 +377,6 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
   }
   else return hipErrorInvalidValue;
 #undef LZ_GEMM
-#undef LZ_GEMM2
   return hipGetLastError();
 }
 

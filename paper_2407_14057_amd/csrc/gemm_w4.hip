@@ -55,6 +55,8 @@
 namespace lz {
 
 constexpr unsigned W4_SPIN_LIMIT = 1u << 22;       // about a second of polling
+typedef int v4i_t __attribute__((ext_vector_type(4)));
+typedef int v8i_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int W4_SLOT = 256 * ROW_BYTES;
 
@@ -87,6 +89,11 @@ __device__ __forceinline__ void acc_mfma(const bf16x8_t& w, const bf16x8_t& a) {
   if constexpr (ZERO) asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, 0" ::"v"(w), "v"(a), "n"(N), "n"(N + 3));
   else asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(w), "v"(a), "n"(N), "n"(N + 3));
 }
+template <int N, bool ZERO>
+__device__ __forceinline__ void acc_mfma(const v8i_t& w, const v8i_t& a) {        // OFP8 E4M3, 128 k at once
+  if constexpr (ZERO) asm volatile("v_mfma_f32_16x16x128_f8f6f4 a[%2:%3], %0, %1, 0" ::"v"(w), "v"(a), "n"(N), "n"(N + 3));
+  else asm volatile("v_mfma_f32_16x16x128_f8f6f4 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(w), "v"(a), "n"(N), "n"(N + 3));
+}
 template <int N>
 __device__ __forceinline__ floatx4_t acc_read() {
   float x, y, z, w;
@@ -108,12 +115,14 @@ __device__ __forceinline__ void unrolled(F&& f) {
   if constexpr (B < N) { f(Int<B>{}); unrolled<N, B + 1>(f); }
 }
 
-template <int TM, int EPI>
+// A and W: rows of lda / ldw BYTES, a K step (KT of them) is 128 bytes of a row: 64 bf16 or, F8, 128 codes.
+// sa, sw (F8): scale of a row of A, of a feature of W.
+template <int TM, int EPI, bool F8>
 __global__ void __launch_bounds__(256)
-gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-               uint16_t* __restrict__ C, const uint16_t* __restrict__ R, int M, int N, int K, int lda,
-               int ldw, int ldc, int tiles_m, int tiles_n, int group_m, int G, int stream_k,
-               float* __restrict__ part, unsigned* __restrict__ flags, EpiArgs ra) {
+gemm_w4_kernel(const char* __restrict__ A, const char* __restrict__ W, const float* __restrict__ sa,
+               const float* __restrict__ sw, uint16_t* __restrict__ C, const uint16_t* __restrict__ R,
+               int M, int KT, int lda, int ldw, int ldc, int tiles_m, int tiles_n, int group_m, int G,
+               int stream_k, float* __restrict__ part, unsigned* __restrict__ flags, EpiArgs ra) {
   constexpr int WN = 2, TN = 8;
   constexpr int BM = 2 * TM * 16, BN = 2 * TN * 16;
   constexpr int NCA = BM / 32, NCW = BN / 32;      // copies per wave of an A / W slab
@@ -137,7 +146,7 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 
   // ---- this workgroup's pieces: n_whole tiles, then (stream-K) the piece of a tile it does not own,
   // then the end of the tile it owns
-  const int T = tiles_m * tiles_n, KT = K / BK;
+  const int T = tiles_m * tiles_n;
   const int full = T / G, Rm = T - full * G;
   const int xcd = g & 7, gi = g >> 3, GX = G >> 3;
   const int Rx = Rm > xcd ? (Rm - xcd + 7) >> 3 : 0;           // remainder tiles of this XCD
@@ -182,13 +191,13 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
       int r = m0 + tr;
       r = r < M ? r : M - 1;                       // rows past the edge: re-read the last row
       if (ra.a_rows != nullptr) r = ra.a_rows[r];
-      a_off[q] = (uint32_t)(((size_t)r * lda + cchunk * 8) * 2);
+      a_off[q] = (uint32_t)((size_t)r * lda + cchunk * 16);
     }
 #pragma unroll
     for (int q = 0; q < NCW; ++q) {
       const int tr = (wave * NCW + q) * 8 + crow;
       const int cchunk = (lane & 7) ^ swz64(tr);
-      w_off[q] = (uint32_t)(((size_t)(n0 + tr) * ldw + cchunk * 8) * 2);
+      w_off[q] = (uint32_t)((size_t)(n0 + tr) * ldw + cchunk * 16);
     }
   };
   auto cursor_next = [&]() {                       // (past the last step: stays, a harmless re-copy)
@@ -198,11 +207,11 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   // one of the wave's copies of a slab (uniform base + 32-bit lane offset; the launcher checks
   // that both operands span less than 4 GB)
   auto copy_a = [&](uint32_t slot, int q) {
-    const char* base = (const char*)A + (uint32_t)c_kt * (uint32_t)ROW_BYTES;
+    const char* base = A + (uint32_t)c_kt * (uint32_t)ROW_BYTES;
     g2l16(base + a_off[q], lds + slot + (wave * NCA + q) * 1024);
   };
   auto copy_w = [&](uint32_t slot, int q) {
-    const char* base = (const char*)W + (uint32_t)c_kt * wstep32;
+    const char* base = W + (uint32_t)c_kt * wstep32;
     g2l16(base + w_off[q], lds + slot + (wave * NCW + q) * 1024);
   };
 
@@ -215,34 +224,56 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     woff[h] = (uint32_t)((wn * TN * 16 + (lane & 15)) * ROW_BYTES) + k;
   }
   // the fragment reads of a half step, in the order in which its MFMAs want them
-#define LZ_READ(buf, sa, sw, h, n)                                                             \
+#define LZ_READ(buf, la, lw, h, n)                                                             \
   do {                                                                                         \
-    if ((n) == 0) wf[buf][0] = *(const bf16x8_t*)(lds + (sw) + woff[h]);                       \
-    else if ((n) <= TM) af[buf][(n)-1] = *(const bf16x8_t*)(lds + (sa) + aoff[h] + ((n)-1) * 16 * ROW_BYTES); \
-    else wf[buf][(n)-TM] = *(const bf16x8_t*)(lds + (sw) + woff[h] + ((n)-TM) * 16 * ROW_BYTES); \
+    if ((n) == 0) wf[buf][0] = *(const bf16x8_t*)(lds + (lw) + woff[h]);                       \
+    else if ((n) <= TM) af[buf][(n)-1] = *(const bf16x8_t*)(lds + (la) + aoff[h] + ((n)-1) * 16 * ROW_BYTES); \
+    else wf[buf][(n)-TM] = *(const bf16x8_t*)(lds + (lw) + woff[h] + ((n)-TM) * 16 * ROW_BYTES); \
   } while (0)
   // TM * TN MFMAs on fragments `buf` (ZERO: from a zero accumulator); behind every RE-th a fragment
   // read of the next half step (buffer `nb`) until they are through, and the nc copies evenly.  The order is
   // the program's: nothing is scheduled across a slot.  RUN = false: reads and copies only.
-#define LZ_HALF(ZERO, RUN, buf, nb, sa, sw, h, copy, nc, slot)                                 \
+#define LZ_HALF(ZERO, RUN, buf, nb, la, lw, h, copy, nc, slot)                                 \
   unrolled<TM * TN>([&](auto nn) {                                                             \
     constexpr int n = decltype(nn)::value, j = n / TM, i = (j & 1) ? TM - 1 - n % TM : n % TM; \
     if constexpr (RUN) acc_mfma<4 * (i * TN + j), ZERO>(wf[buf][j], af[buf][i]);               \
-    if constexpr (n % RE == 0 && n / RE < TM + TN) LZ_READ(nb, sa, sw, h, n / RE);             \
+    if constexpr (n % RE == 0 && n / RE < TM + TN) LZ_READ(nb, la, lw, h, n / RE);             \
     constexpr int CE = TM * TN / (nc);                                                         \
+    if constexpr (n % CE == CE / 2 && n / CE < (nc)) copy(slot, n / CE);                       \
+    __builtin_amdgcn_sched_barrier(0);                                                         \
+  })
+  // The 8-bit form multiplies 128 k at once, so its half steps are the left and the right four columns of
+  // blocks: in the first, the rest of the step's fragments are read (the last row block of A, the
+  // right half of W), in the second each row block's fragment of the next step right behind its last
+  // use, and the left half of W.  Reads and copies stand where those of the 16-bit form do, between
+  // the same two barriers.
+#define LZ_READ8(dst, base, off, n)                                                            \
+  dst = __builtin_shufflevector(*(const v4i_t*)(lds + (base) + off[0] + (n) * 16 * ROW_BYTES), \
+                                *(const v4i_t*)(lds + (base) + off[1] + (n) * 16 * ROW_BYTES), 0, 1, 2, 3, 4, 5, 6, 7)
+#define LZ_HALF8(ZERO, RUN, right, la_, lw_, copy, nc, slot)                                   \
+  unrolled<TM * TN / 2>([&](auto nn) {                                                         \
+    constexpr int n = decltype(nn)::value, i = n / 4, jj = (i & 1) ? 3 - n % 4 : n % 4;        \
+    if constexpr (RUN) acc_mfma<4 * (i * TN + 4 * (right) + jj), ZERO>(f8w[right][jj], f8a[i]); \
+    if constexpr (!(right) && n == 0) LZ_READ8(f8a[TM - 1], la_, aoff, TM - 1);                \
+    if constexpr (!(right) && n % 4 == 3 && n / 4 < 4) LZ_READ8(f8w[1][n / 4], lw_, woff, 4 + n / 4); \
+    if constexpr ((right) && n % 4 == 3 && i < TM - 1) LZ_READ8(f8a[i], la_, aoff, i);         \
+    if constexpr ((right) && n % 4 == 1 && n / 4 < 4) LZ_READ8(f8w[0][n / 4], lw_, woff, n / 4); \
+    constexpr int CE = TM * TN / 2 / (nc);                                                     \
     if constexpr (n % CE == CE / 2 && n / CE < (nc)) copy(slot, n / CE);                       \
     __builtin_amdgcn_sched_barrier(0);                                                         \
   })
 #define LZ_STEP(ZERO, RUN)                                                                     \
   do {                                                                                         \
-    LZ_HALF(ZERO, RUN, 0, 1, sa, sw, 1, copy_a, NCA, next_slot(sa, 4));                        \
+    if constexpr (F8) LZ_HALF8(ZERO, RUN, 0, la, lw, copy_a, NCA, next_slot(la, 4));           \
+    else LZ_HALF(ZERO, RUN, 0, 1, la, lw, 1, copy_a, NCA, next_slot(la, 4));                   \
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NCA) : "memory");         \
     __builtin_amdgcn_sched_barrier(0);                                                         \
-    const uint32_t freed = sa;                                                                 \
-    stage_slot = sw;                                                                           \
-    sa = next_slot(sa, 2);                                                                     \
-    sw = next_slot(sw, 2);                                                                     \
-    LZ_HALF(0, RUN, 1, 0, sa, sw, 0, copy_w, NCW, freed);                                      \
+    const uint32_t freed = la;                                                                 \
+    stage_slot = lw;                                                                           \
+    la = next_slot(la, 2);                                                                     \
+    lw = next_slot(lw, 2);                                                                     \
+    if constexpr (F8) LZ_HALF8(ZERO, RUN, 1, la, lw, copy_w, NCW, freed);                      \
+    else LZ_HALF(0, RUN, 1, 0, la, lw, 0, copy_w, NCW, freed);                                 \
     cursor_next();                                                                             \
     LZ_ACC_RESERVE();                                                                          \
     __builtin_amdgcn_sched_barrier(0);                                                         \
@@ -260,7 +291,7 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #pragma unroll
   for (int q = 0; q < NCW; ++q) copy_w(3 * SLOT, q);
   cursor_next();
-  uint32_t sa = 0, sw = SLOT, stage_slot = 0;      // slots of the current step; of the last step's W slab
+  uint32_t la = 0, lw = SLOT, stage_slot = 0;      // slots of the current step; of the last step's W slab
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NCA + NCW) : "memory");
   __builtin_amdgcn_sched_barrier(0);
@@ -272,16 +303,26 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     // (the last half step of the piece before has read these fragments too: reading them again costs
     // some hundred cycles a tile, keeping them through the epilogue 64 registers that it needs)
     bf16x8_t af[2][TM], wf[2][TN];
+    v8i_t f8a[TM], f8w[2][4];
+    if constexpr (F8) {
 #pragma unroll
-    for (int n = 0; n < TM + TN; ++n) LZ_READ(0, sa, sw, 0, n);
+      for (int n = 0; n < TM - 1; ++n) LZ_READ8(f8a[n], la, aoff, n);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) LZ_READ8(f8w[0][n], lw, woff, n);
+    } else {
+#pragma unroll
+      for (int n = 0; n < TM + TN; ++n) LZ_READ(0, la, lw, 0, n);
+    }
     unsigned long long ssq[TM];                    // of this lane's rows: fetched here, turned into 1/rms below
     float rs[TM];
+    float rowscale[TM];
     int pos[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int row = m0 + (wm * TM + i) * 16 + (lane & 15), rc = row < M ? row : M - 1;
       if (EPI != EPI_RESIDUAL && ra.ssq_in != nullptr) ssq[i] = ra.ssq_in[ra.a_rows != nullptr ? ra.a_rows[rc] : rc];
       if (EPI == EPI_QKV_ROPE64 || EPI == EPI_QKV_ROPE128) pos[i] = ra.pos[rc];
+      if (F8) rowscale[i] = sa[rc];
     }
     const bool gives = it >= n_whole && it - n_whole < n_oth;  // a piece of somebody else's tile
     const bool takes = it >= n_whole && !gives && own_ka > 0;  // the end of a tile of several pieces
@@ -404,7 +445,7 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     // a wave's LDS accesses complete in order, so what it wrote is there when it reads: only the
     // compiler has to keep the order
 #define LZ_LDS_ORDER() asm volatile("" ::: "memory")
-    constexpr int RAHEAD = 4;                      // residual rows are fetched this many blocks ahead
+    constexpr int RAHEAD = F8 ? 3 : 4;                    // residual rows are fetched this many blocks ahead
     u32x4_t rr[RAHEAD][NST];
     auto fetch_residual = [&](auto ii) {
       constexpr int i = decltype(ii)::value;
@@ -430,6 +471,11 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
         tb[i & 1][q][1] = *(const float4*)(cs + q * 16 + 2);
       }
     };
+    floatx4_t colscale[F8 ? TN : 1];               // of this lane's features
+    if constexpr (F8) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) colscale[j] = *(const floatx4_t*)(sw + col0 + 16 * j + feat);
+    }
     // block i of 16 rows; VPART: the columns are V's
     auto put_rows = [&](auto ii, auto vv) {
       constexpr int i = decltype(ii)::value;
@@ -441,6 +487,10 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
       floatx4_t x[TN];
       unrolled<TN>([&](auto jj) { constexpr int j = decltype(jj)::value; x[j] = acc_read<4 * (i * TN + j)>(); });
       if (ra.ssq_clear != nullptr && n0 == 0 && wn == 0 && el < 16 && valid) ra.ssq_clear[row] = 0;
+      if constexpr (F8) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) x[j] *= rowscale[i] * colscale[j];
+      }
       if (EPI != EPI_RESIDUAL && ra.ssq_in != nullptr) {
         // RMSNorm of the A operand's row, applied to the product
 #pragma unroll
@@ -586,6 +636,8 @@ gemm_w4_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   }
 #undef LZ_READ
 #undef LZ_HALF
+#undef LZ_READ8
+#undef LZ_HALF8
 #undef LZ_STEP
 #undef LZ_LDS_ORDER
 #undef LZ_ACC_RESERVE
@@ -603,28 +655,29 @@ static int w4_resident_workgroups(KernT kern, int lds_bytes) {
   return per_cu >= 1 ? cus : 0;
 }
 
-template <int TM>
-static hipError_t launch_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
-                            int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra, int stream_k,
-                            float* part, unsigned* flags, hipStream_t st) {
-  constexpr int BM = 32 * TM, BN = 256, LDS_BYTES = 5 * W4_SLOT;
-  if (N % BN != 0) return hipErrorInvalidValue;
-  if ((unsigned long long)M * lda * 2 >= (1ull << 32) ||
-      (unsigned long long)N * (ra.w_blocked ? K : ldw) * 2 >= (1ull << 32))
+template <int TM, bool F8>
+static hipError_t launch_w4(const void* A, const float* sa, const void* W, const float* sw, void* C, const void* R,
+                            int M, int N, int K, int lda, int ldw, int ldc, int epi, int group_m,
+                            const EpiArgs& ra, int stream_k, float* part, unsigned* flags, hipStream_t st) {
+  constexpr int BM = 32 * TM, BN = 256, LDS_BYTES = 5 * W4_SLOT, ESIZE = F8 ? 1 : 2;
+  if (N % BN != 0 || K % (ROW_BYTES / ESIZE) != 0) return hipErrorInvalidValue;
+  if ((unsigned long long)M * lda * ESIZE >= (1ull << 32) ||
+      (unsigned long long)N * (ra.w_blocked ? K : ldw) * ESIZE >= (1ull << 32))
     return hipErrorInvalidValue;
   if (stream_k && (part == nullptr || flags == nullptr || K > (1 << 24))) return hipErrorInvalidValue;
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
-  EpiArgs ea = ra;
-  ea.w_step_bytes = ra.w_blocked ? (unsigned long long)N * ROW_BYTES : (unsigned long long)ROW_BYTES;
-  if (ra.w_blocked) ldw = BK;                       // rows of one K step are 128 bytes apart
-  ea.sf_blocks_per_seq = (ea.sf_max_rows + 255) / 256;
   // rows leave in 16-byte chunks
   if (epi != EPI_QKV_ROPE && (ldc % 8 != 0 || ((uintptr_t)C & 15) != 0 || ((uintptr_t)R & 15) != 0))
     return hipErrorInvalidValue;
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN, KT = K / (ROW_BYTES / ESIZE);
+  EpiArgs ea = ra;
+  ea.w_step_bytes = ra.w_blocked ? (unsigned long long)N * ROW_BYTES : (unsigned long long)ROW_BYTES;
+  lda *= ESIZE;
+  ldw = ra.w_blocked ? ROW_BYTES : ldw * ESIZE;     // blocked: rows of one K step are 128 bytes apart
+  ea.sf_blocks_per_seq = (ea.sf_max_rows + 255) / 256;
   const int side = ea.sf_z != nullptr ? ea.sf_blocks_per_seq * ea.sf_batch : 0;
 #define LZ_GEMM(E)                                                                               \
   do {                                                                                           \
-    auto kern = gemm_w4_kernel<TM, E>;                                                           \
+    auto kern = gemm_w4_kernel<TM, E, F8>;                                                       \
     static int resident = -1;                                                                    \
     if (resident < 0) {                                                                          \
       hipError_t e = hipFuncSetAttribute((const void*)kern,                                      \
@@ -638,9 +691,9 @@ static hipError_t launch_w4(const void* A, const void* W, void* C, const void* R
       G = gemm_aligned_grid(G, tiles_m * tiles_n);                                               \
       if (G < 8) return hipErrorInvalidConfiguration;                                            \
     } else if (G < 8 || G > tiles_m * tiles_n) G = tiles_m * tiles_n;                            \
-    hipLaunchKernelGGL(kern, dim3(G + side), dim3(256), LDS_BYTES, st, (const uint16_t*)A,       \
-                       (const uint16_t*)W, (uint16_t*)C, (const uint16_t*)R, M, N, K, lda, ldw,  \
-                       ldc, tiles_m, tiles_n, group_m, G, stream_k, part, flags, ea);            \
+    hipLaunchKernelGGL(kern, dim3(G + side), dim3(256), LDS_BYTES, st, (const char*)A,           \
+                       (const char*)W, sa, sw, (uint16_t*)C, (const uint16_t*)R, M, KT, lda,     \
+                       ldw, ldc, tiles_m, tiles_n, group_m, G, stream_k, part, flags, ea);       \
   } while (0)
   if (epi == EPI_STORE) LZ_GEMM(EPI_STORE);
   else if (epi == EPI_RESIDUAL) LZ_GEMM(EPI_RESIDUAL);
@@ -657,10 +710,17 @@ static hipError_t launch_w4(const void* A, const void* W, void* C, const void* R
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra, int stream_k,
                           float* part, unsigned* flags, int rows, hipStream_t st) {
-  if (rows == 256) return launch_w4<8>(A, W, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st);
-  if (rows == 192) return launch_w4<6>(A, W, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st);
-  if (rows == 128) return launch_w4<4>(A, W, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st);
-  return hipErrorInvalidValue;
+#define LZ_W4(TM) launch_w4<TM, false>(A, nullptr, W, nullptr, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st)
+  return rows == 256 ? LZ_W4(8) : rows == 192 ? LZ_W4(6) : rows == 128 ? LZ_W4(4) : hipErrorInvalidValue;
+#undef LZ_W4
+}
+
+hipError_t launch_gemm_w4_f8(const void* A, const float* sa, const void* W, const float* sw, void* C, const void* R,
+                             int M, int N, int K, int lda, int ldw, int ldc, int epi, int group_m,
+                             const EpiArgs& ra, int stream_k, float* part, unsigned* flags, int rows, hipStream_t st) {
+#define LZ_W4(TM) launch_w4<TM, true>(A, sa, W, sw, C, R, M, N, K, lda, ldw, ldc, epi, group_m, ra, stream_k, part, flags, st)
+  return rows == 256 ? LZ_W4(8) : rows == 192 ? LZ_W4(6) : rows == 128 ? LZ_W4(4) : hipErrorInvalidValue;
+#undef LZ_W4
 }
 
 }  // namespace lz
