@@ -318,6 +318,174 @@ flash_attn_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
 }
 
 // ------------------------------------------------------------------------------------------
+// Form for short sequences: the NW waves of a workgroup share 32 queries of one head and deal out the
+// 64-key steps among them (wave w takes steps w, w + NW, ...).  With 128 queries per workgroup a short
+// prompt makes few workgroups, each a serial chain of steps; here there are four times as many and a
+// chain is NW times shorter.  A step's K rows and Vt columns go straight from memory (the L2, mostly) into
+// operand registers, all of a step's loads in flight at once: no LDS staging, no barrier until the
+// waves' results meet.  There the reference points and sums are exchanged, each wave scales its O^T to the
+// common reference point, and the sum over the waves is taken in wave order, each wave adding a part of
+// the rows.  Every step a wave takes holds a key that each of its queries sees (the step's first key
+// is no later than the first query), so a reference point is finite after a wave's first step.
+// Against the form above, us inside the prefill: see launch_attention.
+// ------------------------------------------------------------------------------------------
+template <int HD, int NW>
+__global__ void __launch_bounds__(NW * 64, 2)
+flash_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                        const uint16_t* __restrict__ vt, uint16_t* __restrict__ o,
+                        const int32_t* __restrict__ cu, const int32_t* __restrict__ cu_vt, int n_single,
+                        int vt_ld, int n_heads, float scale_log2e, float* __restrict__ z,
+                        float2* __restrict__ zstat, int z_ld, int kv_group) {
+  constexpr int KSTEPS = HD / 16, HS = HD / 32;
+  __shared__ float2 stat[NW][32];                  // reference point, sum: of a wave's steps, per query
+  __shared__ float4 part[NW][HS * 4][64];          // O^T of the waves, in the accumulator's layout
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int head = blockIdx.x, b = blockIdx.z;
+  int row0, n;
+  seq_range(cu, b, n_single, row0, n);
+  const int qblocks = (n + 31) / 32;
+  if ((int)blockIdx.y >= qblocks) return;
+  const int q0 = (qblocks - 1 - (int)blockIdx.y) * 32;       // longest blocks first
+  const int d = n_heads * HD, kvd = d / kv_group, kvh = head / kv_group;
+  const int hi = lane >> 5, l31 = lane & 31;
+  const int qrow = q0 + l31, qrow_c = qrow < n ? qrow : n - 1;
+  bf16x8_t qf[KSTEPS];
+  {
+    const uint16_t* qp = q + (size_t)(row0 + qrow_c) * d + head * HD + hi * 8;
+#pragma unroll
+    for (int s = 0; s < KSTEPS; ++s) qf[s] = *(const bf16x8_t*)(qp + s * 16);
+  }
+  const int ntiles = q0 / ATT_BN + 1;              // (q0 is a multiple of 32: the queries' own keys end in this step)
+  const uint16_t* kbase = k + (size_t)row0 * kvd + kvh * HD + hi * 8;
+  const uint16_t* vbase = vt + ((size_t)kvh * HD + l31) * vt_ld + (cu_vt ? cu_vt[b] : 0) + hi * 8;
+  const int kperm = (l31 & 0x13) | ((l31 & 4) << 1) | ((l31 & 8) >> 1);   // swap bits 2 and 3
+  const bool score_wg = z != nullptr && q0 <= n - 1 && n - 1 <= q0 + 31;  // owns the last query
+
+  floatx16_t oacc[HS];
+#pragma unroll
+  for (int h = 0; h < HS; ++h)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[h][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  for (int it = wave; it < ntiles; it += NW) {
+    const int k0 = it * ATT_BN;
+    bf16x8_t kf[2][KSTEPS], vf[2 * KSTEPS];
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+      int key = k0 + sub * 32 + kperm;
+      key = key < n ? key : n - 1;
+#pragma unroll
+      for (int s = 0; s < KSTEPS; ++s) kf[sub][s] = *(const bf16x8_t*)(kbase + (size_t)key * kvd + s * 16);
+    }
+    // Vt: fragment i = 4 * h + 2 * sub + t is rows 32 h .., keys k0 + 32 sub + 16 t + 8 hi ..
+#pragma unroll
+    for (int i = 0; i < 2 * KSTEPS; ++i)
+      vf[i] = *(const bf16x8_t*)(vbase + (size_t)(i >> 2) * 32 * vt_ld + k0 + ((i >> 1) & 1) * 32 + (i & 1) * 16);
+    floatx16_t sacc[2];
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sacc[sub][r] = 0.f;
+#pragma unroll
+      for (int s = 0; s < KSTEPS; ++s)
+        sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sub][s], qf[s], sacc[sub], 0, 0, 0);
+    }
+    // Register r of block sub is key k0 + 32*sub + 16*(r/8) + 8*hi + r%8.
+    if (k0 + ATT_BN - 1 > q0) {
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = k0 + 32 * sub + 16 * (r / 8) + 8 * hi + (r % 8);
+          if (key > qrow) sacc[sub][r] = -INFINITY;
+        }
+    }
+    if (score_wg && qrow == n - 1) {               // Eq. 1: the last query's logits (see above)
+      float* zr = z + (size_t)head * z_ld + (cu_vt ? cu_vt[b] : 0) + k0 + 8 * hi;
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *(float4*)(zr + 32 * sub + 16 * (g >> 1) + 4 * (g & 1)) =
+              make_float4(sacc[sub][4 * g] * scale_log2e, sacc[sub][4 * g + 1] * scale_log2e,
+                          sacc[sub][4 * g + 2] * scale_log2e, sacc[sub][4 * g + 3] * scale_log2e);
+    }
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, sacc[sub][r]);
+    mloc *= scale_log2e;
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    if (__builtin_amdgcn_ballot_w64(mloc > m_run + 8.0f) != 0) {
+      const float m_new = fmaxf(m_run, mloc);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int h = 0; h < HS; ++h) oacc[h] *= alpha;
+    }
+    const float neg_m = -m_run;
+    bf16x8_t pf[2][2];
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        float p[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          p[j] = __builtin_amdgcn_exp2f(fmaf(sacc[sub][8 * t + j], scale_log2e, neg_m));
+          l_run += p[j];
+        }
+        uint4 packed = pack8(p);
+        pf[sub][t] = *reinterpret_cast<bf16x8_t*>(&packed);
+      }
+#pragma unroll
+    for (int i = 0; i < 2 * KSTEPS; ++i)
+      oacc[i >> 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], pf[(i >> 1) & 1][i & 1], oacc[i >> 2], 0, 0, 0);
+  }
+
+  // ---- the waves' results meet (a wave without a step: reference point -inf, weight 0)
+  const float l_wave = l_run + __shfl_xor(l_run, 32, 64);
+  if (hi == 0) stat[wave][l31] = make_float2(m_run, l_wave);
+  __syncthreads();
+  float m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, stat[w][l31].x);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) l_all += stat[w][l31].y * __builtin_amdgcn_exp2f(stat[w][l31].x - m_all);
+  const float mine = __builtin_amdgcn_exp2f(m_run - m_all), inv = 1.0f / l_all;
+#pragma unroll
+  for (int h = 0; h < HS; ++h)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      part[wave][h * 4 + g][lane] = make_float4(oacc[h][4 * g] * mine, oacc[h][4 * g + 1] * mine,
+                                                oacc[h][4 * g + 2] * mine, oacc[h][4 * g + 3] * mine);
+  __syncthreads();
+  if (score_wg && wave == 0 && qrow == n - 1 && hi == 0)     // reference point and 1 / sum for Eq. 1
+    zstat[(size_t)b * n_heads + head] = make_float2(m_all, inv);
+  // register 4 * g of block h is dim 32h + 8g + 4*hi
+  static_assert(HS * 4 % NW == 0, "every wave adds the same number of register groups");
+#pragma unroll
+  for (int u = 0; u < HS * 4 / NW; ++u) {
+    const int hg = wave * (HS * 4 / NW) + u;
+    float4 s4 = part[0][hg][lane];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      const float4 t4 = part[w][hg][lane];
+      s4.x += t4.x; s4.y += t4.y; s4.z += t4.z; s4.w += t4.w;
+    }
+    if (qrow < n) {
+      uint2 w2;
+      w2.x = pack_bf16(s4.x * inv, s4.y * inv);
+      w2.y = pack_bf16(s4.z * inv, s4.w * inv);
+      *(uint2*)(o + (size_t)(row0 + qrow) * d + head * HD + (hg >> 2) * 32 + (hg & 3) * 8 + 4 * hi) = w2;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // Ping-pong form for long sequences (8 waves = 256 queries of one head per workgroup, NS stages).
 // The flash_attn_kernel above keeps all eight waves in step (one barrier per 64-key step, after
 // the softmax), so the two waves of a SIMD do their matrix work at the same time and their
@@ -698,6 +866,31 @@ hipError_t launch_attention(const void* q, const void* k, const void* vt, void* 
   // (measured at 32 heads, one sequence: 1967 rows 55 us with 4 waves against 58 with 8, 2364 rows
   // 76 against 68, 3376 rows 135 against 108)
   const int nw = ((max_rows + 255) / 256) * n_heads * batch > 256 ? 8 : 4;
+  // Short sequences: while blocks of 32 queries make at most one workgroup per CU, the form whose waves
+  // share out the keys of such a block (two waves up to two key steps, else four).  Measured, us, 128
+  // queries per workgroup / shared keys: 32 heads of 128 at 97 rows 6.8 / 5.6, 128 rows 7.4 / 5.8, 215 rows
+  // 9.3 / 7.6, 256 rows 10.1 / 8.1, but 300 rows (320 workgroups) 10.2 / 10.8, 512 rows 15.5 / 16.5 (K and V
+  // are read for 32 queries at a time); 4 heads of 64 at 180 rows 5.7 / 4.3, 512 rows 10.8 / 6.7, 1024 rows
+  // 18.8 / 10.5, 1967 rows 32.7 / 18.5.  With up to eight heads the longest sequence of a batch decides,
+  // however many there are: a small model's projections add in the same order whatever the rows, and a packed
+  // prompt then has the bits of the prompt alone (several such workgroups on a CU still beat the longer chain).
+#define LZ_ATT_SPLIT(HD, NW)                                                                     \
+  do {                                                                                           \
+    dim3 grid(n_heads, (max_rows + 31) / 32, batch), block(64 * NW);                             \
+    hipLaunchKernelGGL((flash_attn_split_kernel<HD, NW>), grid, block, 0, st, (const uint16_t*)q,  \
+                       (const uint16_t*)k, (const uint16_t*)vt, (uint16_t*)o, cu, cu_vt, n_single, \
+                       vt_ld, n_heads, scale_log2e, z, (float2*)zstat, z_ld, kv_group);          \
+    return hipGetLastError();                                                                    \
+  } while (0)
+  if ((head_dim == 64 || head_dim == 128) && (long)((max_rows + 31) / 32) * n_heads * (n_heads <= 8 ? 1 : batch) <= 256) {
+    if (max_rows <= 2 * ATT_BN) {
+      if (head_dim == 128) LZ_ATT_SPLIT(128, 2);
+      else LZ_ATT_SPLIT(64, 2);
+    }
+    if (head_dim == 128) LZ_ATT_SPLIT(128, 4);
+    else LZ_ATT_SPLIT(64, 4);
+  }
+#undef LZ_ATT_SPLIT
 #define LZ_ATT(HD, NW, NS)                                                                       \
   do {                                                                                           \
     constexpr int LDS_BYTES = NS * 2 * ATT_BN * HD * 2;                                          \

@@ -661,6 +661,26 @@ def test_attention_sharp_rows():
     assert np.abs(_f64(o) - o_ref.reshape(rows, d)).max() < 3e-2
 
 
+@pytest.mark.parametrize("rows,H,hd", [(1, 8, 128), (33, 8, 64), (128, 32, 128), (129, 32, 128), (256, 32, 128), (257, 32, 128),
+                                       (2048, 4, 64), (2049, 4, 64)])
+def test_attention_shared_keys(rows, H, hd):
+    """The form whose waves share out the keys of 32 queries (two waves up to 128 rows, four up to 256
+    workgroups; the last case of each pair is just past a limit), with keys that grow along the sequence,
+    so that the waves' reference points differ by far more than the lazy-rescale threshold."""
+    rng = np.random.default_rng(rows + H)
+    d = H * hd
+    q = _rand_bf16(rng, (rows, d), 2.0); k = _rand_bf16(rng, (rows, d), 2.0); v = _rand_bf16(rng, (rows, d))
+    k[::53] *= 3.0
+    pad = (rows + 63) // 64 * 64
+    vt = torch.zeros(d, pad, dtype=torch.bfloat16, device=DEV); vt[:, :rows] = v.t()
+    o = torch.empty(rows, d, dtype=torch.bfloat16, device=DEV)
+    B.lazyllm_op_attention(q, k, vt.contiguous(), pad, o, rows, H, hd)
+    torch.cuda.synchronize()
+    sh = (rows, H, hd)
+    o_ref, _ = O.causal_attention(_f64(q).reshape(sh), _f64(k).reshape(sh), _f64(v).reshape(sh))
+    assert np.abs(_f64(o) - o_ref.reshape(rows, d)).max() < 3e-2
+
+
 @pytest.mark.parametrize("rows,H,hd", [(2049, 32, 128), (2364, 32, 128), (3376, 32, 128), (1100, 64, 64), (1281, 64, 64)])
 def test_attention_headline_form(rows, H, hd):
     """The kernel form the 7B workloads launch (more than 256 query blocks of 256 rows over all heads:
