@@ -33,11 +33,11 @@ def gate_up_traffic_bytes():
     return float(m.group(1)) * 1e6 if m else None
 
 
-STEP_KERNEL = {"gemm_gate_up": "gemm_pp_kernel<4,2,2,4,EPI_SWIGLU> (RMSNorm scale + gate/up projection + SiLU*mul; at 355 rows "
-                               "the same epilogue under gemm_stream_kernel<EPI_SWIGLU>)",
-               "gemm_qkv": "gemm_pp_kernel<4,2,2,4,EPI_QKV_ROPE128> (RMSNorm scale + QKV projection + RoPE + V^T)",
-               "gemm_down": "gemm_pp_kernel<4,2,2,4,EPI_RESIDUAL> (down projection + residual + row sums of squares)",
-               "gemm_o": "gemm_pp_kernel<4,2,2,4,EPI_RESIDUAL> (O projection + residual + row sums of squares)"}
+STEP_KERNEL = {"gemm_gate_up": "gemm_w4_kernel<8,EPI_SWIGLU> (RMSNorm scale + gate/up projection + SiLU*mul; at 355 rows "
+                               "the 192-row form, gemm_w4_kernel<6,EPI_SWIGLU>)",
+               "gemm_qkv": "gemm_w4_kernel<8,EPI_QKV_ROPE128> (RMSNorm scale + QKV projection + RoPE + V^T)",
+               "gemm_down": "gemm_w4_kernel<8 or 6,EPI_RESIDUAL> (down projection + residual + row sums of squares)",
+               "gemm_o": "gemm_w4_kernel<8 or 6,EPI_RESIDUAL> (O projection + residual + row sums of squares)"}
 
 
 def kernel_sweep(args, torch, B) -> int:
@@ -265,7 +265,7 @@ def fused_compaction_study(args, wl, model, ids, sched, cu, scale, torch, B) -> 
 
 
 def band_height_sweep(args, torch, B) -> int:
-    """The dominant GEMM alone (gate/up projection of the 7B shape at 3376 rows, 256x256 ping-pong tiles)
+    """The dominant GEMM alone (gate/up projection of the 7B shape at 3376 rows, 256x256 tiles)
     against the height of the tile-walk band: the number of tile rows that share a run of W column blocks in
     one XCD's L2.  Under `rocprofv3 --pmc FETCH_SIZE` the launches of one band height are told apart by their
     order, which the lines printed here give.  The weights rotate over 8 copies, so none is L2-resident from
@@ -284,7 +284,7 @@ def band_height_sweep(args, torch, B) -> int:
     c = torch.zeros(M, N // 2, device=dev, dtype=torch.bfloat16)
     rows = []
     for gm in (1, 2, 4, 7, 14):
-        e = B.EPI_SWIGLU | (5 << 8) | (gm << 16) | (1 << 29)     # forced: 256x256 ping-pong tiles, band height gm
+        e = B.EPI_SWIGLU | (5 << 8) | (gm << 16) | (1 << 29)     # forced: 256x256 tiles, band height gm
         for i in range(warm):
             B.lazyllm_op_gemm(a, ws[i % n_w], c, None, M, N, K, K, K, N // 2, e)
         torch.cuda.synchronize()

@@ -340,16 +340,14 @@ int lazyllm_profile_end(lazyllm_profile_record* out, int32_t capacity, int32_t* 
  * (rows 64j..64j+31 gate, 64j+32..64j+63 up), C[M,N/2] = silu(gate) * up.
  * Requires N % 128 == 0, K % 64 == 0, 16-byte aligned rows.
  * workspace: optional device scratch of lazyllm_op_gemm_workspace_bytes() (256-byte
- * aligned) that lets epilogues 0 and 1 use the stream-K schedule for shapes whose tile
- * count does not divide over the CUs, and epilogue 2 walk its tiles with one workgroup per
- * CU when there are more tiles than CUs (same bits either way); NULL = never.
+ * aligned) that lets the library split tiles over K (stream-K) for shapes whose tile count does not
+ * divide over the CUs; NULL = whole tiles only.
  * Bits 8..15 of `epilogue` force a tile configuration (measurement hook; 0 = the
- * library chooses): 2 = 128x128, 3 = 128x128 in waves of 32x128, 4 = 128x256, 5 = 256x256 ping-pong, 7 = 192x256
- * ping-pong, 6 = 128x128 stream-K (needs the workspace), 8 = the weight-streaming
- * kernel of few token rows (shapes that lazyllm_op_gemm_stream_plan accepts, needs the workspace),
- * 9 / 10 = the 256x256 / 192x256
- * ping-pong tiles under the persistent stream-K schedule (need the workspace), 13 = 128x256 on
- * 8 waves of 32x128 with three stages, 14 = 256x256 on four waves of 128x128 (one per SIMD).  EINVAL where a
+ * library chooses): 2 = 128x128, 3 = 128x128 in waves of 32x128, 4 = 128x256, 13 = 128x256 on
+ * 8 waves of 32x128 with three stages, 6 = 128x128 stream-K (needs the workspace), 8 = the
+ * weight-streaming kernel of few token rows (shapes that lazyllm_op_gemm_stream_plan accepts, needs
+ * the workspace); on four waves, one per SIMD: 5 (and 14) = 256x256, 7 = 192x256, 15 = 128x256, and
+ * with stream-K (need the workspace) 9 = 256x256, 10 = 192x256, 16 = 128x256.  EINVAL where a
  * configuration does not fit the shape. */
 size_t lazyllm_op_gemm_workspace_bytes(void);
 int lazyllm_op_gemm(const void* A, const void* W, void* C, const void* R, int32_t M, int32_t N,

@@ -1101,11 +1101,11 @@ int lazyllm_op_gemm(const void* A, const void* W, void* C, const void* R, int32_
   if (workspace != nullptr && ((uintptr_t)workspace & 255) != 0) return LAZYLLM_EINVAL;
   const int forced = (epilogue >> 8) & 0xff;
   if (forced == 8 && !gemm_stream_takes(M, N, K)) return LAZYLLM_EINVAL;
-  if ((forced == 8 || forced == 9 || forced == 10) && (workspace == nullptr || ws_bytes < gemm_workspace_bytes()))
+  if ((forced == 8 || forced == 9 || forced == 10 || forced == 16) && (workspace == nullptr || ws_bytes < gemm_workspace_bytes()))
     return LAZYLLM_EINVAL;
   EpiArgs ea{};
   if (workspace != nullptr && ws_bytes >= gemm_workspace_bytes()) {
-    // the tickets of the weight-streaming kernel and the flags of the persistent stream-K kernel
+    // the tickets of the weight-streaming kernel and the flags of the four-wave kernel's stream-K
     // live at the end of the workspace and must start at zero
     LZ_HIP(launch_gemm_counters_clear(workspace, (hipStream_t)hip_stream));
     ea.psk_ready = 1;
@@ -1143,7 +1143,7 @@ int lazyllm_op_gemm_rmsnorm(const void* A, const void* W, void* C, const void* R
   ea.ssq_out = (unsigned long long*)ssq_out;
   ea.ssq_clear = (unsigned long long*)ssq_clear;
   // the 128x128 stream-K schedule has no row scaling or clearing: of the forms it may be chosen
-  // for, only the plain residual one gets the workspace; the SiLU*mul form (tile walk, persistent
+  // for, only the plain residual one gets the workspace; the SiLU*mul form (four-wave tiles, whole or
   // stream-K: both scale rows) always may
   const bool sk_ok = (!ssq_in && !ssq_clear) || epi == EPI_SWIGLU;
   const bool use_ws = sk_ok && workspace != nullptr && ws_bytes >= gemm_workspace_bytes();

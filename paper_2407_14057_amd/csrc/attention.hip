@@ -492,8 +492,7 @@ flash_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restri
 // vector work at the same time, and the matrix pipe idles through every softmax.  Measured on
 // this part, matrix and vector instructions of two waves on one SIMD DO run side by side (32
 // MFMAs against 32 fma + exp2 + add groups: 0.60 us together, 0.56 us for the MFMAs alone), so
-// here the two waves of a SIMD (w and w + 4) run half a step apart, as in the GEMM's ping-pong
-// schedule: a wave alternates a MATRIX half step  M(i) = [O^T += Vt(i-1) P^T(i-1)] [S^T(i) = K(i) Q^T]
+// here the two waves of a SIMD (w and w + 4) run half a step apart: a wave alternates a MATRIX half step  M(i) = [O^T += Vt(i-1) P^T(i-1)] [S^T(i) = K(i) Q^T]
 // (32 MFMAs back to back, the LDS reads of the next operands in their shadow) and a VECTOR half
 // step  V(i) = softmax of step i's 64 keys (mask, running maximum, exp2, bf16 P), and while one
 // wave of the pair is in M the other is in V.  A bare s_barrier closes every phase:

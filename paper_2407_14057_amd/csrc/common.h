@@ -164,11 +164,11 @@ struct EpiArgs {
   const int32_t* sf_cu_z;
   int sf_n_single, sf_heads, sf_z_ld, sf_max_rows, sf_batch;
   int sf_blocks_per_seq;             // filled in by the launcher (depends on the workgroup size)
-  int stage_out;                     // filled in by the launcher: tile goes out through LDS (see gemm.hip)
+  int stage_out;                     // filled in by the launcher: tile goes out through LDS (staged_tile_out)
   // the caller keeps the ticket counters at the end of the GEMM workspace zeroed
   // (launch_gemm_counters_clear once before the first use): few rows may take the streaming kernel
   int skinny;
-  // the caller keeps the flags of the persistent stream-K kernel (also at the end of the GEMM
+  // the caller keeps the flags of the four-wave kernel's stream-K (also at the end of the GEMM
   // workspace) zeroed likewise: launches whose tile count leaves the last round of the chip partly
   // idle may take that kernel
   int psk_ready;
