@@ -153,7 +153,7 @@ gemm_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
   for (int t = 0; t < NS; ++t)
     if (t < KT) issue(t, t * BK);
   float rs[TM];
-  load_row_scales<32, TM>(rs, ra, M, m0, wm, lane);
+  load_row_scales<TM>(rs, ra, M, m0, wm, lane);
   // (three steps in flight: only the first has to be there; the row scales fetched last are needed in the epilogue)
   if (NS == 3 && KT >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * (A_INSTR + W_INSTR)) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -188,7 +188,7 @@ gemm_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #undef LZ_MFMAS
 #undef LZ_SCHED
 
-  gemm_epilogue<32, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
+  gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra, rs);
 }
 
 template <int WM, int WN, int TM, int TN, int NS = 2>
@@ -384,7 +384,7 @@ gemm_sk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
 #undef LZ_LOAD_FRAGS
 #undef LZ_MFMAS
     if (ka == 0 && kb == KT) {
-      gemm_epilogue<32, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
+      gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
     } else {
       // fp32 partial sums of this piece, tile-local row-major [128][128]
       float* dst = partial + ((size_t)g * 2 + (tile == first_tile ? 0 : 1)) * SK_TILE_ELEMS;

@@ -293,10 +293,10 @@ gemm_f8_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ W,
   }
 
   if (EPI == EPI_SWIGLU || !ra.stage_out) {
-    gemm_epilogue<32, TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
+    gemm_epilogue<TM, TN, EPI>(acc, C, R, M, ldc, m0, n0, wm, wn, lane, ra);
     return;
   }
-  staged_tile_out<32, TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, nullptr, lds);
+  staged_tile_out<TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, nullptr, lds);
 }
 
 // Costs of the four-wave kernel's forms on 8-bit operands (see TileCost; a K step is 128 elements), fitted to
