@@ -445,7 +445,7 @@ def main() -> int:
     achieved = dwork / (dms * 1e-3) / 1e12                       # TFLOP/s over this step's launches
     traffic = gate_up_traffic_bytes() if (dom == "gemm_gate_up" and wl.name == "7b_3376") else None
     peak = PEAK_FP8_TFLOPS if f8 else PEAK_BF16_TFLOPS
-    kernel = ("quantize_rows_f8_kernel + gemm_f8_kernel (%s)" % dom) if f8 else STEP_KERNEL[dom]
+    kernel = ("quantize_rows_f8_kernel + gemm_w4_kernel<.., true> (%s)" % dom) if f8 else STEP_KERNEL[dom]
     roofline = {"bound": "mfma", "kernel": kernel, "achieved": round(achieved, 1),
                 "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "avg_launch_ms": round(dms / dn, 5), "flops_per_launch": dwork / dn, "traffic": traffic,
