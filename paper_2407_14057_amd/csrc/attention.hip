@@ -325,8 +325,10 @@ flash_attn_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
 // operand registers, all of a step's loads in flight at once: no LDS staging, no barrier until the
 // waves' results meet.  There the reference points and sums are exchanged, each wave scales its O^T to the
 // common reference point, and the sum over the waves is taken in wave order, each wave adding a part of
-// the rows.  Every step a wave takes holds a key that each of its queries sees (the step's first key
-// is no later than the first query), so a reference point is finite after a wave's first step.
+// the rows.  The reference point starts at the lowest finite value, not at -infinity: a wave need not see
+// a finite logit in its first steps (nor in any) where another wave does, and -infinity minus itself would
+// turn keys of weight zero into NaN.  A step or a wave without a finite logit then has weight zero, and
+// only a query whose logits are -infinity throughout ends in 0 / 0, as in the form above.
 // Against the form above, us inside the prefill: see launch_attention.
 // ------------------------------------------------------------------------------------------
 template <int HD, int NW>
@@ -367,7 +369,7 @@ flash_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restri
   for (int h = 0; h < HS; ++h)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[h][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -3.402823466e38f, l_run = 0.f;
   for (int it = wave; it < ntiles; it += NW) {
     const int k0 = it * ATT_BN;
     bf16x8_t kf[2][KSTEPS], vf[2 * KSTEPS];
@@ -446,11 +448,11 @@ flash_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restri
       oacc[i >> 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], pf[(i >> 1) & 1][i & 1], oacc[i >> 2], 0, 0, 0);
   }
 
-  // ---- the waves' results meet (a wave without a step: reference point -inf, weight 0)
+  // ---- the waves' results meet (a wave without a step has weight 0)
   const float l_wave = l_run + __shfl_xor(l_run, 32, 64);
   if (hi == 0) stat[wave][l31] = make_float2(m_run, l_wave);
   __syncthreads();
-  float m_all = -INFINITY, l_all = 0.f;
+  float m_all = -3.402823466e38f, l_all = 0.f;
 #pragma unroll
   for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, stat[w][l31].x);
 #pragma unroll

@@ -681,6 +681,40 @@ def test_attention_shared_keys(rows, H, hd):
     assert np.abs(_f64(o) - o_ref.reshape(rows, d)).max() < 3e-2
 
 
+@pytest.mark.parametrize("rows,H,hd", [(100, 8, 128), (200, 8, 64), (500, 4, 64), (256, 32, 128), (700, 32, 128)])
+def test_attention_keys_of_minus_infinity(rows, H, hd):
+    """Logits that overflow to -infinity have probability zero and leave the other keys alone, also where
+    they are all that a wave sees in a step (keys 64 .. 127: the second step, which in the form with shared keys
+    is another wave's first)."""
+    rng = np.random.default_rng(rows + H + hd)
+    d = H * hd
+    q = _rand_bf16(rng, (rows, d)); k = _rand_bf16(rng, (rows, d)); v = _rand_bf16(rng, (rows, d))
+    q.view(rows, H, hd)[:, :, 0] = 1e20
+    k.view(rows, H, hd)[:, :, 0] = 0.0
+    k.view(rows, H, hd)[64:128, :, 0] = -1e30
+    pad = (rows + 63) // 64 * 64
+    vt = torch.zeros(d, pad, dtype=torch.bfloat16, device=DEV); vt[:, :rows] = v.t()
+    o = torch.empty(rows, d, dtype=torch.bfloat16, device=DEV)
+    s = torch.full((rows,), -1.0, dtype=torch.float32, device=DEV)
+    scratch = torch.empty(B.lazyllm_op_score_scratch_bytes(rows, H), dtype=torch.uint8, device=DEV)
+    B.lazyllm_op_attention_score(q, k, vt.contiguous(), pad, o, s, scratch, rows, H, hd)
+    torch.cuda.synchronize()
+    # the definition without those keys: a query below row 128 sees the first 64, a later one those and its own
+    keys = np.r_[0:64, 128:rows] if rows > 128 else np.arange(64)
+    q64, k64, v64 = (_f64(t).reshape(rows, H, hd) for t in (q, k, v))
+    q64[:, :, 0] = 0.0
+    ref = np.empty((rows, H, hd))
+    z = np.einsum("qhe,khe->hqk", q64, k64[keys]) / math.sqrt(hd)
+    z[:, keys[None, :] > np.arange(rows)[:, None]] = -np.inf
+    p = np.exp(z - z.max(axis=2, keepdims=True))
+    p /= p.sum(axis=2, keepdims=True)
+    ref = np.einsum("hqk,khe->qhe", p, v64[keys]).reshape(rows, d)
+    assert np.abs(_f64(o) - ref).max() < 3e-2
+    want = np.zeros(rows)
+    want[keys] = p[:, rows - 1].mean(axis=0)
+    assert np.allclose(s.cpu().numpy().astype(np.float64), want, rtol=2e-5, atol=1e-9)
+
+
 @pytest.mark.parametrize("rows,H,hd", [(2049, 32, 128), (2364, 32, 128), (3376, 32, 128), (1100, 64, 64), (1281, 64, 64)])
 def test_attention_headline_form(rows, H, hd):
     """The kernel form the 7B workloads launch (more than 256 query blocks of 256 rows over all heads:
