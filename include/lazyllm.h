@@ -453,6 +453,12 @@ int lazyllm_op_v_transpose(const void* v, void* vt, int32_t vt_ld, int32_t rows,
 int lazyllm_op_attention(const void* q, const void* k, const void* vt, int32_t vt_ld, void* o,
                          int32_t rows, int32_t n_heads, int32_t head_dim, void* hip_stream);
 
+/* How many queries of a head one workgroup of the prefill's attention takes, for `batch` sequences of which
+ * the longest has max_rows rows (host only, nothing is enqueued): 32 (its waves share out the keys of those
+ * queries), 128 or 256 (one wave per 32 queries).  The forms add in different orders: a sequence of a batch
+ * can have the bits it gets alone only where both take the same form.  EINVAL for arguments no prefill has. */
+int lazyllm_op_attention_block(int32_t max_rows, int32_t batch, int32_t n_heads, int32_t head_dim);
+
 /* lazyllm_op_attention plus Eq. 1 in the form the prefill uses: the attention
  * kernel leaves the last query's logits against every key in `scratch`, and a
  * second kernel turns them into s[j] = (1/H) sum_h softmax_j(...) (fp32 [rows]).

@@ -147,6 +147,7 @@ _SIGNATURES = {
                                          C.c_int32, C.c_void_p]),
     "lazyllm_op_attention": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p,
                                        C.c_int32, C.c_int32, C.c_int32, C.c_void_p]),
+    "lazyllm_op_attention_block": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
     "lazyllm_op_attention_score": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p,
                                              C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32,
                                              C.c_void_p]),

@@ -1257,6 +1257,11 @@ int lazyllm_op_attention(const void* q, const void* k, const void* vt, int32_t v
   return LAZYLLM_OK;
 }
 
+int lazyllm_op_attention_block(int32_t max_rows, int32_t batch, int32_t n_heads, int32_t head_dim) {
+  if (max_rows <= 0 || batch <= 0 || n_heads <= 0 || (head_dim != 64 && head_dim != 128)) return LAZYLLM_EINVAL;
+  return attention_block(max_rows, batch, n_heads, head_dim);
+}
+
 int lazyllm_op_attention_score(const void* q, const void* k, const void* vt, int32_t vt_ld, void* o,
                                float* s, void* scratch, int32_t rows, int32_t n_heads,
                                int32_t head_dim, void* hip_stream) {

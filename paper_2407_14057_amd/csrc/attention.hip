@@ -329,7 +329,7 @@ flash_attn_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
 // a finite logit in its first steps (nor in any) where another wave does, and -infinity minus itself would
 // turn keys of weight zero into NaN.  A step or a wave without a finite logit then has weight zero, and
 // only a query whose logits are -infinity throughout ends in 0 / 0, as in the form above.
-// Against the form above, us inside the prefill: see launch_attention.
+// Against the form above: see attention_block.
 // ------------------------------------------------------------------------------------------
 template <int HD, int NW>
 __global__ void __launch_bounds__(NW * 64, 2)
@@ -854,27 +854,41 @@ flash_attn_pp_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
   }
 }
 
+// Queries of one workgroup: 32 (its waves share out the keys), 128 or 256 (one wave per 32 queries).
+int attention_block(int max_rows, int batch, int n_heads, int head_dim) {
+  // Short sequences and few of them: the form whose waves share out the keys (two waves up to two key steps,
+  // else four), while its workgroups are at most one per CU, with 64-wide heads (half the LDS and
+  // registers) two.  Past that the chip is busy and what counts is that K and V are read for 32 queries at a
+  // time instead of 128.  Measured, us, 128 or 256 queries per workgroup / shared keys, by workgroups of the latter:
+  //   32 heads of 128, one sequence: 97 rows (128) 7.0 / 5.7, 256 rows (256) 10.2 / 8.2, but 300 rows (320) 10.2 / 10.8
+  //   8 heads of 128: 256 rows x 4 (256) 10.2 / 8.2, x 8 (512) 10.4 / 13.1, x 64 41 / 74; 1024 rows (256) 25.4 / 19.7,
+  //     x 2 (512) 25.8 / 34.5, x 8 52 / 88; 180 rows x 8 (384) 8.0 / 10.0
+  //   4 heads of 64: 512 rows (64) 11.4 / 6.9, x 8 (512) 11.7 / 11.1, x 16 (1024) 12.1 / 18.2; 2048 rows (256) 35.1 / 19.7,
+  //     x 2 (512) 35.2 / 32.5, x 4 (1024) 35.8 / 48.2; 128 rows x 64 (1024) 6.5 / 8.1
+  // With one key step there is no chain to share and little to read: workgroups of two waves replace such of four,
+  // of which two or three idle.  33 rows, 8 heads of 64: x 64 7.5 / 5.7, x 256 27 / 17; of 128: x 64 9.9 / 9.2, x 256
+  // 38 / 32, but 4 heads x 256 20.3 / 21.6; 3 rows x 256, 8 heads 33 / 16.  128-wide heads that fit the chip are
+  // level (4.7 / 4.8), and the form without the exchange stays.
+  const long shared = (long)((max_rows + 31) / 32) * n_heads * batch;
+  if (max_rows <= ATT_BN ? head_dim == 64 || shared > (max_rows <= 32 ? 256 : 2048)
+                         : shared <= (head_dim == 64 ? 512 : 256)) return 32;
+  // 8-wave workgroups (one per CU, four stages) when they alone fill the chip: they halve the
+  // L2 -> LDS traffic per query.  Otherwise 4-wave ones, which spread a short sequence over
+  // more CUs.
+  // (measured at 32 heads, one sequence: 1967 rows 55 us with 4 waves against 58 with 8, 2364 rows
+  // 76 against 68, 3376 rows 135 against 108)
+  return ((max_rows + 255) / 256) * n_heads * batch > 256 ? 256 : 128;
+}
+
 hipError_t launch_attention(const void* q, const void* k, const void* vt, void* o, const int32_t* cu,
                             const int32_t* cu_vt, int n_single, int batch, int max_rows, int vt_ld,
                             int n_heads, int head_dim, hipStream_t st, float* z, void* zstat,
                             int z_ld, int kv_group) {
   if (max_rows <= 0) return hipSuccess;
   if (kv_group < 1 || n_heads % kv_group != 0) return hipErrorInvalidValue;
+  if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)head_dim);
-  // 8-wave workgroups (one per CU, four stages) when they alone fill the chip: they halve the
-  // L2 -> LDS traffic per query.  Otherwise 4-wave ones, which spread a short sequence over
-  // more CUs.
-  // (measured at 32 heads, one sequence: 1967 rows 55 us with 4 waves against 58 with 8, 2364 rows
-  // 76 against 68, 3376 rows 135 against 108)
-  const int nw = ((max_rows + 255) / 256) * n_heads * batch > 256 ? 8 : 4;
-  // Short sequences: while blocks of 32 queries make at most one workgroup per CU, the form whose waves
-  // share out the keys of such a block (two waves up to two key steps, else four).  Measured, us, 128
-  // queries per workgroup / shared keys: 32 heads of 128 at 97 rows 6.8 / 5.6, 128 rows 7.4 / 5.8, 215 rows
-  // 9.3 / 7.6, 256 rows 10.1 / 8.1, but 300 rows (320 workgroups) 10.2 / 10.8, 512 rows 15.5 / 16.5 (K and V
-  // are read for 32 queries at a time); 4 heads of 64 at 180 rows 5.7 / 4.3, 512 rows 10.8 / 6.7, 1024 rows
-  // 18.8 / 10.5, 1967 rows 32.7 / 18.5.  With up to eight heads the longest sequence of a batch decides,
-  // however many there are: a small model's projections add in the same order whatever the rows, and a packed
-  // prompt then has the bits of the prompt alone (several such workgroups on a CU still beat the longer chain).
+  const int block = attention_block(max_rows, batch, n_heads, head_dim), nw = block / 32;
 #define LZ_ATT_SPLIT(HD, NW)                                                                     \
   do {                                                                                           \
     dim3 grid(n_heads, (max_rows + 31) / 32, batch), block(64 * NW);                             \
@@ -883,7 +897,7 @@ hipError_t launch_attention(const void* q, const void* k, const void* vt, void* 
                        vt_ld, n_heads, scale_log2e, z, (float2*)zstat, z_ld, kv_group);          \
     return hipGetLastError();                                                                    \
   } while (0)
-  if ((head_dim == 64 || head_dim == 128) && (long)((max_rows + 31) / 32) * n_heads * (n_heads <= 8 ? 1 : batch) <= 256) {
+  if (block == 32) {
     if (max_rows <= 2 * ATT_BN) {
       if (head_dim == 128) LZ_ATT_SPLIT(128, 2);
       else LZ_ATT_SPLIT(64, 2);
@@ -908,7 +922,6 @@ hipError_t launch_attention(const void* q, const void* k, const void* vt, void* 
                        (const uint16_t*)vt, (uint16_t*)o, cu, cu_vt, n_single, vt_ld, n_heads,   \
                        scale_log2e, z, (float2*)zstat, z_ld, kv_group);                          \
   } while (0)
-  if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
   static const int pp_form = [] { const char* e = getenv("LAZYLLM_ATT_PP"); return e ? atoi(e) : 1; }();
 #define LZ_ATT_PP(HD, NS)                                                                          \
   do {                                                                                           \

@@ -254,6 +254,7 @@ hipError_t launch_v_transpose(const void* v, void* vt, const int32_t* cu, const 
 // so they must be finite) and, for a packed batch, writes the column of every row.
 hipError_t launch_vt_stage_setup(void* vt, int32_t* vt_col, const int32_t* cu, const int32_t* cu_vt,
                                  int n_single, int batch, int vt_ld, int n_feat, hipStream_t st);
+int attention_block(int max_rows, int batch, int n_heads, int head_dim);   // queries of a workgroup: 32, 128 or 256
 hipError_t launch_attention(const void* q, const void* k, const void* vt, void* o, const int32_t* cu,
                             const int32_t* cu_vt, int n_single, int batch, int max_rows, int vt_ld,
                             int n_heads, int head_dim, hipStream_t st, float* z = nullptr,

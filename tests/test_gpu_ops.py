@@ -661,12 +661,14 @@ def test_attention_sharp_rows():
     assert np.abs(_f64(o) - o_ref.reshape(rows, d)).max() < 3e-2
 
 
-@pytest.mark.parametrize("rows,H,hd", [(1, 8, 128), (33, 8, 64), (128, 32, 128), (129, 32, 128), (256, 32, 128), (257, 32, 128),
-                                       (2048, 4, 64), (2049, 4, 64)])
-def test_attention_shared_keys(rows, H, hd):
-    """The form whose waves share out the keys of 32 queries (two waves up to 128 rows, four up to 256
-    workgroups; the last case of each pair is just past a limit), with keys that grow along the sequence,
-    so that the waves' reference points differ by far more than the lazy-rescale threshold."""
+@pytest.mark.parametrize("rows,H,hd,block", [(1, 8, 128, 128), (1, 8, 64, 32), (33, 8, 64, 32), (64, 32, 128, 128), (65, 32, 128, 32), (128, 32, 128, 32),
+                                             (129, 32, 128, 32), (256, 32, 128, 32), (257, 32, 128, 128), (2048, 4, 64, 32), (2049, 4, 64, 32),
+                                             (2048, 8, 64, 32), (2049, 8, 64, 128)])
+def test_attention_shared_keys(rows, H, hd, block):
+    """The form whose waves share out the keys of 32 queries (two waves up to 128 rows, else four) on both
+    sides of the limits of its rule, with keys that grow along the sequence, so that the waves' reference
+    points differ by far more than the lazy-rescale threshold."""
+    assert B.lib().lazyllm_op_attention_block(rows, 1, H, hd) == block
     rng = np.random.default_rng(rows + H)
     d = H * hd
     q = _rand_bf16(rng, (rows, d), 2.0); k = _rand_bf16(rng, (rows, d), 2.0); v = _rand_bf16(rng, (rows, d))

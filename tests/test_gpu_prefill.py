@@ -364,6 +364,21 @@ def test_batch_of_ragged_prompts(tiny_gains):
         assert all(torch.equal(single.kept_pos(l), snap[b][1][l]) for l in range(4))
 
 
+def test_batch_whose_stages_take_different_attention_forms(tiny_gains):
+    """Six packed prompts of 1 to 700 rows: too many query blocks for the form with shared keys before the
+    first pruning, few enough after it."""
+    shape, wb, model = tiny_gains
+    lens = [40, 700, 1, 333, 700, 90]
+    sched = [(1, 800), (3, 400)]
+    assert [B.lib().lazyllm_op_attention_block(n, 6, shape.n_heads, shape.head_dim) for n in (700, 560)] == [128, 32]
+    ids = np.concatenate([synth.make_prompt(n, shape.vocab, 520 + i) for i, n in enumerate(lens)])
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = _run(model, ids, sched, cu=list(cu))
+    assert out.status == 0
+    for b, n in enumerate(lens):
+        check_against_checker(shape, wb, ids[cu[b]:cu[b + 1]], sched, out, seq=b, verbose="batch seq %d" % b)
+
+
 def test_batch_of_a_thousand_short_prompts(tiny_gains):
     """More sequences than one launch carries lengths for (they reach the device by value, 960 per
     launch): the row tables of sequences on both sides of that boundary are right, and a packed

@@ -277,3 +277,21 @@ def test_decode_key_splits_leave_no_wide_step_on_one_range():
                 if keys > 2048 and base <= 256 and 2 * m <= 16 * 128:
                     assert n > 1, (heads, keys, m)
     assert splits(1, 64, 4, 64) == B.LAZYLLM_EINVAL and splits(2, 0, 4, 64) == B.LAZYLLM_EINVAL and splits(2, 64, 4, 96) == B.LAZYLLM_EINVAL
+
+
+def test_attention_form_counts_the_whole_batch():
+    """Shared keys while all sequences together make at most one workgroup per compute unit (two with 64-wide
+    heads): beyond it that form took 1.2 to 2 times as long, whatever the number of heads.  With one key step
+    it is the smaller workgroup of the two."""
+    block = B.lib().lazyllm_op_attention_block
+    for heads in (1, 2, 4, 8, 16, 32):
+        for hd, limit in ((64, 512), (128, 256)):
+            for rows in (65, 97, 180, 256, 512, 1024, 2048):
+                for batch in (1, 2, 3, 8, 64, 1000):
+                    shared = -(-rows // 32) * heads * batch
+                    assert (block(rows, batch, heads, hd) == 32) == (shared <= limit), (rows, batch, heads, hd)
+    assert [block(n, 1000, 4, 64) for n in (5, 32, 33, 64, 65)] == [32, 32, 32, 32, 256]
+    assert [block(n, 64, 8, 128) for n in (5, 32, 33)] == [32, 32, 256] and block(33, 256, 8, 128) == 32 and block(5, 8, 8, 128) == 128
+    assert block(512, 1, 4, 64) == 32 and block(3376, 1, 32, 128) == 256 and block(844, 1, 32, 128) == 128
+    for bad in ((0, 1, 4, 64), (8, 0, 4, 64), (8, 1, 0, 64), (8, 1, 4, 96)):
+        assert block(*bad) == B.LAZYLLM_EINVAL
