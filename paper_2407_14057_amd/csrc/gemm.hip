@@ -685,7 +685,7 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
   const bool ws_ok = sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes();
   // (the four-wave kernel: operands below 4 GB, outputs that 16-byte stores can address)
   const bool w4_ok = N % 256 == 0 && operands_fit_32bit(M, N, K, lda, ldw, ra.w_blocked != 0) &&
-                     (epilogue == EPI_QKV_ROPE || (ldc % 8 == 0 && ((uintptr_t)C & 15) == 0 && ((uintptr_t)R & 15) == 0));
+                     rows_in_16_byte_chunks(epilogue, C, R, ldc, ra);
   if (cfg == 0) {
     // few token rows, and the weight at hand in its streaming layout: gemm_stream.hip, up to where
     // the tile kernels become the better ones (see gemm_stream_takes; row-major, the same kernel is
@@ -709,7 +709,7 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
   // (forced, but with outputs that 16-byte stores cannot address: the 128x128 tile)
   if ((cfg == 5 || cfg == 7 || cfg == 9 || cfg == 10 || cfg >= 14) && N % 256 == 0 && !w4_ok &&
       operands_fit_32bit(M, N, K, lda, ldw, ra.w_blocked != 0))
-    cfg = 2;
+    cfg = epilogue == EPI_QKV_ROPE && ra.head_dim == 128 ? 3 : 2;
   switch (cfg) {
     case 2:                                             // 128x128, 4 waves of 64x64
             return launch_cfg<2, 2, 2, 2>(A, W, C, R, M, N, K, lda, ldw, ldc, epilogue, group_m, ra, st);

@@ -330,7 +330,7 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
   // gate/up 683 / 536, down 316 / 267; 3376 rows 182 / 169, 59 / 58, 282 / 240, 132 / 120).
   // Outputs that its 16-byte stores cannot address stay here.
   int rows = 0, stream_k = 0;                        // 0: this file's kernel
-  if (epilogue == EPI_QKV_ROPE || (ldc % 8 == 0 && ((uintptr_t)C & 15) == 0 && ((uintptr_t)R & 15) == 0)) {
+  if (rows_in_16_byte_chunks(epilogue, C, R, ldc, ea)) {
     const bool sk_ok = ea.psk_ready && sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes();
     double best = (long)tiles_m * tiles_n <= 256 ? 6.0 + 0.8 * KT + (epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU ? 4.5 : 0.0) : 1e30;
     for (int f = 0; f < 3; ++f)
@@ -349,7 +349,8 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
   if (ea.w_blocked) ldw = F8_BK;
   ea.sf_blocks_per_seq = (ea.sf_max_rows + 511) / 512;
   ea.stage_out = (epilogue == EPI_QKV_ROPE)
-                     ? (ea.d_model % BN == 0 && (ea.kv_dim > 0 ? ea.kv_dim : ea.d_model) % BN == 0)
+                     ? (ea.d_model % BN == 0 && (ea.kv_dim > 0 ? ea.kv_dim : ea.d_model) % BN == 0 &&
+                        rows_in_16_byte_chunks(epilogue, C, R, ldc, ea))
                      : (epilogue != EPI_SWIGLU && ldc % 8 == 0 && ((uintptr_t)C & 15) == 0);
   const int side = ea.sf_z != nullptr ? ea.sf_blocks_per_seq * ea.sf_batch : 0;
   const int group_m = tiles_m < 16 ? tiles_m : 16;

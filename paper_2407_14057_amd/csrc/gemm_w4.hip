@@ -666,8 +666,7 @@ static hipError_t launch_w4(const void* A, const float* sa, const void* W, const
     return hipErrorInvalidValue;
   if (stream_k && (part == nullptr || flags == nullptr || K > (1 << 24))) return hipErrorInvalidValue;
   // rows leave in 16-byte chunks
-  if (epi != EPI_QKV_ROPE && (ldc % 8 != 0 || ((uintptr_t)C & 15) != 0 || ((uintptr_t)R & 15) != 0))
-    return hipErrorInvalidValue;
+  if (!rows_in_16_byte_chunks(epi, C, R, ldc, ra)) return hipErrorInvalidValue;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN, KT = K / (ROW_BYTES / ESIZE);
   EpiArgs ea = ra;
   ea.w_step_bytes = ra.w_blocked ? (unsigned long long)N * ROW_BYTES : (unsigned long long)ROW_BYTES;

@@ -602,6 +602,29 @@ def test_qkv_rope(rows, H, hd):
     assert exact > 0.99, exact
 
 
+@pytest.mark.parametrize("rows,H,hd", [(130, 4, 64), (2100, 8, 128)])
+def test_qkv_rope_to_outputs_on_8_byte_boundaries(rows, H, hd):
+    """q, k and v that 16-byte stores cannot address take a tile that stores 8 bytes: the same bits (every tile adds
+    in the same order), nothing in front of them or behind."""
+    rng = np.random.default_rng(rows + H)
+    d = H * hd
+    x = _rand_bf16(rng, (rows, d))
+    w = _rand_bf16(rng, (3 * d, d), 1.0 / math.sqrt(d))
+    pos = torch.arange(rows, dtype=torch.int32, device=DEV)
+    table = torch.empty(rows * hd, dtype=torch.float32, device=DEV)
+    for shifted in (0, 1, 2):                                # which of the three is on an 8-byte boundary
+        bufs = [torch.full((rows * d + 16,), 3.0, dtype=torch.bfloat16, device=DEV) for _ in range(3)]
+        ref = [torch.full((rows * d,), 3.0, dtype=torch.bfloat16, device=DEV) for _ in range(3)]
+        outs = [t[4 if i == shifted else 8:][:rows * d] for i, t in enumerate(bufs)]
+        B.lazyllm_op_qkv_rope(x, w, pos, rows - 1, table, *ref, rows, H, hd, 10000.0)
+        B.lazyllm_op_qkv_rope(x, w, pos, rows - 1, table, *outs, rows, H, hd, 10000.0)
+        torch.cuda.synchronize()
+        for i, t in enumerate(bufs):
+            first = 4 if i == shifted else 8
+            assert torch.equal(outs[i], ref[i]), (shifted, i)
+            assert bool((t[:first] == 3.0).all()) and bool((t[first + rows * d:] == 3.0).all())
+
+
 @pytest.mark.parametrize("rows,H,hd", [(1, 4, 64), (130, 4, 64), (200, 2, 128), (64, 32, 128)])
 def test_v_transpose(rows, H, hd):
     rng = np.random.default_rng(rows + H + hd + 1)
