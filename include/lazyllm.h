@@ -424,6 +424,21 @@ int lazyllm_op_gemm_fp8(const void* a_codes, const float* a_scale, const void* w
                         const float* w_scale, void* C, const void* R, int32_t M, int32_t N, int32_t K,
                         int32_t lda, int32_t ldw, int32_t ldc, int32_t epilogue, void* hip_stream);
 
+/* lazyllm_op_gemm_fp8 with what the prefill has in hand: workspace as in lazyllm_op_gemm (tiles may be split
+ * over K), and bits 8..15 of `epilogue` force a configuration: 2 = 128x256 on 8 waves, and by the
+ * numbers of lazyllm_op_gemm the four-wave tiles 5, 7, 15 and 9, 10, 16 (these three need the workspace). */
+int lazyllm_op_gemm_fp8_ws(const void* a_codes, const float* a_scale, const void* w_codes,
+                           const float* w_scale, void* C, const void* R, int32_t M, int32_t N, int32_t K,
+                           int32_t lda, int32_t ldw, int32_t ldc, int32_t epilogue, void* workspace,
+                           size_t ws_bytes, void* hip_stream);
+
+/* The configuration (numbers as above) that the library chooses for a product, given aligned contiguous
+ * operands; epilogue 3 is the QKV projection with rotary embedding.  have: bit 0 a workspace, bit 1 (with
+ * bit 0; 16-bit only) the weight's streaming layout as well, i.e. 3 for the projections of a model.  Host
+ * only, nothing is enqueued.  EINVAL for shapes that have none. */
+int lazyllm_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t head_dim, int32_t have);
+int lazyllm_op_gemm_fp8_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t have);
+
 /* x = h * rsqrt(mean(h^2) + eps) * gain, bf16 in and out, rows of width d. */
 int lazyllm_op_rmsnorm(const void* h, const void* gain, void* x, int32_t rows, int32_t d,
                        float eps, void* hip_stream);

@@ -137,6 +137,11 @@ _SIGNATURES = {
     "lazyllm_op_gemm_fp8": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                       C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                       C.c_int32, C.c_int32, C.c_void_p]),
+    "lazyllm_op_gemm_fp8_ws": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
+                                         C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
+                                         C.c_int32, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "lazyllm_op_gemm_plan": (C.c_int, [C.c_int32] * 6),
+    "lazyllm_op_gemm_fp8_plan": (C.c_int, [C.c_int32] * 5),
     "lazyllm_op_rmsnorm": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32,
                                      C.c_float, C.c_void_p]),
     "lazyllm_op_qkv_rope": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p,
@@ -354,10 +359,15 @@ def lazyllm_op_quantize_fp8(x, rows, K, ldx, codes, ldq, scale, stream=None) -> 
 
 
 def lazyllm_op_gemm_fp8(a_codes, a_scale, w_codes, w_scale, Cout, R, M, N, K, lda, ldw, ldc, epilogue,
-                        stream=None) -> None:
-    _check(lib().lazyllm_op_gemm_fp8(_ptr(a_codes), _ptr(a_scale), _ptr(w_codes), _ptr(w_scale),
-                                     _ptr(Cout), _ptr(R), M, N, K, lda, ldw, ldc, epilogue,
-                                     _stream_ptr(stream)))
+                        stream=None, workspace=None) -> None:
+    if workspace is None:
+        _check(lib().lazyllm_op_gemm_fp8(_ptr(a_codes), _ptr(a_scale), _ptr(w_codes), _ptr(w_scale),
+                                         _ptr(Cout), _ptr(R), M, N, K, lda, ldw, ldc, epilogue,
+                                         _stream_ptr(stream)))
+        return
+    _check(lib().lazyllm_op_gemm_fp8_ws(_ptr(a_codes), _ptr(a_scale), _ptr(w_codes), _ptr(w_scale),
+                                        _ptr(Cout), _ptr(R), M, N, K, lda, ldw, ldc, epilogue, _ptr(workspace),
+                                        workspace.numel() * workspace.element_size(), _stream_ptr(stream)))
 
 
 def lazyllm_op_rmsnorm(h, gain, x, rows, d, eps, stream=None) -> None:

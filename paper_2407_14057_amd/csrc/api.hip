@@ -1183,9 +1183,10 @@ int lazyllm_op_quantize_fp8(const void* x, int32_t rows, int32_t K, int32_t ldx,
   return LAZYLLM_OK;
 }
 
-int lazyllm_op_gemm_fp8(const void* a_codes, const float* a_scale, const void* w_codes,
-                        const float* w_scale, void* C, const void* R, int32_t M, int32_t N, int32_t K,
-                        int32_t lda, int32_t ldw, int32_t ldc, int32_t epilogue, void* hip_stream) {
+int lazyllm_op_gemm_fp8_ws(const void* a_codes, const float* a_scale, const void* w_codes,
+                           const float* w_scale, void* C, const void* R, int32_t M, int32_t N, int32_t K,
+                           int32_t lda, int32_t ldw, int32_t ldc, int32_t epilogue, void* workspace,
+                           size_t ws_bytes, void* hip_stream) {
   if (!a_codes || !a_scale || !w_codes || !w_scale || !C || M < 0 || N <= 0 || K <= 0)
     return LAZYLLM_EINVAL;
   if (N % 256 != 0 || K % 128 != 0 || lda % 16 != 0 || ldw % 16 != 0 || ldc % 4 != 0 || lda < K || ldw < K)
@@ -1194,16 +1195,49 @@ int lazyllm_op_gemm_fp8(const void* a_codes, const float* a_scale, const void* w
     return LAZYLLM_EINVAL;
   if ((uint64_t)M * (uint64_t)lda >= (1ull << 32) || (uint64_t)N * (uint64_t)ldw >= (1ull << 32))
     return LAZYLLM_EINVAL;
+  if (workspace != nullptr && ((uintptr_t)workspace & 255) != 0) return LAZYLLM_EINVAL;
   const bool blocked = (epilogue & (1 << 29)) != 0;   // w_codes K-step-major: [K / 128][N][128]
   if (epilogue >= 0) epilogue &= ~(1 << 29);
-  if (epilogue < 0 || epilogue > 2 || (epilogue == EPI_RESIDUAL && !R)) return LAZYLLM_EINVAL;
-  if (ldc < (epilogue == EPI_SWIGLU ? N / 2 : N)) return LAZYLLM_EINVAL;
+  const int epi = epilogue & 0xff, forced = epilogue >> 8;
+  if (epilogue < 0 || epi > 2 || (epi == EPI_RESIDUAL && !R)) return LAZYLLM_EINVAL;
+  if (ldc < (epi == EPI_SWIGLU ? N / 2 : N)) return LAZYLLM_EINVAL;
+  const bool use_ws = workspace != nullptr && ws_bytes >= gemm_workspace_bytes();
+  const bool stream_k = forced == 9 || forced == 10 || forced == 16;
+  if (forced != 0 && forced != 2 && forced != 5 && forced != 7 && forced != 15 && !stream_k) return LAZYLLM_EINVAL;
+  if (stream_k && !use_ws) return LAZYLLM_EINVAL;
   if (M == 0) return LAZYLLM_OK;
   EpiArgs ea{};
   ea.w_blocked = blocked ? 1 : 0;
+  if (use_ws) {
+    LZ_HIP(launch_gemm_counters_clear(workspace, (hipStream_t)hip_stream));
+    ea.psk_ready = 1;
+  }
   LZ_HIP(launch_gemm_f8(a_codes, a_scale, w_codes, w_scale, C, R, M, N, K, lda, ldw, ldc, epilogue,
-                        (hipStream_t)hip_stream, &ea));
+                        (hipStream_t)hip_stream, &ea, use_ws ? workspace : nullptr, use_ws ? ws_bytes : 0));
   return LAZYLLM_OK;
+}
+
+int lazyllm_op_gemm_fp8(const void* a_codes, const float* a_scale, const void* w_codes,
+                        const float* w_scale, void* C, const void* R, int32_t M, int32_t N, int32_t K,
+                        int32_t lda, int32_t ldw, int32_t ldc, int32_t epilogue, void* hip_stream) {
+  if (epilogue < 0 || (epilogue & ~(1 << 29)) > 2) return LAZYLLM_EINVAL;
+  return lazyllm_op_gemm_fp8_ws(a_codes, a_scale, w_codes, w_scale, C, R, M, N, K, lda, ldw, ldc, epilogue,
+                                nullptr, 0, hip_stream);
+}
+
+int lazyllm_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t head_dim, int32_t have) {
+  if (M <= 0 || N <= 0 || K <= 0 || N % 128 != 0 || K % 64 != 0 || epilogue < 0 || epilogue > EPI_QKV_ROPE ||
+      (epilogue == EPI_QKV_ROPE && head_dim != 64 && head_dim != 128) || (have & ~3) != 0)
+    return LAZYLLM_EINVAL;
+  const bool fits = (uint64_t)M * (uint64_t)K < (1ull << 31) && (uint64_t)N * (uint64_t)K < (1ull << 31);
+  return gemm_config(M, N, K, epilogue, head_dim, N % 256 == 0 && fits, (have & 1) != 0, (have & 1) != 0, have == 3);
+}
+
+int lazyllm_op_gemm_fp8_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t have) {
+  if (M <= 0 || N <= 0 || K <= 0 || N % 256 != 0 || K % 128 != 0 || epilogue < 0 || epilogue > EPI_QKV_ROPE ||
+      (have & ~1) != 0)
+    return LAZYLLM_EINVAL;
+  return gemm_f8_config(M, N, K, epilogue, true, (have & 1) != 0);
 }
 
 int lazyllm_op_rmsnorm(const void* h, const void* gain, void* x, int32_t rows, int32_t d, float eps,

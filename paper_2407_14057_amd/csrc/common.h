@@ -195,6 +195,10 @@ void set_last_hip_error(int e);
 // sk_ws: optional scratch of gemm_workspace_bytes() for the stream-K variant (fp32 partial tiles).
 size_t gemm_workspace_bytes();
 unsigned* gemm_exchange_flags(void* sk_ws);          // flags of the stream-K schedule of gemm_w4.hip
+// The tile configuration that launch_gemm takes (its forced numbers): what the operands allow, of the four-wave
+// kernel whole tiles and stream-K, 128x128 stream-K, weight streaming.
+int gemm_config(int M, int N, int K, int epilogue, int head_dim, bool w4_ok, bool stream_k_ok, bool split_ok, bool stream_ok);
+int gemm_f8_config(int M, int N, int K, int epilogue, bool w4_ok, bool stream_k_ok);
 hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                        int lda, int ldw, int ldc, int epilogue, hipStream_t st,
                        const EpiArgs* rope = nullptr, void* sk_ws = nullptr, size_t sk_ws_bytes = 0);

@@ -661,6 +661,21 @@ static int choose_tile(int M, int N, int K, int epi, int head_dim, bool w4_ok, b
   return cfg;
 }
 
+int gemm_config(int M, int N, int K, int epilogue, int head_dim, bool w4_ok, bool stream_k_ok, bool split_ok, bool stream_ok) {
+  // few token rows, and the weight at hand in its streaming layout: gemm_stream.hip, up to where
+  // the tile kernels become the better ones (see gemm_stream_takes; row-major, the same kernel is
+  // 20 - 30 % slower).  A weight so wide that
+  // one round of 192- or 256-row tiles keeps five eighths of the CUs is the exception from 289 rows on
+  // (us, streaming / tiles: N 22016, K 4096 at 320 / 384 rows 81 / 78, 448 / 512 rows 94 / 88, 97 / 88;
+  // N 28672 95 / 86, 109 / 102, 110 / 100; N 27648, K 5120 119 / 105, 133 / 126; at 288 rows and below,
+  // and for N 16384, streaming is ahead: 106 / 101, 58 / 71, 56 / 63).
+  const long t256 = (long)((M + 255) / 256) * (N / 256), t192 = (long)((M + 191) / 192) * (N / 256);
+  const bool one_round = w4_ok && N > 20480 && M > 288 && M <= 512 &&
+                         ((t192 >= 160 && t192 <= 256) || (t256 >= 160 && t256 <= 256));
+  if (stream_ok && gemm_stream_takes(M, N, K) && !one_round) return 8;
+  return choose_tile(M, N, K, epilogue, epilogue == EPI_QKV_ROPE ? head_dim : 0, w4_ok, stream_k_ok, split_ok);
+}
+
 hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                        int lda, int ldw, int ldc, int epilogue, hipStream_t st, const EpiArgs* rope,
                        void* sk_ws, size_t sk_ws_bytes) {
@@ -687,22 +702,9 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
   const bool w4_ok = N % 256 == 0 && operands_fit_32bit(M, N, K, lda, ldw, ra.w_blocked != 0) &&
                      rows_in_16_byte_chunks(epilogue, C, R, ldc, ra);
   if (cfg == 0) {
-    // few token rows, and the weight at hand in its streaming layout: gemm_stream.hip, up to where
-    // the tile kernels become the better ones (see gemm_stream_takes; row-major, the same kernel is
-    // 20 - 30 % slower).  Only for callers that keep the workspace's tickets zeroed.  A weight so wide that
-    // one round of 192- or 256-row tiles keeps five eighths of the CUs is the exception from 289 rows on
-    // (us, streaming / tiles: N 22016, K 4096 at 320 / 384 rows 81 / 78, 448 / 512 rows 94 / 88, 97 / 88;
-    // N 28672 95 / 86, 109 / 102, 110 / 100; N 27648, K 5120 119 / 105, 133 / 126; at 288 rows and below,
-    // and for N 16384, streaming is ahead: 106 / 101, 58 / 71, 56 / 63).
-    const long t256 = (long)((M + 255) / 256) * (N / 256), t192 = (long)((M + 191) / 192) * (N / 256);
-    const bool one_round = w4_ok && N > 20480 && M > 288 && M <= 512 &&
-                           ((t192 >= 160 && t192 <= 256) || (t256 >= 160 && t256 <= 256));
-    if ((ra.skinny || ra.psk_ready) && ra.w_stream != nullptr && ws_ok && lda % 8 == 0 &&
-        gemm_stream_takes(M, N, K) && !one_round)
-      cfg = 8;
-    else
-      cfg = choose_tile(M, N, K, epilogue, epilogue == EPI_QKV_ROPE ? ra.head_dim : 0, w4_ok, ws_ok && ra.psk_ready,
-                        ws_ok && ra.a_rows == nullptr);
+    // (streaming: only for callers that keep the workspace's tickets zeroed)
+    const bool stream_ok = (ra.skinny || ra.psk_ready) && ra.w_stream != nullptr && ws_ok && lda % 8 == 0;
+    cfg = gemm_config(M, N, K, epilogue, ra.head_dim, w4_ok, ws_ok && ra.psk_ready, ws_ok && ra.a_rows == nullptr, stream_ok);
   }
   if (ra.w_packed && cfg != 8) return hipErrorInvalidValue;
   if (ra.w_blocked && cfg == 8 && ra.w_stream == nullptr) return hipErrorInvalidValue;

@@ -306,11 +306,34 @@ static const TileCost F8_COST[3] = {
     {8.3, 1.02, 0.90, {7.8, 11.3, 4.4}, 8.1, 2.3, 5.0},
     {9.8, 0.91, 0.87, {1.7, 5.2, 1.6}, 7.5, 1.7, 3.1}};
 
+// Which kernel: by estimated time, as in the 16-bit GEMM.  2: the 128-row tile of this file, one workgroup
+// per CU, ahead while it fits one round and the K loop is short (K 4096, 12288 features: 34 / 37 us at
+// 97 / 512 rows against 35 / 44; K 11008: 75 / 76 against 52 / 45 for stream-K on 128-row four-wave
+// tiles); larger launches take the four-wave kernel (us, 8192 rows, before / now: QKV 422 / 345, O 136 / 121,
+// gate/up 683 / 536, down 316 / 267; 3376 rows 182 / 169, 59 / 58, 282 / 240, 132 / 120).  Its forms have the
+// numbers of the 16-bit GEMM's.
+int gemm_f8_config(int M, int N, int K, int epilogue, bool w4_ok, bool stream_k_ok) {
+  if (!w4_ok) return 2;
+  static const int whole[3] = {5, 7, 15}, cut[3] = {9, 10, 16};
+  const int KT = K / F8_BK;
+  const long t128 = (long)((M + 127) / 128) * (N / 256);
+  double best = t128 <= 256 ? 6.0 + 0.8 * KT + (epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU ? 4.5 : 0.0) : 1e30;
+  int cfg = 2;
+  for (int f = 0; f < 3; ++f)
+    for (int sk = 0; sk <= (stream_k_ok ? 1 : 0); ++sk) {
+      const double t = gemm_w4_cost(F8_COST[f], 256 - 64 * f, sk != 0, M, N, KT, epilogue);
+      if (t < best) { best = t; cfg = sk ? cut[f] : whole[f]; }
+    }
+  return cfg;
+}
+
 hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const float* sw, void* C,
                           const void* R, int M, int N, int K, int lda, int ldw, int ldc, int epilogue,
                           hipStream_t st, const EpiArgs* ea_in, void* sk_ws, size_t sk_ws_bytes) {
   constexpr int BM = 128, BN = 256, LDS_BYTES = 3 * (BM + BN) * ROW_BYTES;
   if (M <= 0) return hipSuccess;
+  int cfg = (epilogue >> 8) & 0xff;                  // forced configuration (measurement hook), 0 = choose here
+  epilogue &= 0xff;
   if (N % BN != 0 || K % F8_BK != 0 || lda % 16 != 0 || ldw % 16 != 0 || lda < K || ldw < K ||
       ((uintptr_t)A & 15) != 0 || ((uintptr_t)W & 15) != 0 || ((uintptr_t)sw & 15) != 0)
     return hipErrorInvalidValue;
@@ -322,28 +345,20 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
     if (ea_in == nullptr || (ea.head_dim != 64 && ea.head_dim != 128) || N != ea.d_model + 2 * kvd)
       return hipErrorInvalidValue;
   }
-  const int tiles_n = N / BN, tiles_m = (M + BM - 1) / BM, KT = K / F8_BK;
-  // Which kernel: by estimated time, as in the 16-bit GEMM.  The 128-row tile of this file, one workgroup
-  // per CU, is ahead while it fits one round and the K loop is short (K 4096, 12288 features: 34 / 37 us at
-  // 97 / 512 rows against 35 / 44; K 11008: 75 / 76 against 52 / 45 for stream-K on 128-row four-wave
-  // tiles); larger launches take the four-wave kernel (us, 8192 rows, before / now: QKV 422 / 345, O 136 / 121,
-  // gate/up 683 / 536, down 316 / 267; 3376 rows 182 / 169, 59 / 58, 282 / 240, 132 / 120).
-  // Outputs that its 16-byte stores cannot address stay here.
-  int rows = 0, stream_k = 0;                        // 0: this file's kernel
-  if (rows_in_16_byte_chunks(epilogue, C, R, ldc, ea)) {
-    const bool sk_ok = ea.psk_ready && sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes();
-    double best = (long)tiles_m * tiles_n <= 256 ? 6.0 + 0.8 * KT + (epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU ? 4.5 : 0.0) : 1e30;
-    for (int f = 0; f < 3; ++f)
-      for (int sk = 0; sk <= (sk_ok ? 1 : 0); ++sk) {
-        const double t = gemm_w4_cost(F8_COST[f], 256 - 64 * f, sk != 0, M, N, KT, epilogue);
-        if (t < best) { best = t; rows = 256 - 64 * f; stream_k = sk; }
-      }
-  }
-  if (rows != 0) {
+  const int tiles_n = N / BN, tiles_m = (M + BM - 1) / BM;
+  // Outputs that the four-wave kernel's 16-byte stores cannot address stay here, forced configuration or not.
+  const bool w4_ok = rows_in_16_byte_chunks(epilogue, C, R, ldc, ea);
+  const bool sk_ok = ea.psk_ready && sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes();
+  if (cfg == 0 || !w4_ok) cfg = gemm_f8_config(M, N, K, epilogue, w4_ok, sk_ok);
+  if (cfg == 5 || cfg == 7 || cfg == 15)
     return launch_gemm_w4_f8(A, sa, W, sw, C, R, M, N, K, lda, ldw, ldc, epilogue, gemm_band_height(M, epilogue), ea,
-                             stream_k, stream_k ? (float*)sk_ws : nullptr,
-                             stream_k ? gemm_exchange_flags(sk_ws) : nullptr, rows, st);
+                             0, nullptr, nullptr, cfg == 7 ? 192 : cfg == 15 ? 128 : 256, st);
+  if (cfg == 9 || cfg == 10 || cfg == 16) {
+    if (!sk_ok) return hipErrorInvalidValue;
+    return launch_gemm_w4_f8(A, sa, W, sw, C, R, M, N, K, lda, ldw, ldc, epilogue, gemm_band_height(M, epilogue), ea,
+                             1, (float*)sk_ws, gemm_exchange_flags(sk_ws), cfg == 10 ? 192 : cfg == 16 ? 128 : 256, st);
   }
+  if (cfg != 2) return hipErrorInvalidValue;
   // K-step-major codes ([K / 128][N][128], see launch_pack_kblock): rows of a step 128 bytes apart
   ea.w_step_bytes = ea.w_blocked ? (unsigned long long)N * ROW_BYTES : (unsigned long long)ROW_BYTES;
   if (ea.w_blocked) ldw = F8_BK;

@@ -131,10 +131,11 @@ def test_gemm_fp8_from_codes(M, N, K, epi):
 @pytest.mark.parametrize("M,N,K", [(2111, 7680, 128), (2200, 7680, 384), (1400, 12288, 256), (4100, 4096, 1408)])
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 def test_gemm_fp8_several_tiles_per_workgroup(M, N, K, epi):
-    """Launches that take the four-wave kernel (persistent workgroups, tiles of 256, 192 or 128 rows, one to
-    three tiles each; K of one, two, three and eleven steps; ragged last tile rows), and their first rows alone
-    in a launch of few tiles: every element against the definition; K-step-major weight codes give the bits of
-    row-major ones; nothing is written past the last row."""
+    """Launches for which the library chooses the four-wave kernel (tiles of 128 rows, in the last shape 192 for
+    SiLU * mul; one to three a workgroup; K of one, two, three and eleven steps; ragged last tile rows), and
+    their first rows alone in a launch of few tiles: every element against the definition; K-step-major weight
+    codes give the bits of row-major ones; nothing is written past the last row."""
+    assert B.lib().lazyllm_op_gemm_fp8_plan(M, N, K, epi, 0) in (7, 15)
     rng = np.random.default_rng(M * 5 + N + K + epi)
     ac, sa = F.quantize_rows(rng.normal(0, 1, (M, K)).astype(np.float32))
     wc, sw = F.quantize_rows(rng.normal(0, 1 / math.sqrt(K), (N, K)).astype(np.float32))
@@ -169,6 +170,57 @@ def test_gemm_fp8_several_tiles_per_workgroup(M, N, K, epi):
     for got in (whole, torch.cat([run(slice(0, 100), w_d, 0), whole[100:]])):
         err = np.abs(_f32(got).astype(np.float64) - ref)
         assert not (err > tol).any(), "%d of %d off, worst %.3g" % (int((err > tol).sum()), err.size, float(err.max()))
+
+
+@pytest.mark.parametrize("M,N,K", [(2111, 7680, 128), (2200, 7680, 384), (1400, 12288, 256), (4100, 4096, 1408), (300, 256, 640),
+                                   (48, 768, 1408), (1, 256, 128)])
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
+def test_gemm_fp8_every_form(M, N, K, epi):
+    """Every form of the four-wave kernel on 8-bit codes, forced: tiles of 256, 192 and 128 rows, whole and with the
+    K steps of the last round shared out (stream-K); one to five tiles a workgroup, tiles cut into up to 32 pieces;
+    K of one, two, three, five and eleven steps; ragged last tile rows with idle waves.  Every element against
+    the definition, the same bits twice and from K-step-major codes, the flags back at zero, nothing written past
+    the last row.  Whole tiles of all heights have the same bits, stored as they are those of the 8-wave kernel
+    (with a residual, scaling and addition are one rounding in one of the two kernels and two in the other)."""
+    rng = np.random.default_rng(M * 3 + N + K + epi)
+    ac, sa = F.quantize_rows(rng.normal(0, 1, (M, K)).astype(np.float32))
+    wc, sw = F.quantize_rows(rng.normal(0, 1 / math.sqrt(K), (N, K)).astype(np.float32))
+    a_d, w_d, sa_d, sw_d = (torch.from_numpy(t).to(DEV) for t in (ac, wc, sa, sw))
+    wb = torch.empty_like(w_d)
+    B.lazyllm_op_pack_weight_ksteps(w_d, N, K // 2, K // 2, wb)
+    R = _bf16_dev(rng.normal(0, 1, (M, N)))
+    ncols = N // 2 if epi == B.EPI_SWIGLU else N
+    ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
+
+    def run(cfg, w=w_d, flag=0):
+        guard = torch.full((M + 1, ncols), 7.0, dtype=torch.bfloat16, device=DEV)
+        Cout = guard[:-1]
+        if epi == B.EPI_RESIDUAL:
+            Cout.copy_(R)
+        B.lazyllm_op_gemm_fp8(a_d, sa_d, w, sw_d, Cout, Cout if epi == B.EPI_RESIDUAL else None, M, N, K, K, K, ncols,
+                              epi | (cfg << 8) | flag, workspace=ws)
+        torch.cuda.synchronize()
+        assert bool((guard[-1] == 7.0).all()), cfg
+        assert int(ws[-4096:].view(torch.int32).abs().sum()) == 0, cfg
+        return Cout
+
+    acc = F.gemm_fp8(ac, sa, wc, sw)
+    mag = F.gemm_fp8(ac & 0x7F, sa, wc & 0x7F, sw)
+    if epi == B.EPI_SWIGLU:
+        blocks = acc.reshape(M, N // 64, 2, 32)
+        ref = (O.silu(blocks[:, :, 0, :]) * blocks[:, :, 1, :]).reshape(M, N // 2)
+    else:
+        ref = acc + (_f32(R).astype(np.float64) if epi == B.EPI_RESIDUAL else 0.0)
+    # tolerance as above
+    tol = 2.0 ** -8 * np.abs(ref) + (3e-5 * mag if epi != B.EPI_SWIGLU else 4e-4) + 1e-30
+    whole = run(5)
+    assert torch.equal(whole, run(7)) and torch.equal(whole, run(15))
+    assert epi != B.EPI_STORE or torch.equal(whole, run(2))
+    for cfg in (2, 5, 9, 10, 16):
+        got = run(cfg)
+        err = np.abs(_f32(got).astype(np.float64) - ref)
+        assert not (err > tol).any(), "%d: %d of %d off, worst %.3g" % (cfg, int((err > tol).sum()), err.size, float(err.max()))
+        assert torch.equal(got, run(cfg, wb, 1 << 29)), cfg
 
 
 @pytest.mark.parametrize("M,N,K", [(37, 256, 384), (300, 768, 1024), (2100, 768, 256)])

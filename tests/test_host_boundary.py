@@ -295,3 +295,22 @@ def test_attention_form_counts_the_whole_batch():
     assert block(512, 1, 4, 64) == 32 and block(3376, 1, 32, 128) == 256 and block(844, 1, 32, 128) == 128
     for bad in ((0, 1, 4, 64), (8, 0, 4, 64), (8, 1, 0, 64), (8, 1, 4, 96)):
         assert block(*bad) == B.LAZYLLM_EINVAL
+
+
+def test_forced_8bit_configurations_that_do_not_fit_are_refused_before_the_device_is_touched():
+    call = B.lib().lazyllm_op_gemm_fp8_ws
+    big = 1 << 30
+    args = (16, 16, 16, 16, 16, None, 64, 256, 128, 128, 128, 256)
+    for cfg in (1, 3, 4, 6, 8, 11, 14, 17, 255):
+        assert call(*args, cfg << 8, 256, big, None) == B.LAZYLLM_EINVAL, cfg
+    for cfg in (9, 10, 16):                                  # stream-K without a (large enough) workspace
+        assert call(*args, cfg << 8, None, 0, None) == B.LAZYLLM_EINVAL
+        assert call(*args, cfg << 8, 256, 4096, None) == B.LAZYLLM_EINVAL
+    assert call(*args, 0, 128, big, None) == B.LAZYLLM_EINVAL        # workspace not on a 256-byte boundary
+    # the entry point without a workspace takes no configuration
+    for cfg in (2, 5, 9):
+        assert B.lib().lazyllm_op_gemm_fp8(*args, cfg << 8, None) == B.LAZYLLM_EINVAL
+    for plan, bad in ((B.lib().lazyllm_op_gemm_fp8_plan, (8, 128, 128, 0, 0)), (B.lib().lazyllm_op_gemm_fp8_plan, (8, 256, 64, 0, 0)),
+                      (B.lib().lazyllm_op_gemm_fp8_plan, (0, 256, 128, 0, 0)), (B.lib().lazyllm_op_gemm_plan, (8, 64, 64, 0, 0, 0)),
+                      (B.lib().lazyllm_op_gemm_plan, (8, 128, 64, 3, 96, 0)), (B.lib().lazyllm_op_gemm_plan, (8, 128, 64, 0, 0, 4))):
+        assert plan(*bad) == B.LAZYLLM_EINVAL
