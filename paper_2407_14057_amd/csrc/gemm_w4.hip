@@ -58,6 +58,8 @@ constexpr unsigned W4_SPIN_LIMIT = 1u << 22;       // about a second of polling
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef int v8i_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
+typedef u16x8_t u16x8_at_2_t __attribute__((aligned(2)));
 constexpr int W4_SLOT = 256 * ROW_BYTES;
 
 // The accumulators live in the accumulation registers a0 .. a255 by name: block (i, j) of a wave is
@@ -517,47 +519,8 @@ gemm_w4_kernel(const char* __restrict__ A, const char* __restrict__ W, const flo
           put((q + HQ) * 16 + feat, make_uint2(pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])));
         }
       } else if constexpr (ROPE) {
-        // V goes to the KV cache row-major and, for the attention kernel's second product, transposed.
-        // Neighbouring lanes hold neighbouring tokens: lane pairs swap one value each so that an even
-        // lane writes tokens (t, t+1) of one feature and the odd lane (t-1, t) of the next feature, 4
-        // bytes per lane.  Needs the even lane's column to be even and both tokens to be in the same
-        // sequence and below M; otherwise 2-byte stores.
-        uint16_t* vtp = nullptr;
-        int vcol = 0;
-        if (ra.vt != nullptr && valid) {
-          vcol = ra.vt_col != nullptr ? ra.vt_col[row] : row;
-          vtp = ra.vt + (size_t)(rcol0 + feat) * ra.vt_ld + vcol;
-        }
-        const int partner_col = __shfl_xor(vtp != nullptr ? vcol : -7, 1, 64);
-        const bool odd = el & 1;
-        const bool paired = vtp != nullptr && partner_col == (odd ? vcol - 1 : vcol + 1) &&
-                            (((odd ? vcol - 1 : vcol) & 1) == 0);
 #pragma unroll
-        for (int q = 0; q < TN; ++q) {
-          const uint2 w2 = make_uint2(pack_bf16(x[q][0], x[q][1]), pack_bf16(x[q][2], x[q][3]));
-          put(q * 16 + feat, w2);
-          // features f0..f3 of this token: w2.x = (f0, f1), w2.y = (f2, f3)
-          // even lane sends (f1, f3), receives partner's (f0, f2); odd lane the other way
-          const uint32_t mine_lo = (w2.x & 0xffff) | (w2.y << 16);        // (f0, f2)
-          const uint32_t mine_hi = (w2.x >> 16) | (w2.y & 0xffff0000u);   // (f1, f3)
-          const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? mine_lo : mine_hi),
-                                                                  0xB1, 0xf, 0xf, true);
-          if (paired) {
-            // even lane: features f0, f2 of tokens (t, t+1); odd lane: f1, f3 of (t-1, t)
-            uint16_t* f0 = vtp + (size_t)(16 * q + (odd ? 1 : 0)) * ra.vt_ld - (odd ? 1 : 0);
-            const uint32_t own = odd ? mine_hi : mine_lo;
-            const uint32_t a = odd ? ((got & 0xffff) | (own << 16)) : ((own & 0xffff) | (got << 16));
-            const uint32_t c = odd ? ((got >> 16) | (own & 0xffff0000u)) : ((own >> 16) | (got & 0xffff0000u));
-            *(uint32_t*)f0 = a;
-            *(uint32_t*)(f0 + 2 * (size_t)ra.vt_ld) = c;
-          } else if (vtp != nullptr) {
-            uint16_t* f0 = vtp + (size_t)(16 * q) * ra.vt_ld;
-            f0[0] = (uint16_t)(w2.x & 0xffff);
-            f0[(size_t)ra.vt_ld] = (uint16_t)(w2.x >> 16);
-            f0[2 * (size_t)ra.vt_ld] = (uint16_t)(w2.y & 0xffff);
-            f0[3 * (size_t)ra.vt_ld] = (uint16_t)(w2.y >> 16);
-          }
-        }
+        for (int q = 0; q < TN; ++q) put(q * 16 + feat, make_uint2(pack_bf16(x[q][0], x[q][1]), pack_bf16(x[q][2], x[q][3])));
       } else if constexpr (EPI == EPI_SWIGLU) {
 #pragma unroll
         for (int q = 0; q < TN; ++q) {
@@ -619,6 +582,37 @@ gemm_w4_kernel(const char* __restrict__ A, const char* __restrict__ W, const flo
           if (orow < M) {
             const size_t dr = (ROPE && region == 1 && ra.k_row != nullptr) ? (size_t)ra.k_row[orow] : (size_t)orow;
             *(uint4*)(obase + dr * old + schunk * 8) = v;
+          }
+        }
+      }
+      if constexpr (ROPE && VPART) {
+        if (ra.vt != nullptr) {
+          // V once more, transposed, for the attention kernel's second product: from the stage a lane
+          // takes eight tokens of one feature.  Where the block's 16 tokens have 16 consecutive columns
+          // they leave in one store of 16 bytes (on a 2-byte boundary in packed sequences: global memory
+          // takes it), else one by one.  The loop is rolled on purpose: written out per block of
+          // columns, with both cases, it was 20 KB of code that did little but wait for the instruction
+          // cache (64 KB for two CUs, the kernel 89 KB; now 70).  With 4-byte stores straight from the
+          // accumulators / so, us: 8192 x 12288 x 4096 626 / 605, 3376 rows 298 / 290, 5000 x 3072 x 1024 45 / 41.
+          const int vcol = valid ? (ra.vt_col != nullptr ? ra.vt_col[row] : row) : -1;
+          const int vcol0 = __builtin_amdgcn_readfirstlane(vcol);
+          const bool whole = __builtin_amdgcn_ballot_w64(vcol != vcol0 + tok) == 0;      // (and every row is below M)
+          LZ_LDS_ORDER();
+#pragma unroll 1
+          for (int s = 0; s < 4; ++s) {
+            const int f = s * 32 + (el >> 1), t0 = (el & 1) * 8;
+            u16x8_t v;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = *(const uint16_t*)(sl + stage_at(t0 + e, f & ~3) + (f & 3) * 2);
+            uint16_t* const vr = ra.vt + (size_t)(rcol0 + f) * ra.vt_ld;
+            if (whole) *(u16x8_at_2_t*)(vr + vcol0 + t0) = v;
+            else
+#pragma unroll 1
+              for (int e = 0; e < 8; ++e) {
+                const int r = row0 + i * 16 + t0 + e;
+                const uint16_t one = *(const uint16_t*)(sl + stage_at(t0 + e, f & ~3) + (f & 3) * 2);
+                if (r < M) vr[ra.vt_col != nullptr ? ra.vt_col[r] : r] = one;
+              }
           }
         }
       }

@@ -322,6 +322,27 @@ def test_few_rows_of_a_packed_batch(few_rows_heads):
                               verbose="few rows packed H=%d hd=%d seq %d" % (shape.n_heads, shape.head_dim, b))
 
 
+@pytest.mark.parametrize("heads,hd", [(8, 128), (16, 64)])
+def test_packed_batch_on_the_four_wave_qkv_tiles(heads, hd):
+    """The QKV epilogue of the large tiles on packed prompts: blocks of 16 rows whose transposed V columns follow on
+    from a multiple of 8 (the first sequence), from elsewhere (the others), across the end of a sequence, and the
+    ragged end of the last tile.  The second layer's K and scores depend on what the first layer's attention read."""
+    shape = synth.ModelShape(2, 1024, heads, hd, 1024, 512)
+    w = synth.make_weights(shape, 1051 + hd, "cpu", gain_jitter=0.3)
+    model = B.Model(shape.as_dict(), _to_dev(w), DEV)
+    wb = synth.weights_to_host_bits(w)
+    lens, sched = [1001, 37, 1502, 900, 1, 758], [(1, 900)]
+    assert B.lib().lazyllm_op_gemm_plan(sum(lens), 3072, 1024, 3, hd, 3) in (5, 7, 15, 9, 10, 16)
+    ids = np.concatenate([synth.make_prompt(n, shape.vocab, 760 + i) for i, n in enumerate(lens)])
+    cu = [int(x) for x in np.concatenate([[0], np.cumsum(lens)])]
+    out = _run(model, ids, sched, cu=cu)
+    assert out.status == 0
+    for b in range(len(lens)):
+        check_against_checker(shape, wb, ids[cu[b]:cu[b + 1]], sched, out, seq=b, tol=FEW_ROWS_TOL,
+                              verbose="packed, four-wave H=%d seq %d" % (heads, b))
+    model.close()
+
+
 def test_few_rows_folded_compaction_gives_the_same_bits(few_rows_model):
     """Row indirection of the A operand and of the residual in the streaming kernel, 300 -> 90 rows."""
     shape, _, model = few_rows_model
