@@ -597,10 +597,10 @@ int gemm_band_height(int M, int epilogue) {
   return epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU ? (tm256 < 8 ? tm256 : tall) : 4;
 }
 
-// ---- which tile.  Every form's time is estimated, in microseconds, from what its tiles cost (measured at
-// 640 - 8192 rows of eleven projections with K of 768 to 14336 and N of 768 to 28672, cold weights) and
-// the smallest estimate is taken.  Against the best form of each of those 380 cases the choice costs
-// 0.6 % on average, the same cases before this rule and the four-wave kernel took 13 % longer.
+// ---- which tile.  Every form's time is estimated, in microseconds, from what its tiles cost and the smallest
+// estimate is taken.  The constants are those that lose least by the choice on 409 shapes of sixteen models
+// (K 256 to 18944, N 256 to 57344, up to 16384 rows, cold weights): 0.7 % behind
+// the best on average, and on 227 further shapes that took no part 0.6 %, at most 12 %.
 //   * a launch: a fixed cost;
 //   * a K step (64 elements) of a round of tiles, one per CU: under the power limit a chip that is
 //     less than about 0.6 full runs at a higher clock (256 rows: 1.02 us a step alone, 1.37 on all CUs);
@@ -608,10 +608,15 @@ int gemm_band_height(int M, int epilogue) {
 //   * stream-K: the whole rounds, then the remaining tiles' steps shared out evenly; the exchange costs a
 //     fixed part, a part for every piece the owner of a tile adds, and more when the pieces do not
 //     align with tiles (a workgroup then has two pieces), the fewer tiles the more.
+// Slower than the eight-wave tiles that stood here before: launches of about one round with K up to 1024,
+// where the end of a tile on one wave per SIMD is not hidden (QKV 6384 x 2304 x 768 32 / 35 us, 9395 x 1536 x 512
+// 27 / 29, 4188 x 3072 x 1024 35 / 38; residual 13264 x 1024 x 1024 36 / 39).
 static const TileCost W4_COST[3] = {                // 256, 192, 128 rows; end: residual or none, rotary, SiLU * mul
-    {5.75, 1.37, 1.02, {13.1, 19.4, 4.8}, 10.9, 2.6, 15.9},
-    {4.5, 1.11, 0.94, {5.9, 14.8, 6.1}, 12.4, 2.0, 24.2},
-    {7.2, 0.94, 0.91, {1.5, 5.0, 9.2}, 9.7, 1.5, 7.4}};
+    {6.47, 1.22, 1.10, {12.41, 13.15, 5.99}, 11.25, 3.55, 20.43},
+    {4.58, 1.03, 0.99, {6.40, 8.88, 5.50}, 9.80, 3.21, 19.60},
+    {4.83, 0.94, 0.94, {1.49, 4.26, 2.97}, 8.17, 2.54, 7.71}};
+// 128x256 with three stages, one workgroup per CU (the rotary epilogue with 128-wide heads)
+static const TileCost THREE_STAGES = {-1.75, 1.03, 0.93, {0.0, 8.12, 0.0}, 0.0, 0.0, 0.0};
 
 double gemm_w4_cost(const TileCost& c, int rows, bool stream_k, int M, int N, int KT, int epi) {
   const long T = (long)((M + rows - 1) / rows) * (N / 256);
@@ -643,15 +648,14 @@ static int choose_tile(int M, int N, int K, int epi, int head_dim, bool w4_ok, b
   // epilogue with 128-wide heads must hold whole heads, so that tile is then cut into 32x128 waves.
   const long rounds = t128 / 512, left = t128 % 512;
   int cfg = epi == EPI_QKV_ROPE && head_dim == 128 ? 3 : 2;
-  double best = 1.7 + KT * ((double)rounds * 1.244 + (left == 0 ? 0.0 : left <= 256 ? 0.785 : 1.244)) +
-                3.4 * (double)(rounds + (left > 0));
+  double best = 1.5 + KT * ((double)rounds * 1.28 + (left == 0 ? 0.0 : left <= 256 ? 0.79 : 1.28)) +
+                (epi == EPI_QKV_ROPE ? 3.62 : epi == EPI_SWIGLU ? 3.77 : 2.71) * (double)(rounds + (left > 0));
   auto consider = [&](int c, double t) { if (t < best) { best = t; cfg = c; } };
-  // 128x256 with three stages, one workgroup per CU, for those heads
   if (epi == EPI_QKV_ROPE && head_dim == 128 && N % 256 == 0)
-    consider(13, -1.6 + (double)(((M + 127) / 128 * (long)(N / 256) + 255) / 256) * (KT * 0.941 + 12.3));
+    consider(13, gemm_w4_cost(THREE_STAGES, 128, false, M, N, KT, epi));
   // stream-K on 128x128 tiles with a second kernel that adds the pieces: few tiles and a long K
   if ((epi == EPI_STORE || epi == EPI_RESIDUAL) && split_ok && KT >= 32 && t128 <= 320)
-    consider(6, 21.0 + 1.41 * (double)t128 * KT / 512.0);
+    consider(6, 19.7 + 1.34 * (double)t128 * KT / 512.0);
   if (w4_ok) {
     static const int whole[3] = {5, 7, 15}, cut[3] = {9, 10, 16};
     for (int f = 0; f < 3; ++f) consider(whole[f], gemm_w4_cost(W4_COST[f], 256 - 64 * f, false, M, N, KT, epi));

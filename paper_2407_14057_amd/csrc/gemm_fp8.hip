@@ -299,12 +299,13 @@ gemm_f8_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ W,
   staged_tile_out<TM, TN, EPI, BM, BN, NWAVES>(acc, C, R, M, ldc, m0, n0, wm, wn, wave, lane, ra, nullptr, lds);
 }
 
-// Costs of the four-wave kernel's forms on 8-bit operands (see TileCost; a K step is 128 elements), fitted to
-// the four projections of the 4096 / 11008-wide layer at 97 - 8192 rows; end: residual or none, rotary, SiLU * mul.
+// Costs of the four-wave kernel's forms on 8-bit operands (see TileCost; a K step is 128 elements): those that lose
+// least by the choice on 288 shapes of ten models (16 - 8192 rows), 0.3 % behind the best form on average; on 168
+// further shapes 0.4 %.  end: residual or none, rotary, SiLU * mul.
 static const TileCost F8_COST[3] = {
-    {6.4, 1.26, 0.96, {14.9, 17.0, 7.5}, 9.0, 2.5, 2.5},
-    {8.3, 1.02, 0.90, {7.8, 11.3, 4.4}, 8.1, 2.3, 5.0},
-    {9.8, 0.91, 0.87, {1.7, 5.2, 1.6}, 7.5, 1.7, 3.1}};
+    {7.73, 1.18, 0.98, {10.29, 14.09, 5.39}, 14.89, 4.16, 2.99},
+    {4.33, 1.00, 0.89, {5.88, 11.85, 6.00}, 9.02, 3.52, 6.13},
+    {9.00, 0.95, 0.87, {1.37, 5.96, 1.99}, 4.26, 2.36, 2.87}};
 
 // Which kernel: by estimated time, as in the 16-bit GEMM.  2: the 128-row tile of this file, one workgroup
 // per CU, ahead while it fits one round and the K loop is short (K 4096, 12288 features: 34 / 37 us at
@@ -317,7 +318,7 @@ int gemm_f8_config(int M, int N, int K, int epilogue, bool w4_ok, bool stream_k_
   static const int whole[3] = {5, 7, 15}, cut[3] = {9, 10, 16};
   const int KT = K / F8_BK;
   const long t128 = (long)((M + 127) / 128) * (N / 256);
-  double best = t128 <= 256 ? 6.0 + 0.8 * KT + (epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU ? 4.5 : 0.0) : 1e30;
+  double best = t128 > 256 ? 1e30 : 3.13 + 0.78 * KT + (epilogue == EPI_QKV_ROPE ? 3.58 : epilogue == EPI_SWIGLU ? 1.44 : 0.39);
   int cfg = 2;
   for (int f = 0; f < 3; ++f)
     for (int sk = 0; sk <= (stream_k_ok ? 1 : 0); ++sk) {

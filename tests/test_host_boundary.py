@@ -314,3 +314,26 @@ def test_forced_8bit_configurations_that_do_not_fit_are_refused_before_the_devic
                       (B.lib().lazyllm_op_gemm_fp8_plan, (0, 256, 128, 0, 0)), (B.lib().lazyllm_op_gemm_plan, (8, 64, 64, 0, 0, 0)),
                       (B.lib().lazyllm_op_gemm_plan, (8, 128, 64, 3, 96, 0)), (B.lib().lazyllm_op_gemm_plan, (8, 128, 64, 0, 0, 4))):
         assert plan(*bad) == B.LAZYLLM_EINVAL
+
+
+def test_tile_choice_at_shapes_where_an_estimate_was_off():
+    """Shapes at which the estimated times once picked a form 8 to 23 % behind the best: one of the forms measured
+    within 3 % of the best must be chosen (16-bit with a workspace, 8-bit likewise)."""
+    for (M, N, K, epi, hd), good in {
+            (1182, 6144, 4096, 3, 128): (15,), (6384, 2304, 768, 3, 64): (5,), (12288, 2304, 768, 3, 64): (5,),
+            (703, 8192, 1536, 2, 64): (2, 15), (645, 2560, 6912, 1, 128): (6,), (704, 22016, 4096, 2, 128): (10,),
+            (768, 22016, 4096, 2, 128): (10,), (991, 22016, 4096, 2, 128): (9,)}.items():
+        assert B.lib().lazyllm_op_gemm_plan(M, N, K, epi, hd, 1) in good, (M, N, K, epi)
+    for (M, N, K, epi), good in {
+            (86, 16384, 3072, 2): (2,), (186, 32768, 6144, 2): (2,), (26, 27648, 5120, 2): (2,), (45, 12288, 4096, 3): (2,),
+            (281, 2048, 5504, 1): (2, 15), (613, 22016, 4096, 2): (2,)}.items():
+        assert B.lib().lazyllm_op_gemm_fp8_plan(M, N, K, epi, 1) in good, (M, N, K, epi)
+
+
+def test_small_models_do_not_split_k_over_workgroups():
+    """A model 256 wide: no tile of any row count adds its sums in pieces, so that a packed prompt's projections
+    have the bits of the prompt alone."""
+    for N, K, epi in ((768, 256, 3), (256, 256, 1), (1536, 256, 2), (256, 768, 1)):
+        for M in list(range(1, 400)) + list(range(400, 16385, 61)):
+            assert B.lib().lazyllm_op_gemm_plan(M, N, K, epi, 64, 3) not in (6, 9, 10, 16), (M, N, K)
+            assert B.lib().lazyllm_op_gemm_fp8_plan(M, N, K, epi, 1) not in (9, 10, 16), (M, N, K)
