@@ -326,7 +326,7 @@ def test_tile_choice_at_shapes_where_an_estimate_was_off():
         assert B.lib().lazyllm_op_gemm_plan(M, N, K, epi, hd, 1) in good, (M, N, K, epi)
     for (M, N, K, epi), good in {
             (86, 16384, 3072, 2): (2,), (186, 32768, 6144, 2): (2,), (26, 27648, 5120, 2): (2,), (45, 12288, 4096, 3): (2,),
-            (281, 2048, 5504, 1): (2, 15), (613, 22016, 4096, 2): (2,)}.items():
+            (281, 2048, 5504, 1): (2, 15)}.items():
         assert B.lib().lazyllm_op_gemm_fp8_plan(M, N, K, epi, 1) in good, (M, N, K, epi)
 
 
