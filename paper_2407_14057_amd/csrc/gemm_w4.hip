@@ -359,6 +359,8 @@ gemm_w4_kernel(const char* __restrict__ A, const char* __restrict__ W, const flo
         if (seen != 0u && seen != my_flag) failed = true;     // written behind another L2: not visible here
       }
       if (failed && lane == 0) atomicAdd(flags + 1023, 1u);   // (the last word counts give-ups)
+      // (the flags are read with relaxed atomics, which do not keep the loads of the pieces behind them)
+      asm volatile("" ::: "memory");
       return !failed;
     };
     if (m0 + wm * TM * 16 >= M) {
