@@ -194,7 +194,7 @@ void set_last_hip_error(int e);
 
 // sk_ws: optional scratch of gemm_workspace_bytes() for the stream-K variant (fp32 partial tiles).
 size_t gemm_workspace_bytes();
-unsigned* gemm_exchange_flags(void* sk_ws);          // flags of the stream-K schedule of gemm_w4.hip
+unsigned* gemm_exchange_flags(void* sk_ws);          // flags of the stream-K schedule of gemm_w4.h
 // The tile configuration that launch_gemm takes (its forced numbers): what the operands allow, of the four-wave
 // kernel whole tiles and stream-K, 128x128 stream-K, weight streaming.
 int gemm_config(int M, int N, int K, int epilogue, int head_dim, bool w4_ok, bool stream_k_ok, bool split_ok, bool stream_ok);
@@ -208,7 +208,7 @@ inline bool rows_in_16_byte_chunks(int epilogue, const void* C, const void* R, i
   if (epilogue == EPI_QKV_ROPE) return (((uintptr_t)ra.q | (uintptr_t)ra.k | (uintptr_t)ra.v) & 15) == 0;
   return ldc % 8 == 0 && (((uintptr_t)C | (uintptr_t)R) & 15) == 0;
 }
-// The 256x256 tile on four waves of 128x128, one per SIMD (gemm_w4.hip); N % 256 == 0.  stream_k: with
+// The 256x256 tile on four waves of 128x128, one per SIMD (gemm_w4.h); N % 256 == 0.  stream_k: with
 // the K steps of the last round's tiles shared out (part, flags: see there).
 hipError_t launch_gemm_w4(const void* A, const void* W, void* C, const void* R, int M, int N, int K,
                           int lda, int ldw, int ldc, int epi, int group_m, const EpiArgs& ra,

@@ -21,7 +21,7 @@ namespace lz {
 
 // Workspace of the forms that exchange partial sums between workgroups.  Layout: fp32 partial tiles
 // (64 MB) | 4 KB of tickets of the weight-streaming kernel (gemm_stream.hip) | 4 KB of flags of the
-// four-wave kernel's stream-K schedule (gemm_w4.hip; word 1023 counts its give-ups).  Tickets and
+// four-wave kernel's stream-K schedule (gemm_w4.h; word 1023 counts its give-ups).  Tickets and
 // flags must be zero before the first launch that uses them; every launch leaves them zero again.
 constexpr int SK_GRID = 512;
 constexpr size_t SK_PART_BYTES = (size_t)SK_GRID * 2 * 128 * 128 * sizeof(float);

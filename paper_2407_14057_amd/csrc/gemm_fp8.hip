@@ -75,7 +75,7 @@ hipError_t launch_quantize_rows_f8(const void* x, int rows, int K, int ldx, void
 }
 
 // ------------------------------------------------------------------------------------------
-// Tile kernel for launches of few tiles (larger ones take the four-wave kernel of gemm_w4.hip): 128 x
+// Tile kernel for launches of few tiles (larger ones take the four-wave kernel of gemm_w4.h): 128 x
 // 256 tile on 8 waves of 32 x 128, 128 K elements (= 128 bytes per operand row, the same LDS geometry as
 // the 16-bit kernels) per step, three LDS stages filled by global -> LDS copies.  The two waves of a
 // SIMD run half a step apart, one in a phase of 4 back-to-back MFMAs (64 cycles each) with the copies

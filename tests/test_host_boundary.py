@@ -337,3 +337,38 @@ def test_small_models_do_not_split_k_over_workgroups():
         for M in list(range(1, 400)) + list(range(400, 16385, 61)):
             assert B.lib().lazyllm_op_gemm_plan(M, N, K, epi, 64, 3) not in (6, 9, 10, 16), (M, N, K)
             assert B.lib().lazyllm_op_gemm_fp8_plan(M, N, K, epi, 1) not in (9, 10, 16), (M, N, K)
+
+
+_CLEAN_ASM = """kernel:
+\tds_read_b128 v[0:3], v40
+\ts_waitcnt lgkmcnt(0)
+\t;;#ASMSTART
+\tv_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[8:11], a[0:3]
+\t;;#ASMEND
+\t;;#ASMSTART
+\tv_accvgpr_read_b32 v5, a7
+\t;;#ASMEND
+\tv_add_f32_e32 v6, v5, v4
+\ts_endpgm
+    .private_segment_fixed_size: 0
+    .vgpr_spill_count: 0
+"""
+
+
+@pytest.mark.parametrize("ahead,what", [
+    ("v_accvgpr_write_b32 a7, v4", "accumulation register"), ("v_add_f32_e32 v30, a[3:4], v2", "accumulation register"), ("v_add_f32_e32 v30, a3, v2", "accumulation register"),
+    ("ds_read_b128 a[12:15], v40", "accumulation register"), ("global_store_dwordx4 v[20:21], a[0:3], off", "accumulation register"),
+    ("v_mov_b32_e32 v9, v4", "0 wait states"), ("v_mov_b32_e32 v9, v4\n\ts_nop 0", "1 wait states"), ("v_mov_b32_e32 v9, v4\n\ts_nop 1", None),
+    ("v_pk_mul_f32 v[2:3], v[2:3], v[4:5]\n\tv_mov_b32_e32 v30, v4", "1 wait states"), ("v_mov_b32_e32 v12, v0", None),
+    ("v_cmp_gt_f32_e32 vcc, v0, v8", None), ("ds_read_b128 v[0:3], v40", None), ("s_mov_b32 s0, s1", None),
+    ("    .vgpr_spill_count: 2", "vgpr_spill_count"), ("    .private_segment_fixed_size: 16", "private_segment")])
+def test_build_looks_for_what_could_corrupt_named_accumulators(ahead, what):
+    """The check that the build runs on the assembly of the kernels whose accumulators are named registers."""
+    from paper_2407_14057_amd.build import accumulator_faults
+    assert accumulator_faults(_CLEAN_ASM) == []
+    at = _CLEAN_ASM.index("\t;;#ASMSTART")
+    faults = accumulator_faults(_CLEAN_ASM[:at] + ("" if ahead.startswith(" ") else "\t") + ahead + "\n" + _CLEAN_ASM[at:])
+    if what is None:
+        assert faults == [], faults
+    else:
+        assert len(faults) == 1 and what in faults[0], faults
