@@ -388,6 +388,21 @@ def test_tiny_fp8_shapes_and_schedules(tiny8, n, sched):
     check_against_checker(shape, wb, ids, sched, out, verbose="fp8 n=%d %s" % (n, sched), gemm8=True, tol=TOL8)
 
 
+@pytest.mark.parametrize("n,cfg", [(1400, 7), (2000, 5), (2600, 15)])
+def test_fp8_qkv_projection_on_the_four_wave_tiles(n, cfg):
+    """The rotary epilogue of the 8-bit four-wave tile in its three heights, 2048 wide: every K and V of a layer,
+    and through its attention q and transposed V."""
+    shape = synth.ModelShape(1, 2048, 16, 128, 256, 256, gemm_dtype=1)
+    assert B.lib().lazyllm_op_gemm_fp8_plan(n, 3 * 2048, 2048, 3, 1) == cfg
+    w = synth.make_weights(shape, 1071 + cfg, "cpu", gain_jitter=0.3)
+    model = B.Model(shape.as_dict(), _to_dev(w), DEV)
+    ids = synth.make_prompt(n, shape.vocab, 780 + cfg)
+    out = _run(model, ids, [])
+    assert out.status == 0
+    check_against_checker(shape, synth.weights_to_host_bits(w), ids, [], out, verbose="fp8 QKV, %d" % cfg, gemm8=True, tol=TOL8)
+    model.close()
+
+
 def test_fp8_runs_are_bit_identical_and_batches_are_independent(tiny8):
     shape, wb, model = tiny8
     lens = [130, 512, 77]

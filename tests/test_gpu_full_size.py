@@ -171,8 +171,8 @@ def test_headline_3376(model7b):
     assert torch.equal(snap[0], out2.logits) and torch.equal(snap[1], out2.kept_pos(31))
     assert torch.equal(snap[2], out2.k(31))
     # ... and so does the form that reads the kept rows of layers 8 / 16 / 24 through the index
-    # instead of compacting them (2364, 1182 and 355 rows: the ping-pong, persistent stream-K,
-    # three-stage and 128x128 stream-K kernels each take an indirect operand or residual there)
+    # instead of compacting them (2364, 1182 and 355 rows: four-wave tiles, whole and stream-K, and the
+    # streaming kernel each take an indirect operand or residual there)
     snap = snap + tuple(out2.v(l).clone() for l in (8, 16, 24)) + tuple(out2.aux_h(l).clone() for l in (8, 16, 24)) + \
         tuple(out2.scores(l).clone() for l in (8, 23, 31))
     _, out3 = _run(model, wl, flags=B.LAZYLLM_FUSE_COMPACTION)

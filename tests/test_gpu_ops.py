@@ -103,12 +103,11 @@ def test_gemm_skinny(M, N, K, epi):
 @pytest.mark.parametrize("cfg,M,N,K", [(5, 1100, 22016, 192), (5, 2100, 22016, 64), (5, 1300, 16384, 128),
                                        (7, 1100, 22016, 192), (7, 1000, 16384, 64), (7, 2100, 22016, 256)])
 def test_gemm_swiglu_walks_several_tiles_per_workgroup(cfg, M, N, K):
-    """More tiles than compute units: with a workspace (its ticket counters) the SiLU*mul form of
-    the ping-pong kernel walks them, a workgroup drawing two to four tiles in turn with the next
-    tile's first K step copied during the last step of the current one.  Odd and even numbers of K
-    steps (the stage that holds step 0 alternates or not), a single K step (no walk: one workgroup
-    per tile), a ragged last tile row; every element against the definition, twice in a row (the
-    first launch must leave the counters zero), and the same bits without a workspace."""
+    """More tiles than compute units on 256- and 192-row four-wave tiles, SiLU*mul: a workgroup takes two to four
+    tiles in turn, the next tile's first K steps copied during the last of the current one.  K of one to four
+    steps, a ragged last tile row; every element against the definition, with a workspace (flags left at
+    zero) and without, twice in a row, from the K-step-major weight, and into rows that are not 16-byte aligned
+    (the 128x128 tile then): the same bits."""
     rng = np.random.default_rng(cfg * 1000 + M + N + K)
     ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
     A = _rand_bf16(rng, (M, K))
@@ -121,8 +120,7 @@ def test_gemm_swiglu_walks_several_tiles_per_workgroup(cfg, M, N, K):
     torch.cuda.synchronize()
     _assert_bf16_close(_f64(Cout), ref, 1.0, "gemm swiglu, tile walk")
     assert int(ws[-4096:].view(torch.int32).abs().sum()) == 0        # flags and counters back at zero
-    # again; the K-step-major weight; an output whose rows are not 16-byte aligned (direct stores);
-    # no workspace (one workgroup per tile)
+    # again; the K-step-major weight; no workspace; an output whose rows are not 16-byte aligned
     Wb = torch.empty_like(W)
     B.lazyllm_op_pack_weight_ksteps(W, N, K, K, Wb)
     outs = []
@@ -143,7 +141,7 @@ def test_gemm_swiglu_walks_several_tiles_per_workgroup(cfg, M, N, K):
 @pytest.mark.parametrize("M,N,K", [(2111, 7680, 64), (2111, 7680, 192), (2200, 7680, 128), (300, 256, 320), (48, 768, 704)])
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 def test_gemm_four_wave_tile_runs_through_its_pieces(M, N, K, epi):
-    """The 256x256 tile on four waves of 128x128 (forced): up to 270 tiles on 256 persistent workgroups,
+    """The four-wave tiles of 256, 192 and 128 rows (forced): up to 510 tiles on 256 persistent workgroups,
     whose copies of the next tile's first steps ride in the last steps of this one; K of one, two, three
     and more steps (the ring of five slots wraps inside a tile and across tiles); last tile rows with
     idle waves and with ragged blocks.  Data-parallel: the bits of the 128x128 tile, whose sums run in
@@ -166,9 +164,9 @@ def test_gemm_four_wave_tile_runs_through_its_pieces(M, N, K, epi):
         assert bool((guard[M:] == 7.0).all())               # nothing past the last row
         return Cout
 
-    small, whole, cut, again = run(2), run(5), run(9), run(9)
-    assert torch.equal(small, whole)
-    assert torch.equal(cut, again)
+    whole = run(2)
+    for cfg in (5, 7, 15):
+        assert torch.equal(whole, run(cfg)), cfg
     acc = _f64(A) @ _f64(W).T
     if epi == B.EPI_SWIGLU:
         blocks = acc.reshape(M, N // 64, 2, 32)
@@ -176,7 +174,10 @@ def test_gemm_four_wave_tile_runs_through_its_pieces(M, N, K, epi):
     else:
         ref = acc + (_f64(R) if epi == B.EPI_RESIDUAL else 0.0)
     _assert_bf16_close(_f64(whole), ref, 1.0, "four-wave tile")
-    _assert_bf16_close(_f64(cut), ref, 1.0, "four-wave tile, stream-K")
+    for cfg in (9, 10, 16):
+        cut = run(cfg)
+        _assert_bf16_close(_f64(cut), ref, 1.0, "four-wave tile, stream-K, %d" % cfg)
+        assert torch.equal(cut, run(cfg)), cfg
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 256, 64), (229, 768, 256), (700, 1536, 704), (355, 512, 128), (130, 256, 1408)])
@@ -246,7 +247,9 @@ def test_gemm_skinny_streamed_weight_layout(M, N, K, epi):
 @pytest.mark.parametrize("cfg,M,N,K", [(2, 300, 768, 256), (3, 229, 1536, 704), (4, 130, 512, 192), (5, 513, 1536, 704),
                                        (7, 700, 768, 1408), (6, 355, 4096, 1408), (0, 2100, 6144, 512), (0, 37, 256, 128),
                                        (13, 229, 1536, 704), (13, 77, 512, 128), (13, 300, 768, 64), (13, 640, 1024, 192),
-                                       (14, 513, 1536, 704), (14, 300, 768, 64), (14, 1, 256, 128), (14, 700, 2048, 1408)])
+                                       (14, 513, 1536, 704), (14, 300, 768, 64), (14, 1, 256, 128), (14, 700, 2048, 1408),
+                                       (15, 513, 1536, 704), (15, 1, 256, 128), (9, 513, 1536, 704), (10, 700, 2048, 1408),
+                                       (16, 513, 1536, 704), (16, 300, 768, 64)])
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 def test_gemm_k_step_major_weight_layout(cfg, M, N, K, epi):
     """The weight stored K-step-major (lazyllm_op_pack_weight_ksteps, the form the model keeps) must
@@ -366,16 +369,22 @@ def test_gemm_stream_k(M, N, K, epi):
     assert torch.equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("epi,M,N,K", [(B.EPI_SWIGLU, 355, 22016, 256), (B.EPI_SWIGLU, 450, 22016, 128),
-                                       (B.EPI_SWIGLU, 600, 22016, 192), (B.EPI_SWIGLU, 1000, 22016, 128),
-                                       (B.EPI_RESIDUAL, 600, 4096, 512), (B.EPI_RESIDUAL, 861, 4096, 512),
-                                       (B.EPI_RESIDUAL, 861, 4096, 8192), (B.EPI_STORE, 700, 12288, 256),
-                                       (B.EPI_RESIDUAL, 600, 4096, 1088), (B.EPI_RESIDUAL, 861, 4096, 1088)])
-def test_gemm_library_choice_with_a_workspace(epi, M, N, K):
-    """With a workspace the library may choose the persistent stream-K schedule on its own: gate/up
-    with a last round two thirds empty (172 or 344 tiles of either height), the O and down
-    projections at 64 - 127 aligned tiles (K above 1024), a last round 0.4 or more empty.  Every element against the
-    definition, the same bits twice, flags back at zero."""
+@pytest.mark.parametrize("epi,M,N,K,cfg", [(B.EPI_SWIGLU, 355, 22016, 256, 7), (B.EPI_SWIGLU, 450, 22016, 128, 2),
+                                           (B.EPI_SWIGLU, 600, 22016, 192, 15), (B.EPI_SWIGLU, 1000, 22016, 128, 15),
+                                           (B.EPI_RESIDUAL, 600, 4096, 512, 2), (B.EPI_RESIDUAL, 861, 4096, 512, 2),
+                                           (B.EPI_RESIDUAL, 861, 4096, 8192, 10), (B.EPI_STORE, 700, 12288, 256, 7),
+                                           (B.EPI_RESIDUAL, 600, 4096, 1088, 2), (B.EPI_RESIDUAL, 861, 4096, 1088, 2),
+                                           (B.EPI_SWIGLU, 861, 5120, 4096, 9), (B.EPI_SWIGLU, 257, 5120, 4096, 10),
+                                           (B.EPI_SWIGLU, 257, 2048, 4096, 16), (B.EPI_RESIDUAL, 2100, 2048, 8192, 9),
+                                           (B.EPI_RESIDUAL, 257, 8192, 4096, 10), (B.EPI_RESIDUAL, 400, 4096, 4096, 16),
+                                           (B.EPI_STORE, 700, 4096, 4096, 10), (B.EPI_STORE, 861, 2048, 4096, 16),
+                                           (B.EPI_RESIDUAL, 969, 768, 2048, 6), (B.EPI_RESIDUAL, 6000, 768, 2048, 15),
+                                           (B.EPI_SWIGLU, 5000, 2816, 512, 5)])
+def test_gemm_library_choice_with_a_workspace(epi, M, N, K, cfg):
+    """With a workspace the library takes whole tiles or shares out the K steps of the last round, by the
+    estimated times: every form, named by the plan.  Every element against the definition, the
+    same bits twice, flags back at zero."""
+    assert B.lib().lazyllm_op_gemm_plan(M, N, K, epi, 0, 1) == cfg
     rng = np.random.default_rng(epi * 977 + M + N + K)
     A = _rand_bf16(rng, (M, K))
     W = _rand_bf16(rng, (N, K), 1.0 / math.sqrt(K))
@@ -402,13 +411,13 @@ def test_gemm_library_choice_with_a_workspace(epi, M, N, K):
     assert torch.equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("cfg", [9, 10])
+@pytest.mark.parametrize("cfg", [9, 10, 16])
 @pytest.mark.parametrize("M,N,K", [(1, 256, 64), (300, 768, 256), (2364, 4096, 1024), (1182, 4096, 4096),
                                    (3376, 2048, 512), (700, 22016, 256), (5000, 256, 128), (8192, 8192, 128),
                                    (600, 4096, 512), (1000, 4096, 704), (1536, 4096, 256)])
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 def test_gemm_persistent_stream_k(cfg, M, N, K, epi):
-    """The persistent stream-K schedule of the ping-pong tiles (forced): shapes with fewer tiles than
+    """The stream-K schedule of the four-wave tiles (forced): shapes with fewer tiles than
     CUs (every tile cut into several K pieces; 48, 64, 80 and 96 tiles of 256 rows take a grid of five,
     four, three and two workgroups per tile), with whole data-parallel rounds plus a cut remainder,
     with exactly whole rounds, and a single K step.  Same result as the plain product up to the order
@@ -437,7 +446,7 @@ def test_gemm_persistent_stream_k(cfg, M, N, K, epi):
         outs.append(Cout)
         tail = ws[-4096:].view(torch.int32)
         assert int(tail.abs().sum().item()) == 0          # flags consumed and reset, no wait given up
-    _assert_bf16_close(_f64(outs[0]), ref, 1.0, "gemm persistent stream-K")
+    _assert_bf16_close(_f64(outs[0]), ref, 1.0, "gemm, four-wave stream-K")
     assert torch.equal(outs[0], outs[1])
 
 
@@ -477,12 +486,12 @@ def test_gemm_with_rmsnorm_folded_in(M, N, K, epi):
 
 
 @pytest.mark.parametrize("cfg,M,N,K", [(5, 1100, 22016, 192), (5, 2100, 22016, 128), (7, 1000, 22016, 192),
-                                       (0, 1182, 22016, 256), (0, 355, 22016, 128)])
+                                       (0, 1182, 22016, 256), (0, 355, 22016, 128), (15, 1000, 22016, 192), (9, 1100, 22016, 192),
+                                       (10, 1000, 16384, 256), (16, 355, 4096, 704)])
 def test_gemm_swiglu_tile_walk_with_rmsnorm_folded_in(cfg, M, N, K):
     """The SiLU*mul GEMM in the form the prefill launches it -- RMSNorm's row scale folded into the
-    epilogue, a workspace, more tiles than compute units -- where a workgroup fetches the row
-    scales of its NEXT tile during the last K step of the current one (and, at 355 rows, under the
-    persistent stream-K schedule).  Every element against the definition, same bits twice."""
+    epilogue, a workspace -- on every form of the four-wave tile and as the library chooses: a workgroup fetches
+    the row scales of each of its tiles or pieces anew.  Every element against the definition, same bits twice."""
     rng = np.random.default_rng(cfg * 31 + M + N + K)
     A = _rand_bf16(rng, (M, K), 0.7)
     A[: M // 2] *= 3.0                                    # row scales that differ from tile to tile
@@ -502,7 +511,7 @@ def test_gemm_swiglu_tile_walk_with_rmsnorm_folded_in(cfg, M, N, K):
         torch.cuda.synchronize()
         assert int(ws[-4096:].view(torch.int32).abs().sum()) == 0
         outs.append(Cout)
-    _assert_bf16_close(_f64(outs[0]), ref, 1.0, "gemm+rmsnorm, tile walk")
+    _assert_bf16_close(_f64(outs[0]), ref, 1.0, "gemm+rmsnorm, several tiles")
     assert torch.equal(outs[0], outs[1])
 
 

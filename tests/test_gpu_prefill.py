@@ -343,6 +343,23 @@ def test_packed_batch_on_the_four_wave_qkv_tiles(heads, hd):
     model.close()
 
 
+@pytest.mark.parametrize("d,kv_heads,n,cfg", [(3072, 8, 650, 16), (3072, 8, 1000, 10), (4096, 32, 1960, 9)])
+def test_qkv_projection_whose_tiles_are_cut_over_k(d, kv_heads, n, cfg):
+    """The rotary epilogue behind a tile's added pieces, in the three heights of the four-wave tile: every K and V
+    of the layer, and through its attention q and transposed V."""
+    shape = synth.ModelShape(1, d, d // 128, 128, 256, 256, n_kv_heads=kv_heads)
+    assert B.lib().lazyllm_op_gemm_plan(n, d + 2 * kv_heads * 128, d, 3, 128, 3) == cfg
+    w = synth.make_weights(shape, 1061 + cfg, "cpu", gain_jitter=0.3)
+    model = B.Model(shape.as_dict(), _to_dev(w), DEV)
+    ids = synth.make_prompt(n, shape.vocab, 770 + cfg)
+    out = _run(model, ids, [])
+    assert out.status == 0
+    check_against_checker(shape, synth.weights_to_host_bits(w), ids, [], out, tol=FEW_ROWS_TOL, verbose="QKV cut over K, %d" % cfg)
+    again = _run(model, ids, [])
+    assert torch.equal(out.logits, again.logits) and torch.equal(out.k(0), again.k(0)) and torch.equal(out.v(0), again.v(0))
+    model.close()
+
+
 def test_few_rows_folded_compaction_gives_the_same_bits(few_rows_model):
     """Row indirection of the A operand and of the residual in the streaming kernel, 300 -> 90 rows."""
     shape, _, model = few_rows_model
