@@ -574,14 +574,12 @@ int lazyllm_prefill_varlen(const lazyllm_model* m, const int32_t* token_ids,
     // One projection: the 16-bit GEMM, or in the 8-bit variant the row quantiser on the operand
     // followed by the 8-bit GEMM with the same epilogue (both in the step's timing).
     auto project = [&](const void* A, int K, const void* w16, const void* ws16, const void* w8, const float* sw8,
-                       void* Cout, const void* R, int N, int ldc, int epi, const EpiArgs* ea,
-                       bool stream_k) -> hipError_t {
+                       void* Cout, const void* R, int N, int ldc, int epi, const EpiArgs* ea) -> hipError_t {
       if (c->gemm_dtype == 0) {
         EpiArgs eb = *ea;
         eb.w_blocked = 1;                            // the model's 16-bit weights are K-step-major
         eb.w_stream = ws16;                          // ... and, for few rows, sequential streams
         eb.psk_ready = 1;                            // (flags cleared at the start of this call)
-        (void)stream_k;
         return launch_gemm(A, w16, Cout, R, n, N, K, K, K, ldc, epi, st, &eb, W + ws.gemm_ws,
                            gemm_workspace_bytes());
       }
@@ -622,7 +620,7 @@ int lazyllm_prefill_varlen(const lazyllm_model* m, const int32_t* token_ids,
                                    cu_vt + s * BW, 0, B, (int)stg.vt_ld[s], kvd, st));
     LZ_RUN(LAZYLLM_STEP_GEMM_QKV, l, n, 2.0 * n * (dd + 2.0 * kvd) * dd,
            project(h, d, m->wqkv[l], m->wqkv_s[l], f8 ? m->wqkv8[l] : nullptr, f8 ? m->sqkv[l] : nullptr, nullptr,
-                   nullptr, d + 2 * kvd, 0, EPI_QKV_ROPE, &ra, false));
+                   nullptr, d + 2 * kvd, 0, EPI_QKV_ROPE, &ra));
     // Eq. 1 needs the last query's logits against every key, which the attention kernel has
     // in registers anyway: it leaves them in the score scratch (the gate/up launch below turns
     // them into the head-averaged probabilities).
@@ -638,13 +636,13 @@ int lazyllm_prefill_varlen(const lazyllm_model* m, const int32_t* token_ids,
     eo.r_rows = rows_of_h;
     if (rows_of_h != nullptr) {                     // residual rows through the index, output compact
       LZ_RUN(LAZYLLM_STEP_GEMM_O, l, n, 2.0 * n * dd * dd,
-             project(W + ws.o, d, m->wo[l], m->wo_s[l], nullptr, nullptr, hbuf[cur ^ 1], h, d, d, EPI_RESIDUAL, &eo, true));
+             project(W + ws.o, d, m->wo[l], m->wo_s[l], nullptr, nullptr, hbuf[cur ^ 1], h, d, d, EPI_RESIDUAL, &eo));
       cur ^= 1;
       h = hbuf[cur];
     } else {
       LZ_RUN(LAZYLLM_STEP_GEMM_O, l, n, 2.0 * n * dd * dd,
              project(W + ws.o, d, m->wo[l], m->wo_s[l], f8 ? m->wo8[l] : nullptr, f8 ? m->so[l] : nullptr, h, h, d, d,
-                     EPI_RESIDUAL, &eo, true));
+                     EPI_RESIDUAL, &eo));
     }
     EpiArgs eg{};
     eg.ssq_in = ssq_ffn; eg.ssq_mul = ssq_mul; eg.eps = c->rms_eps; eg.ssq_clear = ssq_attn;
@@ -660,12 +658,12 @@ int lazyllm_prefill_varlen(const lazyllm_model* m, const int32_t* token_ids,
     }
     LZ_RUN(LAZYLLM_STEP_GEMM_GATE_UP, l, n, 2.0 * n * 2.0 * (double)c->d_ffn * dd,
            project(h, d, m->wgu[l], m->wgu_s[l], f8 ? m->wgu8[l] : nullptr, f8 ? m->sgu[l] : nullptr, W + ws.act,
-                   nullptr, 2 * fp, fp, EPI_SWIGLU, &eg, false));
+                   nullptr, 2 * fp, fp, EPI_SWIGLU, &eg));
     EpiArgs ed{};
     ed.ssq_out = ssq_attn;
     LZ_RUN(LAZYLLM_STEP_GEMM_DOWN, l, n, 2.0 * n * (double)c->d_ffn * dd,
            project(W + ws.act, fp, m->wdown[l], m->wdown_s[l], f8 ? m->wdown8[l] : nullptr, f8 ? m->sdown[l] : nullptr,
-                   h, h, d, d, EPI_RESIDUAL, &ed, true));
+                   h, h, d, d, EPI_RESIDUAL, &ed));
   }
   const int s_last = stg.stage_of_layer[L - 1];
   if (flags & LAZYLLM_KEEP_HIDDEN) {

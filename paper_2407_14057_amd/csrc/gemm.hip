@@ -1,9 +1,10 @@
 // bf16 GEMM on the gfx950 matrix cores: C[M,N] = A[M,K] W[N,K]^T, fp32 accumulation.
 // Both operands are K-contiguous, which is the layout the MFMA instructions want: lane l of
-// v_mfma_f32_32x32x16_bf16 supplies row (l & 31), k elements 8*(l >> 5) .. +8 of a 32x16 operand
-// block, of v_mfma_f32_16x16x32_bf16 row (l & 15), k elements 8*(l >> 4) .. +8 of a 16x32 block.
+// v_mfma_f32_32x32x16_bf16 supplies row (l & 31), k elements 8*(l >> 5) .. +8 of a 32x16 operand block.
+// This file: the 128-row tiles for small shapes, 128x128 stream-K, and the choice among all kernels (the
+// four-wave tiles of gemm_w4.h, the streaming kernel of gemm_stream.hip).
 //
-// Workgroup = WM x WN waves, each wave owns TM x TN blocks of 32x32 or 16x16 (fp32 accumulators stay
+// Workgroup = WM x WN waves, each wave owns TM x TN blocks of 32x32 (fp32 accumulators stay
 // in registers for the whole K loop).  K advances 64 elements per step; the A and W slabs of
 // a step are copied global -> LDS by global_load_lds (no register staging) into one of two
 // LDS stages while the other stage feeds the MFMAs.
@@ -591,6 +592,9 @@ int gemm_band_height(int M, int epilogue) {
   //   QKV (48 column blocks)      1182 rows: 1: 116, 5: 107;  3376 rows: 1: 301, 3..6: 289-292, 14: 301
   //                               4916 rows: 3: 401, 5: 402, 16: 420;  8192 rows: 2: 652, 4: 630, 5: 636, 32: 715
   //   O and down projections: within 1 % from 3 to 8 (4 kept).
+  //   packed batches              gate/up 14528 rows: 2: 1845, 3: 1840, 4: 1842, 8: 1855;  29053 rows: 2: 3631, 3: 3604,
+  //                               4: 3629, 8: 3680;  41499 rows: 2: 5170, 3: 5180, 4: 5215, 5: 5185, 8: 5281
+  //                               QKV 14528 rows: 2: 1098, 4: 1085, 8: 1108;  41499 rows: 2: 3117, 3: 3095, 4: 3133, 8: 3181
   // So: column by column below 8 tile rows, about half the tile rows up to 16 of them, 4 beyond.
   const int tm256 = (M + 255) / 256;
   const int tall = tm256 <= 11 ? 5 : tm256 <= 16 ? 7 : 4;
