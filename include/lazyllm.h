@@ -213,7 +213,12 @@ int lazyllm_prefill(const lazyllm_model* m, const int32_t* token_ids, const floa
  * strictly increasing.  cu_seqlens_dev: the same values in device memory (may be NULL when
  * batch == 1).  Every buffer, launch and row table follows the host copy; the device copy is only
  * compared with it on the GPU, and a difference sets LAZYLLM_ST_BAD_CU in *status (the result is
- * then the one the host copy describes). */
+ * then the one the host copy describes).  The same call gives the same bits every time.  A prompt of a
+ * batch has the bits it gets alone only where its sums run in the same order: the number of packed rows
+ * chooses the tiles of the projections, 16- and 8-bit ones alike, and how a tile's K steps are shared out
+ * (lazyllm_op_gemm_plan, lazyllm_op_gemm_fp8_plan), and the batch chooses the form of the attention
+ * (lazyllm_op_attention_block).  Otherwise the two differ by the rounding of their sums, and a token
+ * next to a selection threshold can be kept in one and not in the other. */
 int lazyllm_prefill_varlen(const lazyllm_model* m, const int32_t* token_ids,
                            const float* embed_scale, const int32_t* cu_seqlens_host,
                            const int32_t* cu_seqlens_dev, int32_t batch, const lazyllm_keep* sched,
