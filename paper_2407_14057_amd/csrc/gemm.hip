@@ -589,7 +589,8 @@ int gemm_band_height(int M, int epilogue) {
   //                               3376 rows: 2: 486, 4..6: 479, 7: 472, 14: 482
   //                               4916 rows: 2: 671, 4: 653, 5: 654, 16: 669;  8192 rows: 2: 1076, 3: 1068,
   //                               4: 1049, 5: 1055, 8: 1048, 32: 1114
-  //   QKV (48 column blocks)      1182 rows: 1: 116, 5: 107;  3376 rows: 1: 301, 3..6: 289-292, 14: 301
+  //   QKV (48 column blocks; up to 8192 rows with an epilogue that was 3 % slower)
+  //                               1182 rows: 1: 116, 5: 107;  3376 rows: 1: 301, 3..6: 289-292, 14: 301
   //                               4916 rows: 3: 401, 5: 402, 16: 420;  8192 rows: 2: 652, 4: 630, 5: 636, 32: 715
   //   O and down projections: within 1 % from 3 to 8 (4 kept).
   //   packed batches              gate/up 14528 rows: 2: 1845, 3: 1840, 4: 1842, 8: 1855;  29053 rows: 2: 3631, 3: 3604,
@@ -612,6 +613,8 @@ int gemm_band_height(int M, int epilogue) {
 //   * stream-K: the whole rounds, then the remaining tiles' steps shared out evenly; the exchange costs a
 //     fixed part, a part for every piece the owner of a tile adds, and more when the pieces do not
 //     align with tiles (a workgroup then has two pieces), the fewer tiles the more.
+// (256 compute units, the whole part; where the runtime reports fewer the launcher's grid follows it and only the
+// estimate is off.)
 // Slower than the eight-wave tiles that stood here before: launches of about one round with K up to 1024,
 // where the end of a tile on one wave per SIMD is not hidden (QKV 6384 x 2304 x 768 32 / 35 us, 9395 x 1536 x 512
 // 27 / 29, 4188 x 3072 x 1024 35 / 38; residual 13264 x 1024 x 1024 36 / 39).

@@ -1,7 +1,7 @@
 // bf16 GEMM, tile of 32*TM x 256 (TM = 8: 256 rows) on FOUR waves, one per SIMD, each holding a
 // 16*TM x 128 block of the product: 8*TM accumulator blocks of 16x16 = 256 registers, the
-// accumulation half of the 512-register file that a lone wave of a SIMD has.  Against the 8-wave
-// ping-pong form (two waves per SIMD, 64x128 each) a wave reads 16 operand fragments from LDS per
+// accumulation half of the 512-register file that a lone wave of a SIMD has.  Against a tile on eight
+// waves (two per SIMD, 64x128 each) a wave reads 16 operand fragments from LDS per
 // 64 MFMAs instead of 12 per 32 -- a third less LDS traffic per FLOP, i.e. less of the power that
 // sets this part's clock -- and there is one workgroup barrier per K step instead of four.
 //
@@ -24,7 +24,7 @@
 // the ring that is free just then (the W slab of the last step) and that only this wave's own copies
 // refill, so the epilogue needs no barrier and the waves of a workgroup may drift through it.
 //
-// Measured, cold weights, against the ping-pong form on the same MFMAs (us): 8192 rows QKV 663 -> 603, O
+// Measured, cold weights, against a tile on eight waves and the same MFMAs (us): 8192 rows QKV 663 -> 603, O
 // 233 -> 205, gate/up 1154 -> 1013 (1.46 PFLOP/s), down 605 -> 504; 3376 rows gate/up 497 -> 441, down
 // 247 -> 228.  A K step takes 1.38 us (1.55 PFLOP/s at the clock the power limit leaves); the rest is the
 // residual read and the stores of all CUs at once: without them O takes 196, gate/up 988.
