@@ -203,10 +203,11 @@ hipError_t launch_gemm(const void* A, const void* W, void* C, const void* R, int
                        int lda, int ldw, int ldc, int epilogue, hipStream_t st,
                        const EpiArgs* rope = nullptr, void* sk_ws = nullptr, size_t sk_ws_bytes = 0);
 
-// Whether a launch's rows can leave in 16-byte chunks: the destinations of the epilogue (and the residual).
-inline bool rows_in_16_byte_chunks(int epilogue, const void* C, const void* R, int ldc, const EpiArgs& ra) {
-  if (epilogue == EPI_QKV_ROPE) return (((uintptr_t)ra.q | (uintptr_t)ra.k | (uintptr_t)ra.v) & 15) == 0;
-  return ldc % 8 == 0 && (((uintptr_t)C | (uintptr_t)R) & 15) == 0;
+// Whether the rows that a launch's epilogue writes (and the residual rows) start on boundaries of so many bytes.
+inline bool rows_on_boundaries(int bytes, int epilogue, const void* C, const void* R, int ldc, const EpiArgs& ra) {
+  const uintptr_t mask = (uintptr_t)bytes - 1;
+  if (epilogue == EPI_QKV_ROPE) return (((uintptr_t)ra.q | (uintptr_t)ra.k | (uintptr_t)ra.v) & mask) == 0;
+  return ldc % (bytes / 2) == 0 && (((uintptr_t)C | (uintptr_t)R) & mask) == 0;
 }
 // The 256x256 tile on four waves of 128x128, one per SIMD (gemm_w4.h); N % 256 == 0.  stream_k: with
 // the K steps of the last round's tiles shared out (part, flags: see there).

@@ -347,8 +347,8 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
       return hipErrorInvalidValue;
   }
   const int tiles_n = N / BN, tiles_m = (M + BM - 1) / BM;
-  // Outputs that the four-wave kernel's 16-byte stores cannot address stay here, forced configuration or not.
-  const bool w4_ok = rows_in_16_byte_chunks(epilogue, C, R, ldc, ea);
+  // Outputs that are not on 8-byte boundaries stay here, forced configuration or not.
+  const bool w4_ok = rows_on_boundaries(8, epilogue, C, R, ldc, ea);
   const bool sk_ok = ea.psk_ready && sk_ws != nullptr && sk_ws_bytes >= gemm_workspace_bytes();
   if (cfg == 0 || !w4_ok) cfg = gemm_f8_config(M, N, K, epilogue, w4_ok, sk_ok);
   if (cfg == 5 || cfg == 7 || cfg == 15)
@@ -366,7 +366,7 @@ hipError_t launch_gemm_f8(const void* A, const float* sa, const void* W, const f
   ea.sf_blocks_per_seq = (ea.sf_max_rows + 511) / 512;
   ea.stage_out = (epilogue == EPI_QKV_ROPE)
                      ? (ea.d_model % BN == 0 && (ea.kv_dim > 0 ? ea.kv_dim : ea.d_model) % BN == 0 &&
-                        rows_in_16_byte_chunks(epilogue, C, R, ldc, ea))
+                        rows_on_boundaries(16, epilogue, C, R, ldc, ea))
                      : (epilogue != EPI_SWIGLU && ldc % 8 == 0 && ((uintptr_t)C & 15) == 0);
   const int side = ea.sf_z != nullptr ? ea.sf_blocks_per_seq * ea.sf_batch : 0;
   const int group_m = tiles_m < 16 ? tiles_m : 16;

@@ -60,6 +60,7 @@ constexpr unsigned W4_SPIN_LIMIT = 1u << 22;       // about a second of polling
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef int v8i_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef u32x4_t u32x4_at_8_t __attribute__((aligned(8)));
 typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
 typedef u16x8_t u16x8_at_2_t __attribute__((aligned(2)));
 constexpr int W4_SLOT = 256 * ROW_BYTES;
@@ -463,7 +464,7 @@ gemm_w4_kernel(const char* __restrict__ A, const char* __restrict__ W, const flo
         int r = row0 + i * 16 + s * RPI + srow;
         r = r < M ? r : M - 1;
         if (ra.r_rows != nullptr) r = ra.r_rows[r];
-        rr[i % RAHEAD][s] = *(const u32x4_t*)(R + (size_t)r * ldc + col0 + schunk * 8);
+        rr[i % RAHEAD][s] = *(const u32x4_at_8_t*)(R + (size_t)r * ldc + col0 + schunk * 8);
       }
     };
     if (EPI == EPI_RESIDUAL) {
@@ -584,11 +585,11 @@ gemm_w4_kernel(const char* __restrict__ A, const char* __restrict__ W, const flo
 #pragma unroll
         for (int s = 0; s < NST; ++s) {
           const int r = s * RPI + srow;
-          const uint4 v = *(const uint4*)(sl + stage_at(r, schunk * 8));
+          const u32x4_t v = *(const u32x4_t*)(sl + stage_at(r, schunk * 8));
           const int orow = row0 + i * 16 + r;
           if (orow < M) {
             const size_t dr = (ROPE && region == 1 && ra.k_row != nullptr) ? (size_t)ra.k_row[orow] : (size_t)orow;
-            *(uint4*)(obase + dr * old + schunk * 8) = v;
+            *(u32x4_at_8_t*)(obase + dr * old + schunk * 8) = v;
           }
         }
       }
@@ -666,8 +667,7 @@ static hipError_t launch_w4(const void* A, const float* sa, const void* W, const
       (unsigned long long)N * (ra.w_blocked ? K : ldw) * ESIZE >= (1ull << 32))
     return hipErrorInvalidValue;
   if (stream_k && (part == nullptr || flags == nullptr || K > (1 << 24))) return hipErrorInvalidValue;
-  // rows leave in 16-byte chunks
-  if (!rows_in_16_byte_chunks(epi, C, R, ldc, ra)) return hipErrorInvalidValue;
+  if (!rows_on_boundaries(8, epi, C, R, ldc, ra)) return hipErrorInvalidValue;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN, KT = K / (ROW_BYTES / ESIZE);
   EpiArgs ea = ra;
   ea.w_step_bytes = ra.w_blocked ? (unsigned long long)N * ROW_BYTES : (unsigned long long)ROW_BYTES;

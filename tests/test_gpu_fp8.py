@@ -223,6 +223,36 @@ def test_gemm_fp8_every_form(M, N, K, epi):
         assert torch.equal(got, run(cfg, wb, 1 << 29)), cfg
 
 
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
+def test_gemm_fp8_into_rows_on_8_byte_boundaries(epi):
+    """A row stride of a multiple of four elements: every form of the four-wave tile gives the bits of aligned rows and
+    writes nothing between them."""
+    M, N, K = 700, 1536, 1408
+    rng = np.random.default_rng(91 + epi)
+    ac, sa = F.quantize_rows(rng.normal(0, 1, (M, K)).astype(np.float32))
+    wc, sw = F.quantize_rows(rng.normal(0, 1 / math.sqrt(K), (N, K)).astype(np.float32))
+    a_d, w_d, sa_d, sw_d = (torch.from_numpy(t).to(DEV) for t in (ac, wc, sa, sw))
+    R = _bf16_dev(rng.normal(0, 1, (M, N)))
+    ncols = N // 2 if epi == B.EPI_SWIGLU else N
+    ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
+
+    def run(cfg, ldc):
+        rows = torch.full((M, ldc), 7.0, dtype=torch.bfloat16, device=DEV)
+        if epi == B.EPI_RESIDUAL:
+            rows[:, :ncols] = R
+        B.lazyllm_op_gemm_fp8(a_d, sa_d, w_d, sw_d, rows, rows if epi == B.EPI_RESIDUAL else None, M, N, K, K, K, ldc,
+                              epi | (cfg << 8), workspace=ws)
+        torch.cuda.synchronize()
+        assert bool((rows[:, ncols:] == 7.0).all())
+        return rows[:, :ncols].clone()
+
+    for cfg in (5, 7, 15, 9, 10, 16):
+        aligned = run(cfg, ncols)
+        # (with a residual the bits tell the kernels apart: scaling and addition are one rounding or two)
+        assert epi != B.EPI_RESIDUAL or not torch.equal(aligned, run(2, ncols)), cfg
+        assert torch.equal(aligned, run(cfg, ncols + 4)), cfg
+
+
 @pytest.mark.parametrize("M,N,K", [(37, 256, 384), (300, 768, 1024), (2100, 768, 256)])
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
 def test_gemm_fp8_k_step_major_codes(M, N, K, epi):

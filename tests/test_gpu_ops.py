@@ -106,8 +106,8 @@ def test_gemm_swiglu_walks_several_tiles_per_workgroup(cfg, M, N, K):
     """More tiles than compute units on 256- and 192-row four-wave tiles, SiLU*mul: a workgroup takes two to four
     tiles in turn, the next tile's first K steps copied during the last of the current one.  K of one to four
     steps, a ragged last tile row; every element against the definition, with a workspace (flags left at
-    zero) and without, twice in a row, from the K-step-major weight, and into rows that are not 16-byte aligned
-    (the 128x128 tile then): the same bits."""
+    zero) and without, twice in a row, from the K-step-major weight, and into rows on 8-byte boundaries: the
+    same bits."""
     rng = np.random.default_rng(cfg * 1000 + M + N + K)
     ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
     A = _rand_bf16(rng, (M, K))
@@ -178,6 +178,37 @@ def test_gemm_four_wave_tile_runs_through_its_pieces(M, N, K, epi):
         cut = run(cfg)
         _assert_bf16_close(_f64(cut), ref, 1.0, "four-wave tile, stream-K, %d" % cfg)
         assert torch.equal(cut, run(cfg)), cfg
+
+
+@pytest.mark.parametrize("cfg", [5, 7, 15, 9, 10, 16])
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESIDUAL, B.EPI_SWIGLU])
+def test_gemm_four_wave_tile_into_rows_on_8_byte_boundaries(cfg, epi):
+    """A row stride that is a multiple of four elements only, and a first row on an 8-byte boundary: every form of the
+    four-wave tile serves them (under stream-K its bits are not those of the 128x128 tile) and gives the bits of
+    aligned rows; nothing is written between the rows.  Rows on 4-byte boundaries take the 128x128 tile."""
+    M, N, K = 700, 1536, 704
+    rng = np.random.default_rng(cfg * 7 + epi)
+    A = _rand_bf16(rng, (M, K)); W = _rand_bf16(rng, (N, K), 1.0 / math.sqrt(K)); R = _rand_bf16(rng, (M, N))
+    ws = torch.empty(B.lazyllm_op_gemm_workspace_bytes(), dtype=torch.uint8, device=DEV)
+    ncols = N // 2 if epi == B.EPI_SWIGLU else N
+
+    def run(cfg, ldc, first):
+        buf = torch.full((M * ldc + 16,), 7.0, dtype=torch.bfloat16, device=DEV)
+        rows = buf[first:first + M * ldc].view(M, ldc)
+        if epi == B.EPI_RESIDUAL:
+            rows[:, :ncols] = R
+        B.lazyllm_op_gemm(A, W, rows, rows if epi == B.EPI_RESIDUAL else None, M, N, K, K, K, ldc, epi | (cfg << 8), workspace=ws)
+        torch.cuda.synchronize()
+        assert int(ws[-4096:].view(torch.int32).abs().sum()) == 0
+        assert bool((rows[:, ncols:] == 7.0).all()) and bool((buf[:first] == 7.0).all()) and bool((buf[first + M * ldc:] == 7.0).all())
+        return rows[:, :ncols].clone()
+
+    aligned = run(cfg, ncols, 0)
+    if cfg in (9, 10, 16):
+        assert not torch.equal(aligned, run(2, ncols, 0))      # (so that the next line tells the two forms apart)
+    for ldc, first in ((ncols + 4, 0), (ncols, 4), (ncols + 12, 12)):
+        assert torch.equal(aligned, run(cfg, ldc, first)), (ldc, first)
+    assert torch.equal(run(2, ncols, 0), run(cfg, ncols + 4, 2))
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 256, 64), (229, 768, 256), (700, 1536, 704), (355, 512, 128), (130, 256, 1408)])
@@ -613,8 +644,7 @@ def test_qkv_rope(rows, H, hd):
 
 @pytest.mark.parametrize("rows,H,hd", [(130, 4, 64), (2100, 8, 128)])
 def test_qkv_rope_to_outputs_on_8_byte_boundaries(rows, H, hd):
-    """q, k and v that 16-byte stores cannot address take a tile that stores 8 bytes: the same bits (every tile adds
-    in the same order), nothing in front of them or behind."""
+    """q, k and v on 8-byte boundaries: the bits of aligned ones, nothing in front of them or behind."""
     rng = np.random.default_rng(rows + H)
     d = H * hd
     x = _rand_bf16(rng, (rows, d))
